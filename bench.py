@@ -52,8 +52,8 @@ WORKLOADS = {
 }
 # 3D: three launches per subiteration (the penalty gradient and mu run as
 # extra blocks of the back-projector's launch)
-KERNELS = {0: "k_fp3 (forward projection + Poisson ratio)",
-           1: "k_bp3 (back-projection; RDP gradient and mu blocks in the same launch)",
+KERNELS = {0: "k_fp3q (forward projection + Poisson ratio)",
+           1: "k_bp3q (back-projection; RDP gradient and mu blocks in the same launch)",
            2: "k_upd3 (G = b + (beta/M) grad R, nu, S, relaxed step, P_t; z-fastest copy)"}
 # 2D: two launches per subiteration (the update is fused into the back-projection)
 KERNELS_2D = {0: "k_fp_px (forward projection + Poisson ratio; snapshot of f and mu)",
@@ -68,7 +68,7 @@ def kernel_source_hash():
     stored traffic measurement stays valid across comment-only edits."""
     import re
     h = hashlib.sha256()
-    for name in ("kernels.hip", "kernels3d.hip", "devutil.h", "raygeom.h"):
+    for name in ("kernels.hip", "kernels3d.hip", "kernels3q.hip", "pen3.h", "devutil.h", "raygeom.h"):
         with open(os.path.join(ROOT, "paper_2111_07886_amd", "csrc", name), encoding="utf-8") as fh:
             src = fh.read()
         src = re.sub(r"/\*.*?\*/", " ", src, flags=re.S)
@@ -79,7 +79,7 @@ def kernel_source_hash():
 
 # kernel-name prefixes of the per-subiteration launches, by kernel index
 TRAFFIC_KERNELS = {2: {0: "void petos::k_fp_px<", 1: "void petos::k_bp<"},
-                   3: {0: "petos::k_fp3(", 1: "void petos::k_bp3<", 2: "petos::k_upd3("}}
+                   3: {0: "void petos::k_fp3q<", 1: "void petos::k_bp3", 2: "petos::k_upd3("}}
 COPY_BYTES = 64 * 1024 * 1024 * 4      # the --calibrate-copy transfer
 
 

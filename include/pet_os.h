@@ -46,7 +46,7 @@
  *     one device pass over y, r and f followed by a synchronisation of
  *     `stream`; a state makes it when it first sees a (f, y, r) triple of
  *     buffers, not again while the same buffers come back.
- *   - A 3D state (up to 64 rings and 15 ring differences) also copies y and r
+ *   - A 3D state (up to 64 rings) also copies y and r
  *     into a bin-major layout of its own (8 bytes per bin, allocated at the
  *     first subiteration) when it first sees a (y, r) pair of buffers, and
  *     reads the copy while the same pair comes back: new contents in the
@@ -253,8 +253,10 @@ int pet_os_reconstruct(const pet_os_geom* geom, const pet_os_params* params, flo
  * harnesses that forbid hipMalloc): pet_os_reconstruct with obj == NULL, the
  * same kernels and the same result bit for bit, with the request's scratch
  * (subset sinogram, gradient, mu, nu, iterate copy, FP64 partials) placed in
- * a static device array of PET_OS_NOALLOC_SCRATCH_BYTES that every GPU the
- * library runs on holds until the process ends, instead of allocated memory.
+ * a static device array for requests of up to PET_OS_NOALLOC_SCRATCH_BYTES of
+ * scratch (bin by bin; 9/4 of that, for the 3D projectors' own layout) that
+ * every GPU the library runs on holds until the process ends, instead of
+ * allocated memory.
  * It calls no device allocation routine.  Arguments as pet_os_reconstruct;
  * the geometry must belong to the current device.  Errors: INVALID_ARG also
  * when the request's scratch exceeds the array (the message states both

@@ -59,6 +59,7 @@ struct pet_os_batch {
     int* d_counts = nullptr;
     int grids[WL_COUNT] = {};
     int live_mask = 0;               // lists launched by the captured graph
+    size_t bp3q_lds = 0;             // dynamic LDS of the quad back-projection: the largest of the slots'
     bool lists_dirty = true;
     bool graph_ok = false;
     hipStream_t cap_stream = nullptr;
@@ -120,17 +121,25 @@ int rebuild_lists(pet_os_batch* B) {
         }
     }
     std::vector<Item> L[WL_COUNT];
+    size_t bp_lds = 0;
     for (int s = 0; s < B->max_slots; ++s) {
         const BatchSlot& S = B->slots[s];
         if (!S.used) continue;
         const bool d3 = S.g->d.dim == 3;
         // 2D: forward blocks, then the pixel-pass blocks (snapshot, mu)
-        const int nfp = d3 ? fp3_grid(S.g, S.g->max_sub_angles)
-                           : fp_grid_seg(S.g, S.g->max_sub_angles, S.fp_seg) + px_items(S.g);
-        for (int b = 0; b < nfp; ++b) L[d3 ? WL_FP3 : WL_FP].push_back({s, b});
-        const int nbp = d3 ? bp3_grid_batch(S.g) : bp_grid_kind(S.g, S.bp_kind);
+        const bool fq = d3 && fp3q_ok(S.g), quad = d3 && quad_ok(S.g);
+        const int wide = S.g->d.nz > 32 ? 1 : 0;
+        const int nfp = fq ? fp3q_grid(S.g, S.g->max_sub_angles)
+                        : d3 ? fp3_grid(S.g, S.g->max_sub_angles)
+                             : fp_grid_seg(S.g, S.g->max_sub_angles, S.fp_seg) + px_items(S.g);
+        const int wfp = fq ? WL_FP3Q + wide : d3 ? WL_FP3 : WL_FP;
+        for (int b = 0; b < nfp; ++b) L[wfp].push_back({s, b});
+        const int nbp = quad ? bp3q_grid(S.g) : d3 ? bp3_grid_batch(S.g) : bp_grid_kind(S.g, S.bp_kind);
         const int zi = d3 ? (bp3_zb(S.g) == 16 ? 0 : (bp3_zb(S.g) == 32 ? 1 : 2)) : 0;
-        const int wbp = d3 ? WL_BP3 + 2 * zi + (bp3_nbs_of(S.g) == 40 ? 1 : 0) : WL_BP0 + S.bp_kind;
+        const int wbp = quad ? WL_BP3Q + wide
+                        : d3 ? WL_BP3 + 2 * zi + (bp3_nbs_of(S.g) == 40 ? 1 : 0)
+                             : WL_BP0 + S.bp_kind;
+        if (quad) bp_lds = std::max(bp_lds, bp3q_lds(S.g));
         for (int b = 0; b < nbp; ++b) L[wbp].push_back({s, b});
         if (d3) {
             const int npen = pen3_grid(S.g);
@@ -155,9 +164,11 @@ int rebuild_lists(pet_os_batch* B) {
         B->count[k] = n;
         if (n) mask |= 1 << k;
     }
-    // the graph launches only the non-empty lists: capture again when that set changes
-    if (mask != B->live_mask) {
+    // the graph launches only the non-empty lists: capture again when that set
+    // changes or a slot needs more LDS
+    if (mask != B->live_mask || bp_lds > B->bp3q_lds) {
         B->live_mask = mask;
+        B->bp3q_lds = std::max(B->bp3q_lds, bp_lds);
         B->graph_ok = false;
     }
     PETOS_HIP(hipMemcpy(B->d_counts, B->count, sizeof(B->count), hipMemcpyHostToDevice));
@@ -172,7 +183,7 @@ int capture(pet_os_batch* B) {
     for (int k = 0; k < WL_COUNT; ++k) B->grids[k] = 8 * ((std::max(1, std::min(B->cap[k], GRID_CAP)) + 7) / 8);
     PETOS_HIP(hipStreamBeginCapture(B->cap_stream, hipStreamCaptureModeThreadLocal));
     int rc = launch_batch_step(B->d_slots, B->max_slots, B->d_items, B->d_counts, B->grids, B->live_mask,
-                               B->cap_stream);
+                               B->bp3q_lds, B->cap_stream);
     hipGraph_t g = nullptr;
     hipError_t e = hipStreamEndCapture(B->cap_stream, &g);
     if (rc) { if (g) (void)hipGraphDestroy(g); return rc; }
@@ -318,7 +329,11 @@ int pet_os_batch_add(pet_os_batch* B, const pet_os_geom* g, const pet_os_params*
     D.box = make_box(p->U, p->t_clip);
     D.fp_seg = S.fp_seg;
     D.bp_kind = S.bp_kind;
-    if (g->d.dim == 3) {
+    if (g->d.dim == 3 && quad_ok(g)) {
+        D.quad = 1;
+        D.rows_max = bp3q_rows(g);
+        D.chunk = bp3q_buf(g);
+    } else if (g->d.dim == 3) {
         rc = bp3_shape(g, D.nb_max, D.zb, D.rows_max, D.chunk);
         if (rc) { slot_release(S); return rc; }
     } else {

@@ -462,7 +462,9 @@ struct WorkLayout {
     bool need_nu, d3, psf;
 };
 
-static WorkLayout work_layout(const pet_os_geom* g, bool need_nu) {
+// sums: with the partials of the sums over all bins; quads: the subset
+// sinogram in the layout of the geometry's 3D projectors, else bin by bin
+static WorkLayout work_layout(const pet_os_geom* g, bool need_nu, bool sums, bool quads = true) {
     WorkLayout L{};
     Carver cv;
     size_t nv = (size_t)g->n_vox;
@@ -471,7 +473,8 @@ static WorkLayout work_layout(const pet_os_geom* g, bool need_nu) {
     L.psf = g->k.psf_kx > 0;
     // + 4 floats: the 3D back-projector's 16-byte staging loads may read up to
     // three bins past the last row
-    L.o_w = cv.take<float>((size_t)g->max_sub_angles * g->n_planes * g->d.n_radial + 4);
+    const size_t compact = (size_t)g->max_sub_angles * g->n_planes * g->d.n_radial + 4;
+    L.o_w = cv.take<float>(quads && quad_ok(g) ? std::max(compact, quad_floats(g, g->max_sub_angles)) : compact);
     L.o_G = cv.take<float>(nv);
     L.o_mu = cv.take<float>(nv);
     L.o_nu = need_nu ? cv.take<float>(nv) : 0;
@@ -482,8 +485,8 @@ static WorkLayout work_layout(const pet_os_geom* g, bool need_nu) {
     L.caps[RED_SUMMU] = std::max(std::max(bp_grid_max(g), elem_grid(g->n_vox)), g->d.dim == 3 ? pen3_grid(g) : 0);
     L.caps[RED_FID] = fp_grid(g, g->d.n_angles);
     L.caps[RED_RDP] = elem_grid(g->n_vox);
-    L.caps[RED_SUMY] = elem_grid(g->n_bins);
-    L.caps[RED_SUMR] = elem_grid(g->n_bins);
+    L.caps[RED_SUMY] = sums ? elem_grid(g->n_bins) : 0;
+    L.caps[RED_SUMR] = sums ? elem_grid(g->n_bins) : 0;
     L.caps[RED_SUMS] = 1;
     for (int r = 0; r < RED_COUNT; ++r) L.o_red[r] = cv.take<double>((size_t)L.caps[r]);
     L.o_tot = cv.take<double>(RED_COUNT);
@@ -515,11 +518,11 @@ static void work_carve(const WorkLayout& L, char* blk, Work* w) {
     }
 }
 
-size_t work_bytes(const pet_os_geom* g, bool need_nu) { return work_layout(g, need_nu).bytes; }
+size_t work_bytes(const pet_os_geom* g, bool need_nu) { return work_layout(g, need_nu, false).bytes; }
 
-int work_alloc(const pet_os_geom* g, bool need_nu, Work* w) {
+int work_alloc(const pet_os_geom* g, bool need_nu, Work* w, bool sums) {
     *w = Work{};
-    const WorkLayout L = work_layout(g, need_nu);
+    const WorkLayout L = work_layout(g, need_nu, sums);
     char* blk = nullptr;
     if (hipMalloc(&blk, L.bytes) != hipSuccess) return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of scratch failed");
     work_carve(L, blk, w);
@@ -531,12 +534,14 @@ int work_alloc(const pet_os_geom* g, bool need_nu, Work* w) {
     return PET_OS_OK;
 }
 
-int work_place(const pet_os_geom* g, bool need_nu, void* base, size_t cap, Work* w, hipStream_t s) {
+int work_place(const pet_os_geom* g, bool need_nu, void* base, size_t cap, size_t most, Work* w, hipStream_t s) {
     *w = Work{};
-    const WorkLayout L = work_layout(g, need_nu);
-    if (L.bytes > cap)
-        return fail(PET_OS_ERR_INVALID_ARG, "the reconstruction needs " + std::to_string(L.bytes) +
-                                                " bytes of scratch; the static area holds " + std::to_string(cap));
+    const size_t need = work_layout(g, need_nu, true, false).bytes;
+    if (need > most)
+        return fail(PET_OS_ERR_INVALID_ARG, "the reconstruction needs " + std::to_string(need) +
+                                                " bytes of scratch; the static area holds " + std::to_string(most));
+    const WorkLayout L = work_layout(g, need_nu, false);
+    if (L.bytes > cap) return fail(PET_OS_ERR_DEVICE, "static scratch smaller than the largest layout");
     work_carve(L, (char*)base, w);
     // the totals start at zero, as in a fresh allocation (a fill kernel, so
     // that no memset is recorded if the caller captures the stream)
@@ -766,6 +771,7 @@ static int run_subiteration(pet_os_state* st, float* f, const float* y, const fl
     F.f = f; F.fz = st->w.fz; F.y = y; F.r = r; F.out = st->w.w; F.angles = angles; F.n_al = n_al;
     if (d3 && (rc = ensure_yr(st, y, r, s))) return rc;
     F.yr = (d3 && st->yr != nullptr && st->yr_y == y && st->yr_r == r) ? st->yr : nullptr;
+    F.quad = quad_ok(g) ? 1 : 0;
     const bool osem = st->p.mode == PET_OS_OSEM;
     const float* sens_i = osem ? st->osem_sens + (size_t)(st->i - 1) * g->n_vox : nullptr;
     F.mode = osem ? FP_EM : FP_RATIO;
@@ -824,6 +830,7 @@ static int run_subiteration(pet_os_state* st, float* f, const float* y, const fl
         // the penalty gradient of f and mu, then the update, which adds the
         // penalty gradient to the back-projection
         B.out = st->w.G;
+        B.quad = F.quad;
         if (!osem) {
             B.f = f; B.mu = st->w.mu; B.want_mu = want_mu ? 1 : 0;
             B.part_f = st->w.red[RED_SUMF].part;
@@ -835,6 +842,7 @@ static int run_subiteration(pet_os_state* st, float* f, const float* y, const fl
         rc = launch_bp(g, B, s);
         if (rc || (rc = prof_end(ev, s))) return rc;
         UpdLaunch U{};
+        U.g_zfast = F.quad;
         if (!osem) {
             U.gradR = st->w.gradR;
             U.beta_over_M = B.beta_over_M;
@@ -1084,7 +1092,7 @@ int pet_os_default_U(const pet_os_geom* g, const float* f0, const float* y, cons
     if (!g || !f0 || !y || !r || !U) return fail(PET_OS_ERR_INVALID_ARG, "NULL argument");
     hipStream_t s = (hipStream_t)stream;
     Work w;
-    int rc = work_alloc(g, false, &w);
+    int rc = work_alloc(g, false, &w, true);
     if (rc) return rc;
     rc = launch_sum(y, g->n_bins, w.red[RED_SUMY], s);
     if (!rc) rc = launch_finalize(w.red[RED_SUMY], elem_grid(g->n_bins), s);
@@ -1128,7 +1136,8 @@ int pet_os_subset_gradient(const pet_os_geom* g, const pet_os_params* p, const f
     float* big = nullptr;
     if (n_al > g->max_sub_angles) {
         // + 4 floats of padding for the 3D back-projector's 16-byte staging loads
-        if (hipMalloc(&big, sizeof(float) * ((size_t)n_al * g->n_planes * g->d.n_radial + 4)) != hipSuccess) {
+        const size_t n = quad_ok(g) ? quad_floats(g, n_al) : (size_t)n_al * g->n_planes * g->d.n_radial + 4;
+        if (hipMalloc(&big, sizeof(float) * n) != hipSuccess) {
             work_free(&w);
             return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of the ratio sinogram failed");
         }
@@ -1138,6 +1147,7 @@ int pet_os_subset_gradient(const pet_os_geom* g, const pet_os_params* p, const f
     FPLaunch F{};
     F.f = f; F.fz = w.fz; F.y = y; F.r = r; F.out = wsino; F.angles = angles; F.n_al = n_al;
     F.mode = FP_RATIO;
+    F.quad = quad_ok(g) ? 1 : 0;
     F.seg = fp_seg_for(g, (long long)n_al * g->n_planes * g->d.n_radial, g->tuned_seg);
     const bool psf = g->d.dim == 2 && g->k.psf_kx > 0;
     if (psf && !rc) {
@@ -1164,6 +1174,12 @@ int pet_os_subset_gradient(const pet_os_geom* g, const pet_os_params* p, const f
         // the back-projection into grad, then the penalty gradient added to it
         BPLaunch P = B;
         P.f = nullptr;
+        if (F.quad) {
+            // (left z-fastest in the scratch)
+            P.quad = 1;
+            P.out = w.G;
+            B.bz = w.G;
+        }
         rc = launch_bp(g, P, s);
         if (!rc) rc = launch_pen3(g, B, s);
     } else if (!rc) {
@@ -1360,7 +1376,7 @@ int pet_os_nnz(const pet_os_geom* g, int32_t subset, int64_t* nnz) {
     const int n_al = subset == 0 ? g->d.n_angles : ex->subset_count[subset - 1];
     const int64_t n = (int64_t)n_al * g->n_planes * g->d.n_radial;
     Work w;
-    int rc = work_alloc(g, false, &w);
+    int rc = work_alloc(g, false, &w, true);
     if (rc) return rc;
     float* cnt = nullptr;
     if (hipMalloc(&cnt, (size_t)n * sizeof(float)) != hipSuccess) {

@@ -99,13 +99,15 @@ struct Work {
     size_t bytes = 0;
 };
 
-int work_alloc(const pet_os_geom* g, bool need_nu, Work* w);
+// sums: with the partials of the sums over all bins (default U, nnz)
+int work_alloc(const pet_os_geom* g, bool need_nu, Work* w, bool sums = false);
 void work_free(Work* w);
 // bytes of one request's scratch, and the same scratch placed in caller
 // memory at base (cap bytes, 256-byte aligned): no allocation; the reduction
-// totals are cleared by a fill kernel on s
+// totals are cleared by a fill kernel on s.  Requests of more than `most`
+// bytes with the subset sinogram bin by bin are refused, whatever its layout.
 size_t work_bytes(const pet_os_geom* g, bool need_nu);
-int work_place(const pet_os_geom* g, bool need_nu, void* base, size_t cap, Work* w, hipStream_t s);
+int work_place(const pet_os_geom* g, bool need_nu, void* base, size_t cap, size_t most, Work* w, hipStream_t s);
 
 // device angle lists of a geometry
 struct GeomExtra {
@@ -138,13 +140,14 @@ struct FPLaunch {
     const float* y;
     const float* r;
     // 3D: (y, r) pairs bin-major, [(angle * n_radial + bin) * n_planes + plane]
-    // (launch_yr3), read instead of y and r by the staged forward projector
+    // (launch_yr3), read instead of y and r by the quad forward projector
     const float2* yr = nullptr;
     float* out;              // FP_RATIO, FP_EM, FP_COUNT, FP_COMPACT: compact [al][plane][b]; FP_PLAIN: natural q
     const int* angles;       // device list of natural angle indices for this pass
     int n_al;                // number of angles
     int mode;
     Reduction red;           // FP_OBJECTIVE
+    int quad = 0;            // 3D, FP_RATIO / FP_EM: out as quads of mirror rays (kernels3q.hip)
     int seg = 0;             // threads per ray (0: tuned or heuristic)
     int raw = 0;             // 1: no attenuation factors (line integrals of f itself)
     // 2D subiteration: pixel pass in the same launch (snapshot of f and mu)
@@ -157,7 +160,7 @@ struct FPLaunch {
     Reduction px_red_mu{};
 };
 int launch_fp(const pet_os_geom* g, const FPLaunch& L, hipStream_t s);
-// 3D: the bin-major copy of y and r that the staged forward projector reads
+// 3D: the bin-major copy of y and r that the quad forward projector reads
 // (yr: n_bins pairs); whether the geometry's forward projector uses it
 int launch_yr3(const pet_os_geom* g, const float* y, const float* r, float2* yr, hipStream_t s);
 bool fp3_reads_yr(const pet_os_geom* g);
@@ -193,6 +196,8 @@ struct BPLaunch {
     // back-projector's launch into gradR (with f, mu, want_mu, the penalty
     // constants, part_f and red_mu); the update then adds it to b
     float* gradR = nullptr;
+    int quad = 0;                      // 3D: w holds quads of mirror rays; the back-projection is left z-fastest
+    const float* bz = nullptr;         // launch_pen3: a z-fastest back-projection to add to, instead of out
 };
 int launch_bp(const pet_os_geom* g, const BPLaunch& L, hipStream_t s);
 // 2D full model: out = B in (PSF), and the image-space part of a subiteration
@@ -206,6 +211,7 @@ struct UpdLaunch {
     float* f;
     float* fz = nullptr;     // 3D: z-fastest copy, rewritten with the new iterate
     const float* G;
+    int g_zfast = 0;         // 3D: G is z-fastest
     const float* mu;
     const float* pnorm;
     float* nu_frozen;
@@ -281,6 +287,18 @@ int launch_update3(const pet_os_geom* g, const UpdLaunch& L, hipStream_t s);
 // L.out, mu and the partials of sum mu (L.f, mu, want_mu, beta_over_M,
 // gamma_R, eps, part_f, n_part_f, red_mu); one partial per block of pen3_grid
 int launch_pen3(const pet_os_geom* g, const BPLaunch& L, hipStream_t s);
+// quads of mirror rays (kernels3q.hip): whether a geometry takes them, and the
+// floats of the subset sinogram of n_al angles in that layout
+bool quad_ok(const pet_os_geom* g);
+bool fp3q_ok(const pet_os_geom* g);         // whether the forward projector alone takes them
+size_t quad_floats(const pet_os_geom* g, int n_al);
+int launch_fp3q(const pet_os_geom* g, const FPLaunch& L, hipStream_t s);
+int launch_bp3q(const pet_os_geom* g, const BPLaunch& L, hipStream_t s);
+int fp3q_grid(const pet_os_geom* g, int n_al);
+int bp3q_grid(const pet_os_geom* g);
+size_t bp3q_lds(const pet_os_geom* g);      // bytes of dynamic LDS
+int bp3q_rows(const pet_os_geom* g);        // staged bin pairs per angle
+int bp3q_buf(const pet_os_geom* g);         // float4 of one staging buffer
 int pen3_grid(const pet_os_geom* g);
 // z-fastest copy of f and the partials of sum f (same tiles and order as the 3D update)
 int launch_prep3(const pet_os_geom* g, const float* f, float* fz, Reduction red, hipStream_t s);
@@ -316,6 +334,7 @@ struct SlotDev {
     int fp_seg, bp_kind;
     int nb_max, rows_max, chunk;   // back-projector staging (3D: bins, rows, ring differences per group)
     int zb;                        // 3D: slices per back-projection block
+    int quad;                      // 3D: w in quads, G z-fastest (rows_max: bin pairs, chunk: float4 per buffer)
     int active;
 };
 
@@ -328,14 +347,19 @@ struct Item {
 // kind, and the 3D forward, back-projection per z-block size (16/32/64),
 // penalty gradient and mu, and update
 // (lists WL_BP3 + 2 * zi + wi: z-block 16/32/64 for zi = 0/1/2, LDS row
-// stride 20/40 bins for wi = 0/1)
-enum { WL_FP = 0, WL_BP0 = 1, WL_BP1 = 2, WL_FP3 = 3, WL_BP3 = 4, WL_UPD3 = 10, WL_PEN3 = 11, WL_COUNT = 12 };
+// stride 20/40 bins for wi = 0/1; lists WL_FP3Q + wi and WL_BP3Q + wi: the
+// projectors on quads, more than 32 slices for wi = 1)
+enum { WL_FP = 0, WL_BP0 = 1, WL_BP1 = 2, WL_FP3 = 3, WL_BP3 = 4, WL_UPD3 = 10, WL_PEN3 = 11, WL_FP3Q = 12, WL_BP3Q = 14,
+       WL_COUNT = 16 };
 
 // Queue one batched subiteration (every active slot advances by one):
 // forward, back-projection (one launch per tile kind), update, advance.
 // Lists whose bit is clear in `live_mask` are not launched.
 int launch_batch_step(SlotDev* d_slots, int n_slots, Item* const lists[WL_COUNT], const int* d_counts,
-                      const int grids[WL_COUNT], int live_mask, hipStream_t s);
+                      const int grids[WL_COUNT], int live_mask, size_t bp3q_lds_bytes, hipStream_t s);
+void launch_batch3q_fp(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, int kl, hipStream_t s);
+void launch_batch3q_bp(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, int kl, size_t lds,
+                       hipStream_t s);
 void launch_batch3_fp(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, hipStream_t s);
 void launch_batch3_bp(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, int zb, int nbs,
                       hipStream_t s);

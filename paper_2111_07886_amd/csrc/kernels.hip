@@ -103,7 +103,7 @@ __device__ __forceinline__ float fp_subray_acc(const GeoK& g, const FPArgs& A, c
 // every SEG, and the batched kernels' choice of it, give the same bits.
 template <int DIM, int SEG, bool SUB = false>
 __device__ void fp_body(const GeoK& g, const FPArgs& A, long long vblock) {
-    static_assert(DIM == 2, "the 3D forward projector is k_fp3");
+    static_assert(DIM == 2, "the 3D forward projectors are k_fp3q and k_fp3_wave");
     static_assert(SEG == 1 || (64 % SEG == 0), "segments of a ray stay in one wave");
     constexpr int RPB = NT / SEG;
     __shared__ double s_red[NT / 64];
@@ -1397,11 +1397,14 @@ __global__ __launch_bounds__(NT) void k_advance(SlotDev* S, int n_slots) {
 }
 
 int launch_batch_step(SlotDev* d_slots, int n_slots, Item* const lists[WL_COUNT], const int* d_counts,
-                      const int grids[WL_COUNT], int live_mask, hipStream_t s) {
+                      const int grids[WL_COUNT], int live_mask, size_t bp3q_lds_bytes, hipStream_t s) {
     auto live = [&](int k) { return (live_mask >> k) & 1; };
     if (live(WL_FP))
         hipLaunchKernelGGL(k_fp_batch, dim3(grids[WL_FP]), dim3(NT), 0, s, d_slots, lists[WL_FP], d_counts + WL_FP);
     if (live(WL_FP3)) launch_batch3_fp(d_slots, lists[WL_FP3], d_counts + WL_FP3, grids[WL_FP3], s);
+    for (int k = 0; k < 2; ++k)
+        if (live(WL_FP3Q + k))
+            launch_batch3q_fp(d_slots, lists[WL_FP3Q + k], d_counts + WL_FP3Q + k, grids[WL_FP3Q + k], k ? 64 : 32, s);
     if (live(WL_BP0))
         hipLaunchKernelGGL((k_bp_batch<Tile2L>), dim3(grids[WL_BP0]), dim3(NT), bp_lds_budget(0), s, d_slots,
                            lists[WL_BP0], d_counts + WL_BP0);
@@ -1413,6 +1416,10 @@ int launch_batch_step(SlotDev* d_slots, int n_slots, Item* const lists[WL_COUNT]
         if (live(WL_BP3 + k))
             launch_batch3_bp(d_slots, lists[WL_BP3 + k], d_counts + WL_BP3 + k, grids[WL_BP3 + k], zbs[k / 2],
                              (k & 1) ? 40 : 20, s);
+    for (int k = 0; k < 2; ++k)
+        if (live(WL_BP3Q + k))
+            launch_batch3q_bp(d_slots, lists[WL_BP3Q + k], d_counts + WL_BP3Q + k, grids[WL_BP3Q + k], k ? 64 : 32,
+                              bp3q_lds_bytes, s);
     if (live(WL_PEN3)) launch_batch3_pen(d_slots, lists[WL_PEN3], d_counts + WL_PEN3, grids[WL_PEN3], s);
     if (live(WL_UPD3)) launch_batch3_upd(d_slots, lists[WL_UPD3], d_counts + WL_UPD3, grids[WL_UPD3], s);
     hipLaunchKernelGGL(k_advance, dim3((n_slots + NT - 1) / NT), dim3(NT), 0, s, d_slots, n_slots);

@@ -8,19 +8,17 @@
 // slice r1 + o is crossed exactly where zeta lies in [o, o + 1).  Both
 // projectors are built on that:
 //
-//   k_fp3    one block per (angle, bin), a wave per ring difference in
-//            turn; the lanes are the first rings r1.  The 64 lanes first walk
-//            64 major cells in parallel and list the (transaxial cell, slice
-//            offset o, length) pieces of that stretch in LDS; then every lane
-//            adds length * f[cell, slice r1 + o] for every piece.  The image
-//            columns of the stretch (a copy of the image with z fastest) are
-//            staged in LDS once for all ring differences, so a piece costs
-//            one conflict-free LDS read of 64 consecutive slices.  The
-//            Poisson ratio (or the FP64 log-likelihood term) is the
-//            epilogue, as in 2D.  k_fp3_wave (one wave per (angle, bin, ring
-//            difference), the same pieces read from device memory) covers
-//            more than 64 rings or 32 ring differences, and the batched path.
-//   k_bp3    one block per 8x8 column tile and z-range.  A lane owns one
+//   k_fp3_wave  one wave per (angle, bin, ring difference); the lanes are the
+//            first rings r1.  The 64 lanes first walk 64 major cells in
+//            parallel and list the (transaxial cell, slice offset o, length)
+//            pieces of that stretch in LDS; then every lane adds length *
+//            f[cell, slice r1 + o] for every piece (64 consecutive slices of
+//            the z-fastest copy).  The Poisson ratio (or the FP64
+//            log-likelihood term) is the epilogue, as in 2D.  It takes what
+//            the projector on quads of mirror rays (kernels3q.hip) does not:
+//            more than 64 rings, and the count of nonzeros.
+//   k_bp3    (natural-layout and unit weights, and geometries without quads)
+//            one block per 8x8 column tile and z-range.  A lane owns one
 //            column; wave v takes ring differences v, v+4, ... of each
 //            staged group.  Per angle a lane finds the bins whose ray crosses
 //            its column's transaxial cell and, per ring difference, the one
@@ -36,8 +34,8 @@
 //   k_pen3   the image-space part of a subiteration on 32 x 8 x 8 voxel
 //            tiles with an LDS halo of f: G = A_i^T w + (beta/M) grad R(f)
 //            (eqn:gradRD), mu (Sec. III-B) and FP64 partials of sum mu.
-//            Apart from the back-projector, it runs at the occupancy of a
-//            small kernel instead of at the end of every column tile.
+//            In a single-request subiteration its blocks (pen3.h) run in the
+//            back-projector's launch.
 //   k_upd3   the update of k_update on 64 x 32 (x, z) tiles, also writing
 //            the z-fastest copy through LDS; FP64 partials of sum f.
 //   k_prep3  the z-fastest copy and the sum-f partials of a caller's image
@@ -49,6 +47,7 @@
 
 #include "devutil.h"
 #include "internal.h"
+#include "pen3.h"
 
 namespace petos {
 
@@ -58,7 +57,6 @@ struct FP3Args {
     const float* fz;        // image with z fastest: fz[(iy * nx + ix) * nz + iz]
     const float* y;
     const float* r;
-    const float2* yr;       // null, or (y, r) bin-major (read by the staged kernel instead)
     float* out;
     const int* angles;
     int n_al;
@@ -262,289 +260,7 @@ __global__ __launch_bounds__(NT) void k_fp3_wave(GeoK g, FP3Args A, long long n_
     fp3_body(g, A, vb);
 }
 
-// Forward projection with the ray's image columns staged in LDS, used when
-// the rings fit one chunk (nz <= 64) and there are at most 32 ring
-// differences.  One block takes one (angle, bin); its eight waves take the
-// ring differences w, w + 8, w + 16, w + 24.  The transaxial path of the ray
-// is the same for every ring difference, so for each stretch of 64 major
-// cells the columns it can enter (minor cells c0 and c0 + qstep of each major
-// cell, all nz slices) are copied to LDS once, and every ring difference
-// reads its pieces there instead of from device memory, where each piece
-// cost a 256-byte wave load through the vector L1.  Pieces, their order and
-// their arithmetic are those of fp3_body, so the results agree bit for bit.
-constexpr int FPS_NT = 512;
-constexpr int FPS_W = FPS_NT / 64;      // waves per block
-constexpr int FPS_DPW = 4;              // ring differences per wave at most
-constexpr int FPS_ZS = 64;              // floats per staged column (nz <= 64)
-constexpr int FPS_SLOTS = 128;          // staged columns of a stretch: slot 2k (c0) and 2k + 1 (c0 + qstep) of cell mb + k
-
-__host__ __device__ inline bool fp3_staged(int nz, int max_rd) {
-    return nz <= FPS_ZS && 2 * max_rd + 1 <= FPS_W * FPS_DPW;
-}
-
-// Copy a stretch's columns into s_col: slot 2k holds minor cell c0 of major
-// cell mb + k, slot 2k + 1 its neighbour c0 + qstep, all nz slices; columns
-// outside the image or past m1 stay unwritten (no piece refers to them).
-// With nz a multiple of 4 (column starts 16-byte aligned) a wave instruction
-// copies four columns, sixteen lanes of 16 bytes each; else one column, a
-// slice per lane.  Returns without waiting.
-__device__ __forceinline__ void fp3s_stage(const float* fz, float* s_col, const TxRay& tx, int mb, int m1, int n_minor,
-                                           int qstep, int ms, int cs, int nz, int wave, int lane) {
-    if ((nz & 3) == 0) {
-        const int sub = lane >> 4, q = (lane & 15) * 4;
-        for (int s0 = wave * 4; s0 < FPS_SLOTS; s0 += FPS_W * 4) {
-            const int slot = s0 + sub, m = mb + (slot >> 1);
-            bool ok = m <= m1 && q < nz;
-            int src = 0;
-            if (ok) {
-                const int c = (int)floor(__fma_rn(tx.Q, (double)m, tx.P)) + ((slot & 1) ? qstep : 0);
-                ok = (unsigned)c < (unsigned)n_minor;
-                src = __mul24(m, ms) + __mul24(c, cs) + q;
-            }
-            if (ok)
-                __builtin_amdgcn_global_load_lds(fz + src, (__attribute__((address_space(3))) void*)(s_col + s0 * FPS_ZS),
-                                                 16, 0, 0);
-        }
-    } else {
-        for (int slot = wave; slot < FPS_SLOTS; slot += FPS_W) {
-            const int m = mb + (slot >> 1);
-            bool ok = m <= m1 && lane < nz;
-            int src = 0;
-            if (ok) {
-                const int c = (int)floor(__fma_rn(tx.Q, (double)m, tx.P)) + ((slot & 1) ? qstep : 0);
-                ok = (unsigned)c < (unsigned)n_minor;
-                src = __mul24(m, ms) + __mul24(c, cs) + lane;
-            }
-            if (ok)
-                __builtin_amdgcn_global_load_lds(fz + src, (__attribute__((address_space(3))) void*)(s_col + slot * FPS_ZS),
-                                                 4, 0, 0);
-        }
-    }
-}
-
-__device__ void fp3s_body(const GeoK& g, const FP3Args& A, long long vblock) {
-    __shared__ __attribute__((aligned(16))) float s_col[FPS_SLOTS * FPS_ZS];
-    // the pieces as two arrays: length, and the byte offset (off + 16) * 4 of
-    // slice o of the staged column, which fits 16 bits (o >= -15 here), so
-    // that the broadcast reads of a batch of pieces move 6 bytes a piece
-    __shared__ __attribute__((aligned(16))) unsigned short s_po[FPS_W][FP3_CAP];
-    __shared__ __attribute__((aligned(16))) float s_pl[FPS_W][FP3_CAP];
-    __shared__ double s_red[FPS_W];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int D = g.max_rd, ND = 2 * D + 1, Nr = g.n_radial, R = g.n_rings, nz = g.nz;
-    const int b = (int)(vblock % Nr), al = (int)(vblock / Nr);
-    const bool counting = A.mode == FP_COUNT;
-    const int a = A.angles[al];
-    const AngleK& AK = g.ang[a];
-    // the ray's FP64 constants live in LDS (read where used) rather than in
-    // registers across the loops
-    __shared__ double s_ray[5];    // P, L, tau0, tauQ, inv_tauQ
-    const TxRay tx0 = tx_ray(g, AK, b);
-    const ZBin zb0 = z_bin(g, AK, b);
-    if (threadIdx.x == 0) {
-        s_ray[0] = tx0.P;
-        s_ray[1] = tx0.L;
-        s_ray[2] = zb0.tau0;
-        s_ray[3] = zb0.tauQ;
-        s_ray[4] = zb0.inv_tauQ;
-    }
-    TxRay tx = tx0;
-    const int n_major = tx.row_major ? g.ny : g.nx;
-    const int n_minor = tx.row_major ? g.nx : g.ny;
-    int m0, m1;
-    major_range(tx, n_major, n_minor, m0, m1);
-    const int qstep = (tx.Q >= 0.0) ? 1 : -1;
-    const float invQf = (float)tx.invQ;
-    // offset of voxel (minor cell c, major cell m, slice o) in the z-fastest
-    // copy: m ms + c cs + o (24-bit products, as in fp3_body)
-    const int cs = tx.row_major ? nz : g.nx * nz;
-    const int ms = tx.row_major ? g.nx * nz : nz;
-
-    float acc[FPS_DPW];
-#pragma unroll
-    for (int j = 0; j < FPS_DPW; ++j) acc[j] = 0.0f;
-
-    for (int mb = m0; mb <= m1; mb += 64) {
-        // (1) stage the stretch's columns (counting reads no image, and is
-        // given none)
-        __syncthreads();    // the previous stretch's columns are read no more (and s_ray is written)
-        tx.P = s_ray[0];
-        if (!counting) fp3s_stage(A.fz, s_col, tx, mb, m1, n_minor, qstep, ms, cs, nz, wave, lane);
-        __builtin_amdgcn_s_waitcnt(0);      // this wave's copies have landed
-        __syncthreads();                    // and every other wave's
-
-        // (2) the transaxial part of the lane's major cell, shared by the
-        // wave's ring differences (lanes past the last cell repeat it and
-        // keep no piece)
-        const int mraw = mb + lane;
-        const int m = min(mraw, m1);
-        const double gm = __fma_rn(tx.Q, (double)m, tx.P);
-        const double cf = floor(gm);
-        const int c0 = (int)cf, c1 = c0 + qstep;
-        const double ce = (tx.Q >= 0.0) ? cf + 1.0 : cf;
-        const double ge = gm + tx.Q;
-        const bool xc = (tx.Q >= 0.0) ? (ge > ce) : (ge < ce);
-        const float tX = xc ? (float)(ce - gm) * invQf : 1.0f;
-        const bool in0 = (unsigned)c0 < (unsigned)n_minor, in1 = (unsigned)c1 < (unsigned)n_minor;
-        const int sl0 = 2 * (m - mb) * FPS_ZS, sl1 = sl0 + FPS_ZS;    // LDS offsets of the two columns
-
-#pragma unroll
-        for (int j = 0; j < FPS_DPW; ++j) {
-            const int di = wave + FPS_W * j;
-            if (di >= ND) break;
-            const int d = di - D;
-            // (3) the axial part and the pieces, as in fp3_body
-            const double zeta0 = __fma_rn((double)d, s_ray[2], 0.5);
-            const double Qz = (double)d * s_ray[3];
-            const double invQz = (d == 0) ? 0.0 : g.inv_d[di] * s_ray[4];
-            const float Lkf = (float)(s_ray[1] * g.kappa[(long long)b * ND + di]), invQzf = (float)invQz;
-            const int zstep = (Qz >= 0.0) ? 1 : -1;
-            const int olo = min(0, d), ohi = max(0, d);
-            const double zm = __fma_rn(Qz, (double)m, zeta0);
-            const double of = floor(zm);
-            const int o0 = (int)of, o1 = o0 + zstep;
-            const double oe = (Qz >= 0.0) ? of + 1.0 : of;
-            const double ze = zm + Qz;
-            const bool zc = (Qz >= 0.0) ? (ze > oe) : (ze < oe);
-            const float tZ = zc ? (float)(oe - zm) * invQzf : 1.0f;
-            const bool x_first = tX <= tZ;
-            const float t1 = fminf(tX, tZ), t2 = fmaxf(tX, tZ);
-            const int po1 = x_first ? o0 : o1;
-            const bool pin1 = x_first ? in1 : in0;
-            const float f0 = t1, f1 = t2 - t1, f2 = 1.0f - t2;
-            const bool v0 = f0 > 0.0f && in0 && o0 >= olo && o0 <= ohi;
-            const bool v1 = (xc || zc) && f1 > 0.0f && pin1 && po1 >= olo && po1 <= ohi;
-            const bool v2 = xc && zc && f2 > 0.0f && in1 && o1 >= olo && o1 <= ohi;
-            const int off[3] = {sl0 + o0, (x_first ? sl1 : sl0) + po1, sl1 + o1};
-            const float len[3] = {Lkf * f0, Lkf * f1, Lkf * f2};
-            const int present = mraw <= m1 ? (v0 ? 1 : 0) | (v1 ? 2 : 0) | (v2 ? 4 : 0) : 0;
-            // (4) compact the pieces in cell order (as in fp3_body)
-            const int cnt = __popc(present);
-            int pos = 0, total = 0;
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const unsigned long long bm = __ballot((cnt >> k) & 1);
-                pos += __builtin_amdgcn_mbcnt_hi((unsigned)(bm >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bm, 0u)) << k;
-                total += __popcll(bm) << k;
-            }
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                if (present & (1 << k)) {
-                    s_po[wave][pos] = (unsigned short)((off[k] + 16) * 4);
-                    s_pl[wave][pos] = len[k];
-                    ++pos;
-                }
-            }
-            wave_lds_sync();
-            // (5) every lane (first ring r1) applies every piece from LDS
-            const int r1 = max(0, -d) + lane;
-            if (r1 <= min(R - 1, R - 1 - d)) {
-                if (counting) {
-                    acc[j] += (float)total;
-                } else {
-                    // byte address of slice o of a piece's column for this
-                    // lane: colb + (o + 16) * 4 with colb at ring r1 - 16
-                    const char* colb = reinterpret_cast<const char*>(s_col) + 4 * r1 - 64;
-                    int k = 0;
-                    for (; k + 8 <= total; k += 8) {
-                        // eight pieces: offsets in one 16-byte read, lengths in
-                        // two, the eight column reads in flight together
-                        const uint4 po4 = *reinterpret_cast<const uint4*>(&s_po[wave][k]);
-                        const float4 l0 = *reinterpret_cast<const float4*>(&s_pl[wave][k]);
-                        const float4 l1 = *reinterpret_cast<const float4*>(&s_pl[wave][k + 4]);
-                        const unsigned po[4] = {po4.x, po4.y, po4.z, po4.w};
-                        const float ln[8] = {l0.x, l0.y, l0.z, l0.w, l1.x, l1.y, l1.z, l1.w};
-                        float x[8];
-#pragma unroll
-                        for (int u = 0; u < 8; ++u) {
-                            const unsigned ob = (u & 1) ? (po[u >> 1] >> 16) : (po[u >> 1] & 0xffffu);
-                            x[u] = *reinterpret_cast<const float*>(colb + ob);
-                        }
-#pragma unroll
-                        for (int u = 0; u < 8; ++u) acc[j] = fmaf(ln[u], x[u], acc[j]);
-                    }
-                    for (; k < total; ++k)
-                        acc[j] = fmaf(s_pl[wave][k], *reinterpret_cast<const float*>(colb + s_po[wave][k]), acc[j]);
-                }
-            }
-            wave_lds_sync();
-        }
-    }
-
-    // (6) the rays' outputs, as in fp3_body
-    double term = 0.0;
-#pragma unroll
-    for (int j = 0; j < FPS_DPW; ++j) {
-        const int di = wave + FPS_W * j;
-        if (di >= ND) break;
-        const int d = di - D;
-        const int r1lo = max(0, -d), r1 = r1lo + lane;
-        if (r1 > min(R - 1, R - 1 - d)) continue;
-        const int plane = g.plane_base[di] + (r1 - r1lo);
-        const long long nat = ((long long)plane * g.n_angles + a) * Nr + b;
-        const long long ray = ((long long)al * g.n_planes + plane) * Nr + b;
-        if (A.mode == FP_RATIO || A.mode == FP_EM) {
-            // y and r of the ray: from the bin-major copy the lanes' planes
-            // are consecutive (one 512-byte wave load), in the natural layout
-            // they lie n_angles * n_radial apart
-            float yv, rv;
-            if (A.yr != nullptr) {
-                const float2 v = A.yr[((long long)a * Nr + b) * g.n_planes + plane];
-                yv = v.x;
-                rv = v.y;
-            } else {
-                yv = A.y[nat];
-                rv = A.r[nat];
-            }
-            A.out[ray] = A.mode == FP_RATIO ? 1.0f - yv / (acc[j] + rv) : yv / (acc[j] + rv);
-        } else if (A.mode == FP_COUNT || A.mode == FP_COMPACT) {
-            A.out[ray] = acc[j];
-        } else if (A.mode == FP_PLAIN) {
-            A.out[nat] = acc[j];
-        } else {
-            const double q = (double)acc[j];
-            term += q - (double)A.y[nat] * log(q + (double)A.r[nat]);
-        }
-    }
-    if (A.mode == FP_OBJECTIVE) write_partial(term, A.red, s_red, vblock);
-}
-
-// six waves per SIMD: 44 KB of LDS per block lets three blocks share a CU
-__global__ __launch_bounds__(FPS_NT, 6) void k_fp3(GeoK g, FP3Args A, long long n_blocks) {
-    const long long vb = xcd_block(blockIdx.x, n_blocks);
-    if (vb >= n_blocks) return;
-    fp3s_body(g, A, vb);
-}
-
 // ------------------------------------------------------------------ back projection
-
-// The image-space part of a 3D subiteration: grad R(f) (eqn:gradRD, 26
-// in-image neighbours), either added after the back-projection b = A_i^T w
-// as G = b + (beta/M) grad R(f) in place over b, or (gradR given) stored on
-// its own for the update to add, so that it can run in the back-projector's
-// launch; with want_mu the smoothness measure mu = max(0.01, |grad f| /
-// mean f) (Sec. III-B) with the block's FP64 partial of sum mu.  One block
-// per 32 (x) x 8 (y) x 8 (z) voxels (a thread per (x, y), eight slices
-// each); f with a one-voxel halo in LDS.
-constexpr int PEN3_X = 32, PEN3_Y = 8, PEN3_Z = 8;
-constexpr int PEN3_HALO = (PEN3_X + 2) * (PEN3_Y + 2) * (PEN3_Z + 2);   // floats of the halo tile
-
-struct Pen3Args {
-    const float* f;
-    float* G;                // in: b, out: G (gradR null)
-    float* gradR;            // non-null: grad R(f) goes here and G is left alone
-    float* mu;
-    int want_mu;
-    float beta_over_M, gamma_R, eps;
-    const double* part_f;    // partials of sum f of the entering iterate (mean f)
-    int n_part_f;
-    Reduction red_mu;
-};
-
-__host__ __device__ inline int pen3_tiles(int n, int t) { return (n + t - 1) / t; }
-
-__device__ void pen3_body(const GeoK& g, const Pen3Args& A, int vblock, float* s_f, double* s_red);
-
 
 struct BP3Args {
     const float* w;          // null => unit weights (sensitivity)
@@ -1002,80 +718,6 @@ __global__ __launch_bounds__(NT, ZB <= 32 ? 4 : 3) void k_bp3(GeoK g, BP3Args A,
 // ------------------------------------------------------------------ penalty gradient and mu
 
 
-// s_f: PEN3_HALO floats of LDS, s_red: NT / 64 doubles
-__device__ void pen3_body(const GeoK& g, const Pen3Args& A, int vblock, float* s_f, double* s_red) {
-    constexpr int HX = PEN3_X + 2, HY = PEN3_Y + 2, HZ = PEN3_Z + 2;
-    const int tx = pen3_tiles(g.nx, PEN3_X), ty = pen3_tiles(g.ny, PEN3_Y);
-    const int x0 = (vblock % tx) * PEN3_X, y0 = ((vblock / tx) % ty) * PEN3_Y, z0 = (vblock / (tx * ty)) * PEN3_Z;
-    for (int e = threadIdx.x; e < HX * HY * HZ; e += NT) {
-        const int hx = e % HX, hy = (e / HX) % HY, hz = e / (HX * HY);
-        const int gx = x0 - 1 + hx, gy = y0 - 1 + hy, gz = z0 - 1 + hz;
-        float v = 0.0f;
-        if (gx >= 0 && gx < g.nx && gy >= 0 && gy < g.ny && gz >= 0 && gz < g.nz)
-            v = A.f[((long long)gz * g.ny + gy) * g.nx + gx];
-        s_f[e] = v;
-    }
-    float meanf = 1.0f;
-    if (A.want_mu) meanf = (float)(sum_partials(A.part_f, A.n_part_f, s_red) / (double)g.nvox);
-    __syncthreads();
-    const int lx = threadIdx.x % PEN3_X, ly = threadIdx.x / PEN3_X;
-    const int ix = x0 + lx, iy = y0 + ly;
-    double mu_part = 0.0;
-    if (ix < g.nx && iy < g.ny) {
-        // The thread's column, slice by slice, with the 3x3 neighbourhood of
-        // three slices in registers (one new slice read from LDS per step)
-        // and the out-of-image neighbours masked instead of branched around
-        // (the 26 in-image neighbours of eqn:gradRD, in stencil_at's order).
-        const bool okx[3] = {ix > 0, true, ix < g.nx - 1};
-        const bool oky[3] = {iy > 0, true, iy < g.ny - 1};
-        const float gR = A.gamma_R, eps = A.eps;
-        float pl[3][9];     // slices lz - 1, lz, lz + 1 of the halo tile (hz = lz .. lz + 2)
-        auto load = [&](float (&p)[9], int hz) {
-#pragma unroll
-            for (int q = 0; q < 9; ++q) p[q] = s_f[(hz * HY + ly + q / 3) * HX + lx + q % 3];
-        };
-        load(pl[0], 0);
-        load(pl[1], 1);
-#pragma unroll
-        for (int lz = 0; lz < PEN3_Z; ++lz) {
-            const int iz = z0 + lz;
-            if (iz >= g.nz) break;
-            float (&pm)[9] = pl[lz % 3];
-            float (&pc)[9] = pl[(lz + 1) % 3];
-            float (&pp)[9] = pl[(lz + 2) % 3];
-            load(pp, lz + 2);
-            const bool okz[3] = {iz > 0, true, iz < g.nz - 1};
-            const float fj = pc[4], fje = fj + eps, fj2e = fj + 2.0f * eps;
-            float acc = 0.0f;
-#pragma unroll
-            for (int dz = 0; dz < 3; ++dz) {
-                const float* p = dz == 0 ? pm : (dz == 1 ? pc : pp);
-#pragma unroll
-                for (int q = 0; q < 9; ++q) {
-                    if (dz == 1 && q == 4) continue;
-                    const RdpPair t = rdp_pair(fj, fje, fj2e, p[q], gR);
-                    // an out-of-image neighbour adds 0
-                    acc = fmaf(t.num, (okz[dz] && oky[q / 3] && okx[q % 3]) ? t.rden : 0.0f, acc);
-                }
-            }
-            const float gradR = 2.0f * acc;
-            const float gx = mat_der(ix, g.nx, pc[5], fj, pc[3]);
-            const float gy = mat_der(iy, g.ny, pc[7], fj, pc[1]);
-            const float gz = mat_der(iz, g.nz, pp[4], fj, pm[4]);
-            const float gmag = sqrtf(gx * gx + gy * gy + gz * gz);
-            const long long j = ((long long)iz * g.ny + iy) * g.nx + ix;
-            if (A.gradR != nullptr) A.gradR[j] = gradR;
-            else A.G[j] = fmaf(A.beta_over_M, gradR, A.G[j]);
-            if (A.want_mu) {
-                const float mu = fmaxf(0.01f, gmag / meanf);
-                A.mu[j] = mu;
-                mu_part += (double)mu;
-            }
-        }
-    }
-    if (A.want_mu) write_partial(mu_part, A.red_mu, s_red, vblock);
-}
-
 __global__ __launch_bounds__(NT) void k_pen3(GeoK g, Pen3Args A) {
     __shared__ float s_f[PEN3_HALO];
     __shared__ double s_red[NT / 64];
@@ -1087,17 +729,10 @@ int pen3_grid(const pet_os_geom* G) {
 }
 
 int launch_pen3(const pet_os_geom* G, const BPLaunch& L, hipStream_t s) {
-    Pen3Args a{};
-    a.f = L.f;
+    Pen3Args a;
+    fill_pen3(L, a);
     a.G = L.out;
-    a.mu = L.mu;
-    a.want_mu = L.want_mu;
-    a.beta_over_M = L.beta_over_M;
-    a.gamma_R = L.gamma_R;
-    a.eps = L.eps;
-    a.part_f = L.part_f;
-    a.n_part_f = L.n_part_f;
-    a.red_mu = L.red_mu;
+    a.bz = L.bz;
     const int grid = pen3_grid(G);
     if (L.want_mu && grid > L.red_mu.cap) return fail(PET_OS_ERR_DEVICE, "mu partials too small");
     petos_launch(k_pen3, dim3(grid), dim3(NT), 0, s, G->k, a);
@@ -1111,6 +746,7 @@ struct Upd3Args {
     float* f;
     float* fz;
     const float* G;
+    int g_zfast;             // G is z-fastest (gradR is not)
     const float* gradR;      // non-null: G = b + (beta/M) gradR, with b in G
     float beta_over_M;
     const float* mu;
@@ -1126,7 +762,8 @@ struct Upd3Args {
     const float* osem_sens;  // OSEM: f <- f * G / s_i (G = A_i^T (y/(q+r)))
 };
 
-constexpr int U3X = 64, U3Z = 32;
+constexpr int U3X = 32, U3Z = 32;
+constexpr int U3R = NT / U3X;          // slices at a time
 
 // update == false: only copy f into fz and write the partials of sum f
 __device__ void upd3_body(const Upd3Args& A, long long vblock, bool update) {
@@ -1138,28 +775,54 @@ __device__ void upd3_body(const Upd3Args& A, long long vblock, bool update) {
     t /= nxt;
     const int y = (int)(t % A.ny);
     const int z0 = (int)(t / A.ny) * U3Z, x0 = xt * U3X;
-    const int lx = threadIdx.x & 63, zq = threadIdx.x >> 6;
+    const int lx = threadIdx.x % U3X, zq = threadIdx.x / U3X;
     const int x = x0 + lx;
     const long long nvox = (long long)A.nx * A.ny * A.nz;
     const bool want_mu = update && (A.nu_mode == NU_COMPUTE || A.nu_mode == NU_COMPUTE_FREEZE);
     float meanmu = 1.0f;
     if (want_mu) meanmu = (float)(sum_partials(A.part_mu, A.n_part_mu, s_red) / (double)nvox);
+    const bool gt = update && A.g_zfast;
+    // what does not depend on G is loaded first, all slices together
+    float fv[U3Z / U3R], gv[U3Z / U3R];
+#pragma unroll
+    for (int k = 0; k < U3Z / U3R; ++k) {
+        const int z = z0 + zq + U3R * k;
+        fv[k] = gv[k] = 0.0f;
+        if (x < A.nx && z < A.nz) {
+            const long long j = ((long long)z * A.ny + y) * A.nx + x;
+            fv[k] = A.f[j];
+            if (update && A.gradR != nullptr) gv[k] = A.gradR[j];
+        }
+    }
+    if (gt) {
+        // G comes z-fastest: its tile through LDS (each thread then reads the
+        // places that it overwrites with its new values)
+#pragma unroll
+        for (int k = 0; k < U3Z * U3X / NT; ++k) {
+            const int e = threadIdx.x + NT * k;
+            const int xx = e / U3Z, zz = e % U3Z;
+            const int xg = x0 + xx, z = z0 + zz;
+            if (xg < A.nx && z < A.nz) s_t[xx * (U3Z + 1) + zz] = A.G[((long long)y * A.nx + xg) * A.nz + z];
+        }
+        __syncthreads();
+    }
     double part = 0.0;
 #pragma unroll
-    for (int k = 0; k < U3Z / 4; ++k) {
-        const int zz = zq + 4 * k, z = z0 + zz;
+    for (int k = 0; k < U3Z / U3R; ++k) {
+        const int zz = zq + U3R * k, z = z0 + zz;
         float v = 0.0f;
         if (x < A.nx && z < A.nz) {
             const long long j = ((long long)z * A.ny + y) * A.nx + x;
-            const float fj = A.f[j];
+            const float fj = fv[k];
+            const float bj = gt ? s_t[lx * (U3Z + 1) + zz] : (update ? A.G[j] : 0.0f);
             if (update && A.osem_sens != nullptr) {
                 // ordered-subsets EM (Hudson-Larkin): multiplicative update
                 const float sj = A.osem_sens[j];
-                const float fn = (sj > 0.0f) ? fj * A.G[j] / sj : fj;
+                const float fn = (sj > 0.0f) ? fj * bj / sj : fj;
                 A.f[j] = fn;
                 v = fn;
             } else if (update) {
-                const float Gj = A.gradR != nullptr ? fmaf(A.beta_over_M, A.gradR[j], A.G[j]) : A.G[j];
+                const float Gj = A.gradR != nullptr ? fmaf(A.beta_over_M, gv[k], bj) : bj;
                 const float pj = A.pnorm[j];
                 float nu = 1.0f;
                 if (want_mu) {
@@ -1199,12 +862,9 @@ int fp3_grid(const pet_os_geom* G, int n_al) {
     return (int)((n + FP3_W - 1) / FP3_W);
 }
 
-// blocks of the single-request forward projection: one per (angle, bin) with
-// staged columns, else the per-wave items of fp3_body
-int fp3_launch_grid(const pet_os_geom* G, int n_al) {
-    if (fp3_staged(G->d.nz, G->d.max_ring_diff)) return n_al * G->d.n_radial;
-    return fp3_grid(G, n_al);
-}
+// blocks of the single-request forward projection: quads of mirror rays, else
+// the per-wave items of fp3_body
+int fp3_launch_grid(const pet_os_geom* G, int n_al) { return fp3q_ok(G) ? fp3q_grid(G, n_al) : fp3_grid(G, n_al); }
 
 // Slices per block of the batched back-projector, and the default of the
 // single-request one: the smallest of 16, 32, 64 that holds the volume's depth.
@@ -1280,7 +940,7 @@ int bp3_shape_single(const pet_os_geom* G, int zb, int dpg_req, int& nb, int& rw
     return PET_OS_OK;
 }
 
-bool fp3_reads_yr(const pet_os_geom* G) { return G->d.dim == 3 && fp3_staged(G->d.nz, G->d.max_ring_diff); }
+bool fp3_reads_yr(const pet_os_geom* G) { return fp3q_ok(G); }
 
 // yr[(a * n_radial + b) * n_planes + plane] = (y, r)[(plane * n_angles + a) *
 // n_radial + b]: a transpose of [plane][angle-bin] by 64 x 64 tiles through
@@ -1314,24 +974,22 @@ int launch_yr3(const pet_os_geom* G, const float* y, const float* r, float2* yr,
 }
 
 int launch_fp3(const pet_os_geom* G, const FPLaunch& L, hipStream_t s) {
+    if (L.n_al == 0) return PET_OS_OK;
+    if (L.mode != FP_COUNT && L.fz == nullptr) return fail(PET_OS_ERR_DEVICE, "3D forward projection without z copy");
+    // (FP_COMPACT is a 2D mode of the batch)
+    if (fp3q_ok(G) && L.mode != FP_COMPACT) return launch_fp3q(G, L, s);
     FP3Args a;
     a.fz = L.fz;
     a.y = L.y;
     a.r = L.r;
-    a.yr = L.yr;
     a.out = L.out;
     a.angles = L.angles;
     a.n_al = L.n_al;
     a.mode = L.mode;
     a.red = L.red;
-    if (L.n_al == 0) return PET_OS_OK;
-    if (L.mode != FP_COUNT && L.fz == nullptr) return fail(PET_OS_ERR_DEVICE, "3D forward projection without z copy");
-    const int grid = fp3_launch_grid(G, L.n_al);
+    const int grid = fp3_grid(G, L.n_al);
     if (L.mode == FP_OBJECTIVE && grid > L.red.cap) return fail(PET_OS_ERR_DEVICE, "objective partials too small");
-    if (fp3_staged(G->d.nz, G->d.max_ring_diff))
-        petos_launch(k_fp3, dim3(8 * ((grid + 7) / 8)), dim3(FPS_NT), 0, s, G->k, a, (long long)grid);
-    else
-        petos_launch(k_fp3_wave, dim3(8 * ((grid + 7) / 8)), dim3(NT), 0, s, G->k, a, (long long)grid);
+    petos_launch(k_fp3_wave, dim3(8 * ((grid + 7) / 8)), dim3(NT), 0, s, G->k, a, (long long)grid);
     PETOS_HIP(hipGetLastError());
     return PET_OS_OK;
 }
@@ -1353,6 +1011,7 @@ static void fill_bp3(const pet_os_geom* G, const BPLaunch& L, BP3Args& a) {
 }
 
 int launch_bp3(const pet_os_geom* G, const BPLaunch& L, hipStream_t s) {
+    if (L.quad) return launch_bp3q(G, L, s);
     if (2 * G->d.max_ring_diff + 1 > BP3_MAXND) return fail(PET_OS_ERR_INVALID_ARG, "max_ring_diff too large");
     BP3Args a;
     fill_bp3(G, L, a);
@@ -1366,17 +1025,8 @@ int launch_bp3(const pet_os_geom* G, const BPLaunch& L, hipStream_t s) {
     a.pen = Pen3Args{};
     a.n_pen = 0;
     if (L.gradR != nullptr) {
-        a.pen.f = L.f;
-        a.pen.G = nullptr;
+        fill_pen3(L, a.pen);
         a.pen.gradR = L.gradR;
-        a.pen.mu = L.mu;
-        a.pen.want_mu = L.want_mu;
-        a.pen.beta_over_M = L.beta_over_M;
-        a.pen.gamma_R = L.gamma_R;
-        a.pen.eps = L.eps;
-        a.pen.part_f = L.part_f;
-        a.pen.n_part_f = L.n_part_f;
-        a.pen.red_mu = L.red_mu;
         a.n_pen = pen3_grid(G);
         if (L.want_mu && a.n_pen > L.red_mu.cap) return fail(PET_OS_ERR_DEVICE, "mu partials too small");
         a.lds = std::max(a.lds, PEN3_HALO);
@@ -1413,6 +1063,7 @@ static void fill_upd3(const pet_os_geom* G, const UpdLaunch& L, Upd3Args& a) {
     a.f = L.f;
     a.fz = L.fz;
     a.G = L.G;
+    a.g_zfast = L.g_zfast;
     a.gradR = L.gradR;
     a.beta_over_M = L.beta_over_M;
     a.mu = L.mu;
@@ -1527,6 +1178,7 @@ __global__ __launch_bounds__(NT) void k_pen3_batch(const SlotDev* __restrict__ S
         Pen3Args A{};
         A.f = d.f;
         A.G = d.G;
+        A.g_zfast = d.quad;
         A.mu = d.mu;
         A.want_mu = (nu_mode == NU_COMPUTE || nu_mode == NU_COMPUTE_FREEZE) ? 1 : 0;
         A.beta_over_M = d.beta_over_M;
@@ -1552,6 +1204,7 @@ __global__ __launch_bounds__(NT) void k_upd3_batch(const SlotDev* __restrict__ S
         A.f = d.f;
         A.fz = d.fz;
         A.G = d.G;
+        A.g_zfast = d.quad;
         A.mu = d.mu;
         A.pnorm = d.pnorm;
         A.nu_frozen = d.nu_frozen;

@@ -19,7 +19,10 @@
 
 namespace {
 
-constexpr size_t SCRATCH_BYTES = (size_t)PET_OS_NOALLOC_SCRATCH_BYTES;
+// A request is accepted by its scratch with the subset sinogram bin by bin, at
+// most PET_OS_NOALLOC_SCRATCH_BYTES; the 3D projectors' layout of the sinogram
+// takes up to 2.2 times the bins' floats (quad_ok).
+constexpr size_t SCRATCH_BYTES = (size_t)PET_OS_NOALLOC_SCRATCH_BYTES / 4 * 9;
 static __device__ __align__(256) char scratch[SCRATCH_BYTES];
 
 constexpr int MAX_DEVICES = 64;
@@ -75,7 +78,7 @@ extern "C" int pet_os_reconstruct_noalloc(const pet_os_geom* g, const pet_os_par
     st.have_frozen = 0;
     st.may_allocate = false;    // y and r read in their natural layout
     const bool need_nu = p->mode == PET_OS_P1 || p->mode == PET_OS_P2;
-    if ((rc = work_place(g, need_nu, base, SCRATCH_BYTES, &st.w, s))) return rc;
+    if ((rc = work_place(g, need_nu, base, SCRATCH_BYTES, PET_OS_NOALLOC_SCRATCH_BYTES, &st.w, s))) return rc;
     // the data check of Sec. II-A before anything of the iterations is queued
     if ((rc = check_data(g, p, &st.w, f, y, r, s))) return rc;
     return run_plain(&st, f, y, r, n_iter, s);
