@@ -69,7 +69,10 @@ def kernel_source_hash():
     import re
     h = hashlib.sha256()
     for name in ("kernels.hip", "kernels3d.hip", "kernels3q.hip", "pen3.h", "devutil.h", "raygeom.h"):
-        with open(os.path.join(ROOT, "paper_2111_07886_amd", "csrc", name), encoding="utf-8") as fh:
+        path = os.path.join(ROOT, "paper_2111_07886_amd", "csrc", name)
+        if not os.path.exists(path):
+            continue
+        with open(path, encoding="utf-8") as fh:
             src = fh.read()
         src = re.sub(r"/\*.*?\*/", " ", src, flags=re.S)
         src = re.sub(r"//[^\n]*", " ", src)
