@@ -450,7 +450,8 @@ struct BP3QArgs {
 constexpr int BQ_X = 4, BQ_Y = 4;      // column pairs of a tile: a row of four per wave
 constexpr int BQ_C = BQ_X * BQ_Y;      // column pairs of a tile
 constexpr int BQ_W = 4;                // column pairs of a wave
-constexpr int BQ_DG = 2;               // ring-difference magnitudes staged together
+// ring-difference magnitudes staged together, by the lanes per k-range
+__host__ __device__ constexpr int bq_dg(int kl) { return kl == 32 ? 4 : 2; }
 constexpr int BQ_PAD = 64;             // zeros before the first staged row (k - o < 0, and pieces that are none)
 constexpr int BQ_AMAX = 16;            // angles per chunk (axis-parallel ones, two at most, count twice)
 constexpr int BQ_E = 4;                // angles whose hits are found together
@@ -489,12 +490,13 @@ constexpr unsigned long long BQ_SECOND = 0xff00ff00ff00ff00ull;    // lanes of s
 // pairs to dst, a quad per thread at a time.  s: the pairs' row of magnitude
 // d, dstep bytes to the next (wave-uniform, so that a copy's address is a
 // scalar base and the thread's offset).  Returns without waiting.
+template <int DG>
 __device__ __forceinline__ void bq_stage(float4* dst, const char* s, long long dstep, int ng, int n4, int wave) {
     typedef __attribute__((address_space(3))) void* Lds;
     for (int e0 = 0; e0 < n4; e0 += NT) {
         if (e0 + (int)threadIdx.x < n4) {
 #pragma unroll
-            for (int e = 0; e < BQ_DG; ++e)
+            for (int e = 0; e < DG; ++e)
                 if (e < ng)
                     __builtin_amdgcn_global_load_lds(
                         reinterpret_cast<const float*>(s + e * dstep + (size_t)e0 * 16 + threadIdx.x * 16u),
@@ -549,11 +551,12 @@ __device__ __forceinline__ void bq_hits(const GeoK& g, BP3QShared& sh, int e0, i
 
 // The pieces of the wave's columns for magnitudes ddc .. ddc + BQ_DC - 1: lane =
 // (column, hit, magnitude).
+template <int DG>
 __device__ __forceinline__ void bq_pieces(const GeoK& g, BP3QShared& sh, int el, int ddc, int nrow, int wave, int lane,
                                           BQMasks& M) {
     static_assert(BQ_W * 2 * BQ_DC == 64, "a lane per column, hit and magnitude");
     const int c = lane >> 4, h = (lane >> 3) & 1, dd = ddc + (lane & 7);
-    const int ds = min(BQ_DG, g.max_rd + 1 - (dd - dd % BQ_DG)) - 1 - dd % BQ_DG;   // largest first
+    const int ds = min(DG, g.max_rd + 1 - (dd - dd % DG)) - 1 - dd % DG;   // largest first
     const float4 H = sh.hit[el][wave * BQ_W + c][h];
     const int rf = sh.row[el][wave * BQ_W + c][h];
     // the piece's axial range in slice units (FP32: at most 1/2 + D, its
@@ -627,10 +630,11 @@ __device__ __forceinline__ void bq_orient(float (&acc)[sizeof...(J)][4], unsigne
 template <int KL, bool AXIS, int J>
 __device__ __forceinline__ void bq_next(float (&acc)[4], const BQMasks& M, const int2* pl, const char* __restrict__ lb,
                                         int h, int src0, unsigned long long turn, int grp) {
+    constexpr int DG = bq_dg(KL);
     const int src = 16 * J + 8 * h + src0;
     unsigned m = (unsigned)(M.split >> src);
     if (KL == 32) m |= (unsigned)(M.split >> (32 + src));
-    m &= (1u << BQ_DG) - 1;
+    m &= (1u << DG) - 1;
     if (m == 0) return;
     const bool any = h == 1 && bq_any<KL>(turn, J), on = any && bq_bit<KL>(turn, J, grp);
     const bool up = bq_bit<KL>(h ? M.upper >> 8 : M.upper, J, grp);
@@ -648,22 +652,23 @@ __device__ __forceinline__ void bq_next(float (&acc)[4], const BQMasks& M, const
     if (any) bq_swap(acc, on);
 }
 
-// apply hit h's pieces of column slots J0 .. J0 + N - 1, BQ_DG magnitudes each,
+// apply hit h's pieces of column slots J0 .. J0 + N - 1, DG magnitudes each,
 // from the staged rows: their reads in flight together
 template <int KL, bool AXIS, int J0, int N, int CPG>
 __device__ __forceinline__ void bq_apply(float (&acc)[CPG][4], const int2* pl, int h, const char* __restrict__ lb,
                                          unsigned long long upper, int grp) {
-    int4 q[N][BQ_DG / 2];
-    float4 x[N][BQ_DG];
+    constexpr int DG = bq_dg(KL);
+    int4 q[N][DG / 2];
+    float4 x[N][DG];
 #pragma unroll
     for (int j = 0; j < N; ++j)
 #pragma unroll
-        for (int e = 0; e < BQ_DG / 2; ++e)
+        for (int e = 0; e < DG / 2; ++e)
             q[j][e] = *reinterpret_cast<const int4*>(pl + ((J0 + j) * 2 + h) * BQ_DC + 2 * e);
 #pragma unroll
     for (int j = 0; j < N; ++j)
 #pragma unroll
-        for (int e = 0; e < BQ_DG / 2; ++e) {
+        for (int e = 0; e < DG / 2; ++e) {
             x[j][2 * e] = *reinterpret_cast<const float4*>(lb + q[j][e].x);
             x[j][2 * e + 1] = *reinterpret_cast<const float4*>(lb + q[j][e].z);
         }
@@ -671,7 +676,7 @@ __device__ __forceinline__ void bq_apply(float (&acc)[CPG][4], const int2* pl, i
     for (int j = 0; j < N; ++j) {
         const bool up = bq_bit<KL>(upper, J0 + j, grp);
 #pragma unroll
-        for (int e = 0; e < BQ_DG / 2; ++e) {
+        for (int e = 0; e < DG / 2; ++e) {
             bq_fma<AXIS>(acc[J0 + j], q[j][e].y, up, x[j][2 * e]);
             bq_fma<AXIS>(acc[J0 + j], q[j][e].w, up, x[j][2 * e + 1]);
         }
@@ -686,15 +691,15 @@ __device__ __forceinline__ void bq_column(float (&acc)[CPG][4], const BQMasks& M
     if (bq_any<KL>(M.valid >> 8, J)) bq_apply<KL, AXIS, J, 1>(acc, pl, 1, lb, M.upper >> 8, grp);
 }
 
-// apply the pieces of magnitudes dd0 .. dd0 + BQ_DG - 1 (src0: the first
+// apply the pieces of magnitudes dd0 .. dd0 + DG - 1 (src0: the first
 // one's place among those held): the first hits of the wave's columns, the
 // second hits that there are, and the few second slices
 template <int KL, bool AXIS, int... J>
 __device__ __forceinline__ void bq_gather(float (&acc)[sizeof...(J)][4], const BQMasks& M, const int2* pl,
                                           const char* __restrict__ lb, int src0, int grp,
                                           std::integer_sequence<int, J...>) {
-    constexpr int CPG = sizeof...(J), N = std::min(CPG, 4 / BQ_DG);
-    static_assert(BQ_DG % 2 == 0 && CPG <= 2 * N, "pairs of magnitudes, at most two batches of columns");
+    constexpr int DG = bq_dg(KL), CPG = sizeof...(J), N = std::min(CPG, 4 / DG);
+    static_assert(DG % 2 == 0 && CPG <= 2 * N, "pairs of magnitudes, at most two batches of columns");
     bq_apply<KL, AXIS, 0, N>(acc, pl, 0, lb, M.upper, grp);
     if constexpr (N < CPG) bq_apply<KL, AXIS, N, CPG - N>(acc, pl, 0, lb, M.upper, grp);
     // columns whose second hit lies on the other side of the centre
@@ -704,7 +709,7 @@ __device__ __forceinline__ void bq_gather(float (&acc)[sizeof...(J)][4], const B
         (bq_column<KL, AXIS, J, CPG>(acc, M, pl, lb, grp), ...);
         if (turn) (bq_swap(acc[J], bq_bit<KL>(turn, J, grp)), ...);
     }
-    constexpr unsigned long long LANES = ((1ull << BQ_DG) - 1) * 0x0101010101010101ull;
+    constexpr unsigned long long LANES = ((1ull << DG) - 1) * 0x0101010101010101ull;
     if (M.split & (LANES << src0))
         ((bq_next<KL, AXIS, J>(acc[J], M, pl, lb, 0, src0, turn, grp),
           bq_next<KL, AXIS, J>(acc[J], M, pl, lb, 1, src0, turn, grp)), ...);
@@ -718,6 +723,7 @@ template <int KL, bool AXIS, int CPG>
 __device__ __forceinline__ void bq_angles(const GeoK& g, const BP3QArgs& A, BP3QShared& sh, int e0, int e1, int ne, int c0,
                                           float (&acc)[CPG][4], unsigned long long& sw, int& cur, float4* s_w, int wave,
                                           int lane) {
+    constexpr int DG = bq_dg(KL);
     constexpr auto COLS = std::make_integer_sequence<int, CPG>{};
     const int D = g.max_rd, nz = g.nz, NP = (g.n_radial + 1) / 2, grp = lane / KL;
     const long long dstep = (long long)NP * nz * 16;  // bytes of one magnitude
@@ -733,13 +739,13 @@ __device__ __forceinline__ void bq_angles(const GeoK& g, const BP3QArgs& A, BP3Q
         const char* srcn = reinterpret_cast<const char*>(A.wq + ((long long)(c0 + aln) * (D + 1) * NP + plon) * nz);
         BQMasks M;
 #pragma unroll 1
-        for (int dd0 = 0; dd0 <= D; dd0 += BQ_DG) {
+        for (int dd0 = 0; dd0 <= D; dd0 += DG) {
             const int src0 = dd0 % BQ_DC;
             if (src0 == 0) {
-                bq_pieces(g, sh, e % BQ_E, dd0, nrow, wave, lane, M);
+                bq_pieces<DG>(g, sh, e % BQ_E, dd0, nrow, wave, lane, M);
                 bq_orient<KL>(acc, sw, M, AXIS && ((e - sh.n_oblique) & 1), grp, COLS);
             }
-            const int ddn = dd0 + BQ_DG <= D ? dd0 + BQ_DG : 0;
+            const int ddn = dd0 + DG <= D ? dd0 + DG : 0;
             const bool more = ddn > 0 || e + 1 < ne;
             float4* nxt = s_w + (cur ? 0 : A.buf) + BQ_PAD;
             const char* lb = reinterpret_cast<const char*>(s_w + (cur ? A.buf : 0) + lane % KL);
@@ -747,7 +753,7 @@ __device__ __forceinline__ void bq_angles(const GeoK& g, const BP3QArgs& A, BP3Q
             __builtin_amdgcn_s_waitcnt(0);      // this wave's copies have landed
             __syncthreads();                    // and every wave's; the other buffer is read no more
             if (more)
-                bq_stage(nxt, ddn ? src + ddn * dstep : srcn, dstep, min(BQ_DG, D + 1 - ddn), (ddn ? nrow : nrown) * nz,
+                bq_stage<DG>(nxt, ddn ? src + ddn * dstep : srcn, dstep, min(DG, D + 1 - ddn), (ddn ? nrow : nrown) * nz,
                          wave);
             bq_gather<KL, AXIS>(acc, M, pl + src0, lb, src0, grp, COLS);
         }
@@ -815,9 +821,9 @@ __device__ __forceinline__ void bp3q_body(const GeoK& g, const BP3QArgs& A, int 
         {
             const int plo = __builtin_amdgcn_readfirstlane(sh.plo[0]), nrow = __builtin_amdgcn_readfirstlane(sh.nrow[0]);
             const int al = __builtin_amdgcn_readfirstlane(sh.al[0]), D = g.max_rd, NP = (Nr + 1) / 2;
-            bq_stage(s_w + BQ_PAD,
+            bq_stage<bq_dg(KL)>(s_w + BQ_PAD,
                      reinterpret_cast<const char*>(A.wq + ((long long)(c0 + al) * (D + 1) * NP + plo) * nz),
-                     (long long)NP * nz * 16, min(BQ_DG, D + 1), nrow * nz, wave);
+                     (long long)NP * nz * 16, min(bq_dg(KL), D + 1), nrow * nz, wave);
         }
 #pragma unroll 1
         for (int e0 = 0; e0 < ne; e0 += BQ_E) {
@@ -876,7 +882,9 @@ __device__ __forceinline__ bool bq_tile(const GeoK& g, int block, int& tile) {
 // 32 KB of LDS, so that five blocks of a CU hide each other's waits: four
 // magnitudes at a time (three blocks) measured 171 us, this 117 (200x200x64,
 // 281 bins, 8 angles, ring differences to 15, with the penalty blocks); the
-// column tiles of k_bp3, which take every LOR by itself, 180.9.
+// column tiles of k_bp3, which take every LOR by itself, 180.9.  With at most
+// 32 slices four magnitudes fit, and half the barriers and copies in flight
+// per piece: 41.0 -> 33.9 us (128x128x32, 185 bins, 9 angles, to 7).
 //
 // The first bp_blocks blocks back-project; A.n_pen more compute the penalty
 // gradient and mu of the entering iterate (pen3_body, halo tile in the
@@ -904,7 +912,9 @@ static int bq_rows(const pet_os_geom* G) {
 }
 
 // (a lane past the last slice reads up to 63 - nz past a row)
-static int bq_buf(const pet_os_geom* G) { return BQ_PAD + BQ_DG * bq_rows(G) * G->d.nz + 64 - std::min(G->d.nz, 64); }
+static int bq_buf(const pet_os_geom* G) {
+    return BQ_PAD + bq_dg(G->d.nz > 32 ? 64 : 32) * bq_rows(G) * G->d.nz + 64 - std::min(G->d.nz, 64);
+}
 
 size_t bp3q_lds(const pet_os_geom* G) {
     return std::max<size_t>(2 * (size_t)bq_buf(G) * sizeof(float4), PEN3_HALO * sizeof(float));
