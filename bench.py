@@ -447,7 +447,7 @@ def bench_batched(args, cpu=True):
     iters = [n for _, _, n in reqs]
     if getattr(args, "calibrate_copy", False):
         calibrate_copy(dev)
-    # warm-up (graph capture, caches)
+    # warm-up (work lists, caches)
     progress("batched: geometries ready, timing")
     fs = [torch.tensor(w.f0, dtype=torch.float32, device=dev) for w, _, _ in reqs]
     pet.reconstruct_batch(geoms, params, fs, ys, rs, [1] * len(reqs))

@@ -341,11 +341,9 @@ int pet_os_batch_add(pet_os_batch* batch, const pet_os_geom* geom, const pet_os_
 /* Release a slot (synchronises `stream`); its f holds the last iterate. */
 int pet_os_batch_remove(pet_os_batch* batch, int32_t slot, pet_os_stream stream);
 /* Queue n_steps batched subiterations on `stream` (asynchronous).  After
- * slots joined or left, the first step rebuilds the work lists and captures
- * a new graph (on a private stream, thread-local capture mode).  A capture
- * fails if another thread issues default-stream (NULL-stream) work at the
- * same time, so a program that drives batches and other pet_os calls from
- * several threads serializes those calls (the server does). */
+ * slots joined or left, the first step waits for the stream and rebuilds the
+ * work lists.  Refused on a capturing stream.  A program that drives one batch
+ * from several threads serializes its calls. */
 int pet_os_batch_step(pet_os_batch* batch, int32_t n_steps, pet_os_stream stream);
 /* Queue as many steps as the longest active request still needs. */
 int pet_os_batch_run(pet_os_batch* batch, pet_os_stream stream);

@@ -429,7 +429,7 @@ def reconstruct_noalloc(geom: Geometry, params: dict, f, y, r, n_iter: int, stre
 
 class Batch:
     """pet_os_batch: independent reconstructions advanced together, one
-    captured batched subiteration per step."""
+    batched subiteration per step."""
 
     def __init__(self, max_slots: int):
         h = _P()

@@ -1,7 +1,6 @@
 // batch.cpp -- many independent reconstructions of uneven sizes advanced
 // together: one batched subiteration (forward + ratio, back-projection +
-// stencil, update, advance) for every active request per launch sequence,
-// captured once in a hipGraph and replayed.
+// stencil, update) for every active request per launch sequence.
 //
 // Each request keeps its iterate, scratch, FP64-derived schedule (lambda_k
 // alpha_{k,i} and the nu mode of eq:nuki for every subiteration, evaluated on
@@ -58,13 +57,8 @@ struct pet_os_batch {
     int count[WL_COUNT] = {};
     int* d_counts = nullptr;
     int grids[WL_COUNT] = {};
-    int live_mask = 0;               // lists launched by the captured graph
     size_t bp3q_lds = 0;             // dynamic LDS of the quad back-projection: the largest of the slots'
     bool lists_dirty = true;
-    bool graph_ok = false;
-    hipStream_t cap_stream = nullptr;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
     size_t bytes = 0;
 };
 
@@ -121,7 +115,7 @@ int rebuild_lists(pet_os_batch* B) {
         }
     }
     std::vector<Item> L[WL_COUNT];
-    size_t bp_lds = 0;
+    B->bp3q_lds = 0;
     for (int s = 0; s < B->max_slots; ++s) {
         const BatchSlot& S = B->slots[s];
         if (!S.used) continue;
@@ -139,7 +133,7 @@ int rebuild_lists(pet_os_batch* B) {
         const int wbp = quad ? WL_BP3Q + wide
                         : d3 ? WL_BP3 + 2 * zi + (bp3_nbs_of(S.g) == 40 ? 1 : 0)
                              : WL_BP0 + S.bp_kind;
-        if (quad) bp_lds = std::max(bp_lds, bp3q_lds(S.g));
+        if (quad) B->bp3q_lds = std::max(B->bp3q_lds, bp3q_lds(S.g));
         for (int b = 0; b < nbp; ++b) L[wbp].push_back({s, b});
         if (d3) {
             const int npen = pen3_grid(S.g);
@@ -148,7 +142,6 @@ int rebuild_lists(pet_os_batch* B) {
             for (int b = 0; b < nup; ++b) L[WL_UPD3].push_back({s, b});
         }
     }
-    int mask = 0;
     for (int k = 0; k < WL_COUNT; ++k) {
         const int n = (int)L[k].size();
         if (n > B->cap[k]) {
@@ -158,39 +151,14 @@ int rebuild_lists(pet_os_batch* B) {
             if (hipMalloc(&B->d_items[k], (size_t)std::max(c, 1) * sizeof(Item)) != hipSuccess)
                 return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of work list failed");
             B->cap[k] = c;
-            B->graph_ok = false;       // captured kernel arguments point at the old list
         }
         if (n) PETOS_HIP(hipMemcpy(B->d_items[k], L[k].data(), (size_t)n * sizeof(Item), hipMemcpyHostToDevice));
         B->count[k] = n;
-        if (n) mask |= 1 << k;
-    }
-    // the graph launches only the non-empty lists: capture again when that set
-    // changes or a slot needs more LDS
-    if (mask != B->live_mask || bp_lds > B->bp3q_lds) {
-        B->live_mask = mask;
-        B->bp3q_lds = std::max(B->bp3q_lds, bp_lds);
-        B->graph_ok = false;
+        // multiples of 8: the kernels deal contiguous item runs to each XCD
+        B->grids[k] = 8 * ((std::min(n, GRID_CAP) + 7) / 8);
     }
     PETOS_HIP(hipMemcpy(B->d_counts, B->count, sizeof(B->count), hipMemcpyHostToDevice));
     B->lists_dirty = false;
-    return PET_OS_OK;
-}
-
-int capture(pet_os_batch* B) {
-    if (B->exec) { (void)hipGraphExecDestroy(B->exec); B->exec = nullptr; }
-    if (B->graph) { (void)hipGraphDestroy(B->graph); B->graph = nullptr; }
-    // multiples of 8: the kernels deal contiguous item runs to each XCD
-    for (int k = 0; k < WL_COUNT; ++k) B->grids[k] = 8 * ((std::max(1, std::min(B->cap[k], GRID_CAP)) + 7) / 8);
-    PETOS_HIP(hipStreamBeginCapture(B->cap_stream, hipStreamCaptureModeThreadLocal));
-    int rc = launch_batch_step(B->d_slots, B->max_slots, B->d_items, B->d_counts, B->grids, B->live_mask,
-                               B->bp3q_lds, B->cap_stream);
-    hipGraph_t g = nullptr;
-    hipError_t e = hipStreamEndCapture(B->cap_stream, &g);
-    if (rc) { if (g) (void)hipGraphDestroy(g); return rc; }
-    if (e != hipSuccess) return fail(PET_OS_ERR_DEVICE, std::string("graph capture: ") + hipGetErrorString(e));
-    B->graph = g;
-    PETOS_HIP(hipGraphInstantiate(&B->exec, B->graph, nullptr, nullptr, 0));
-    B->graph_ok = true;
     return PET_OS_OK;
 }
 
@@ -214,8 +182,7 @@ int pet_os_batch_create(int32_t max_slots, pet_os_batch** out) {
     }
     if (hipMemcpy(B->d_slots, B->h_slots.data(), sizeof(SlotDev) * (size_t)max_slots, hipMemcpyHostToDevice) !=
             hipSuccess ||
-        hipMemset(B->d_counts, 0, sizeof(int) * WL_COUNT) != hipSuccess ||
-        hipStreamCreateWithFlags(&B->cap_stream, hipStreamNonBlocking) != hipSuccess) {
+        hipMemset(B->d_counts, 0, sizeof(int) * WL_COUNT) != hipSuccess) {
         (void)hipFree(B->d_slots);
         (void)hipFree(B->d_counts);
         delete B;
@@ -230,13 +197,10 @@ int pet_os_batch_destroy(pet_os_batch* B) {
     (void)hipDeviceSynchronize();
     for (auto& s : B->slots)
         if (s.used) slot_release(s);
-    if (B->exec) (void)hipGraphExecDestroy(B->exec);
-    if (B->graph) (void)hipGraphDestroy(B->graph);
     for (int k = 0; k < WL_COUNT; ++k)
         if (B->d_items[k]) (void)hipFree(B->d_items[k]);
     (void)hipFree(B->d_slots);
     (void)hipFree(B->d_counts);
-    if (B->cap_stream) (void)hipStreamDestroy(B->cap_stream);
     delete B;
     return PET_OS_OK;
 }
@@ -370,12 +334,20 @@ int pet_os_batch_step(pet_os_batch* B, int32_t n_steps, pet_os_stream stream) {
     if (!B || n_steps < 0) return fail(PET_OS_ERR_INVALID_ARG, "bad argument");
     hipStream_t st = (hipStream_t)stream;
     int rc;
+    // (a step is not for a caller's own graph: the host counts the steps)
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    PETOS_HIP(hipStreamIsCapturing(st, &cs));
+    if (cs != hipStreamCaptureStatusNone) return fail(PET_OS_ERR_DEVICE, "batch step on a capturing stream");
     if (B->lists_dirty) {
         PETOS_HIP(hipStreamSynchronize(st));
         if ((rc = rebuild_lists(B))) return rc;
     }
-    if (!B->graph_ok && (rc = capture(B))) return rc;
-    for (int n = 0; n < n_steps; ++n) PETOS_HIP(hipGraphLaunch(B->exec, st));
+    // Launched one by one: queued kernels of a stream follow each other without
+    // a gap, where a graph of one step (3 to 9 kernels) left 8 us before each
+    // of its launches, more than a kernel's launch costs the host.
+    for (int n = 0; n < n_steps; ++n)
+        if ((rc = launch_batch_step(B->d_slots, n, B->d_items, B->d_counts, B->grids, B->bp3q_lds, st))) return rc;
+    if (n_steps > 0 && (rc = launch_batch_advance(B->d_slots, B->max_slots, n_steps, st))) return rc;
     for (auto& s : B->slots)
         if (s.used) s.J_next = std::min<int64_t>(s.J_end + 1, s.J_next + n_steps);
     return PET_OS_OK;

@@ -352,20 +352,22 @@ struct Item {
 enum { WL_FP = 0, WL_BP0 = 1, WL_BP1 = 2, WL_FP3 = 3, WL_BP3 = 4, WL_UPD3 = 10, WL_PEN3 = 11, WL_FP3Q = 12, WL_BP3Q = 14,
        WL_COUNT = 16 };
 
-// Queue one batched subiteration (every active slot advances by one):
-// forward, back-projection (one launch per tile kind), update, advance.
-// Lists whose bit is clear in `live_mask` are not launched.
-int launch_batch_step(SlotDev* d_slots, int n_slots, Item* const lists[WL_COUNT], const int* d_counts,
-                      const int grids[WL_COUNT], int live_mask, size_t bp3q_lds_bytes, hipStream_t s);
-void launch_batch3q_fp(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, int kl, hipStream_t s);
-void launch_batch3q_bp(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, int kl, size_t lds,
+// Queue one batched subiteration, the step-th since the slots' counters moved:
+// forward, back-projection (one launch per tile kind), update.  Empty lists
+// (no grid) are not launched.  launch_batch_advance moves the counters on.
+int launch_batch_step(const SlotDev* d_slots, int step, Item* const lists[WL_COUNT], const int* d_counts,
+                      const int grids[WL_COUNT], size_t bp3q_lds_bytes, hipStream_t s);
+int launch_batch_advance(SlotDev* d_slots, int n_slots, int n, hipStream_t s);
+void launch_batch3q_fp(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, int step, int kl,
                        hipStream_t s);
-void launch_batch3_fp(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, hipStream_t s);
-void launch_batch3_bp(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, int zb, int nbs,
+void launch_batch3q_bp(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, int step, int kl, size_t lds,
+                       hipStream_t s);
+void launch_batch3_fp(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, int step, hipStream_t s);
+void launch_batch3_bp(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, int step, int zb, int nbs,
                       hipStream_t s);
 int bp3_nbs_of(const pet_os_geom* g);   // LDS row stride of the 3D back-projector (20 or 40)
-void launch_batch3_upd(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, hipStream_t s);
-void launch_batch3_pen(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, hipStream_t s);
+void launch_batch3_upd(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, int step, hipStream_t s);
+void launch_batch3_pen(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, int step, hipStream_t s);
 
 }  // namespace petos
 

@@ -1336,7 +1336,9 @@ int launch_rdp_value(const pet_os_geom* G, const float* f, float gamma_R, float 
 // grid stride; the lists, their lengths and the slot table live in device
 // memory, so one captured graph stays valid while requests come and go.
 
-__device__ __forceinline__ bool slot_live(const SlotDev& d) { return d.active && d.J <= d.J_end; }
+// (subiteration J of the slot: a queued step's kernels add its number to the
+// counter, which moves on when all steps of a call are queued)
+__device__ __forceinline__ bool slot_live(const SlotDev& d, int J) { return d.active && J <= d.J_end; }
 
 __device__ void fp_dispatch(const GeoK& g, const FPArgs& A, int seg, long long vblock) {
     switch (seg) {
@@ -1347,16 +1349,18 @@ __device__ void fp_dispatch(const GeoK& g, const FPArgs& A, int seg, long long v
     }
 }
 
-__global__ __launch_bounds__(NT) void k_fp_batch(const SlotDev* __restrict__ S, const Item* __restrict__ items, const int* __restrict__ count) {
+__global__ __launch_bounds__(NT) void k_fp_batch(const SlotDev* __restrict__ S, const Item* __restrict__ items,
+                                                 const int* __restrict__ count, int step) {
     const int n = *count;
     for (int it = blockIdx.x; it < n; it += gridDim.x) {
         const Item I = items[it];
         const SlotDev& d = S[I.slot];
-        if (!slot_live(d)) continue;
-        const int i = (d.J - 1) % d.g.n_subsets;
+        const int J = d.J + step;
+        if (!slot_live(d, J)) continue;
+        const int i = (J - 1) % d.g.n_subsets;
         if (I.block >= d.n_fp) {
             // pixel pass: snapshot of f and mu, PX_ITEM pixel blocks per item
-            const int nu_mode = d.sched_nu[d.J - 1];
+            const int nu_mode = d.sched_nu[J - 1];
             PxArgs P;
             P.f = d.f;
             P.fsnap = d.fsnap;
@@ -1391,14 +1395,16 @@ __global__ __launch_bounds__(NT) void k_fp_batch(const SlotDev* __restrict__ S, 
 // references need more than 72 without spilling to scratch (6 waves: 80
 // VGPRs and 7 spilled; 5 waves measured 1 % faster, with no scratch traffic)
 template <class T>
-__global__ __launch_bounds__(NT, 5) void k_bp_batch(const SlotDev* __restrict__ S, const Item* __restrict__ items, const int* __restrict__ count) {
+__global__ __launch_bounds__(NT, 5) void k_bp_batch(const SlotDev* __restrict__ S, const Item* __restrict__ items,
+                                                    const int* __restrict__ count, int step) {
     const int n = *count;
     for (int it = blockIdx.x; it < n; it += gridDim.x) {
         const Item I = items[it];
         const SlotDev& d = S[I.slot];
-        if (!slot_live(d)) continue;
-        const int i = (d.J - 1) % d.g.n_subsets;
-        const int nu_mode = d.sched_nu[d.J - 1];
+        const int J = d.J + step;
+        if (!slot_live(d, J)) continue;
+        const int i = (J - 1) % d.g.n_subsets;
+        const int nu_mode = d.sched_nu[J - 1];
         BPArgs A{};
         A.w = d.w;
         A.w_natural = 0;
@@ -1419,7 +1425,7 @@ __global__ __launch_bounds__(NT, 5) void k_bp_batch(const SlotDev* __restrict__ 
         A.pnorm = d.pnorm;
         A.nu_frozen = d.nu_frozen;
         A.nu_mode = nu_mode;
-        A.step = d.sched_step[d.J - 1];
+        A.step = d.sched_step[J - 1];
         A.nu1 = d.nu1;
         A.nu2 = d.nu2;
         A.box = d.box;
@@ -1433,39 +1439,47 @@ __global__ __launch_bounds__(NT, 5) void k_bp_batch(const SlotDev* __restrict__ 
     }
 }
 
-// J += 1 for every live slot (one thread per slot, after the update)
-__global__ __launch_bounds__(NT) void k_advance(SlotDev* S, int n_slots) {
+// J past the n queued steps for every live slot (one thread per slot)
+__global__ __launch_bounds__(NT) void k_advance(SlotDev* S, int n_slots, int n) {
     const int sidx = blockIdx.x * NT + threadIdx.x;
-    if (sidx < n_slots && S[sidx].active && S[sidx].J <= S[sidx].J_end) S[sidx].J += 1;
+    if (sidx < n_slots && S[sidx].active && S[sidx].J <= S[sidx].J_end)
+        S[sidx].J += min(n, S[sidx].J_end + 1 - S[sidx].J);
 }
 
-int launch_batch_step(SlotDev* d_slots, int n_slots, Item* const lists[WL_COUNT], const int* d_counts,
-                      const int grids[WL_COUNT], int live_mask, size_t bp3q_lds_bytes, hipStream_t s) {
-    auto live = [&](int k) { return (live_mask >> k) & 1; };
+int launch_batch_advance(SlotDev* d_slots, int n_slots, int n, hipStream_t s) {
+    hipLaunchKernelGGL(k_advance, dim3((n_slots + NT - 1) / NT), dim3(NT), 0, s, d_slots, n_slots, n);
+    PETOS_HIP(hipGetLastError());
+    return PET_OS_OK;
+}
+
+int launch_batch_step(const SlotDev* d_slots, int step, Item* const lists[WL_COUNT], const int* d_counts,
+                      const int grids[WL_COUNT], size_t bp3q_lds_bytes, hipStream_t s) {
+    auto live = [&](int k) { return grids[k] > 0; };
     if (live(WL_FP))
-        hipLaunchKernelGGL(k_fp_batch, dim3(grids[WL_FP]), dim3(NT), 0, s, d_slots, lists[WL_FP], d_counts + WL_FP);
-    if (live(WL_FP3)) launch_batch3_fp(d_slots, lists[WL_FP3], d_counts + WL_FP3, grids[WL_FP3], s);
+        hipLaunchKernelGGL(k_fp_batch, dim3(grids[WL_FP]), dim3(NT), 0, s, d_slots, lists[WL_FP], d_counts + WL_FP,
+                           step);
+    if (live(WL_FP3)) launch_batch3_fp(d_slots, lists[WL_FP3], d_counts + WL_FP3, grids[WL_FP3], step, s);
     for (int k = 0; k < 2; ++k)
         if (live(WL_FP3Q + k))
-            launch_batch3q_fp(d_slots, lists[WL_FP3Q + k], d_counts + WL_FP3Q + k, grids[WL_FP3Q + k], k ? 64 : 32, s);
+            launch_batch3q_fp(d_slots, lists[WL_FP3Q + k], d_counts + WL_FP3Q + k, grids[WL_FP3Q + k], step,
+                              k ? 64 : 32, s);
     if (live(WL_BP0))
         hipLaunchKernelGGL((k_bp_batch<Tile2L>), dim3(grids[WL_BP0]), dim3(NT), bp_lds_budget(0), s, d_slots,
-                           lists[WL_BP0], d_counts + WL_BP0);
+                           lists[WL_BP0], d_counts + WL_BP0, step);
     if (live(WL_BP1))
         hipLaunchKernelGGL((k_bp_batch<Tile2S>), dim3(grids[WL_BP1]), dim3(NT), bp_lds_budget(1), s, d_slots,
-                           lists[WL_BP1], d_counts + WL_BP1);
+                           lists[WL_BP1], d_counts + WL_BP1, step);
     const int zbs[3] = {16, 32, 64};
     for (int k = 0; k < 6; ++k)
         if (live(WL_BP3 + k))
-            launch_batch3_bp(d_slots, lists[WL_BP3 + k], d_counts + WL_BP3 + k, grids[WL_BP3 + k], zbs[k / 2],
+            launch_batch3_bp(d_slots, lists[WL_BP3 + k], d_counts + WL_BP3 + k, grids[WL_BP3 + k], step, zbs[k / 2],
                              (k & 1) ? 40 : 20, s);
     for (int k = 0; k < 2; ++k)
         if (live(WL_BP3Q + k))
-            launch_batch3q_bp(d_slots, lists[WL_BP3Q + k], d_counts + WL_BP3Q + k, grids[WL_BP3Q + k], k ? 64 : 32,
-                              bp3q_lds_bytes, s);
-    if (live(WL_PEN3)) launch_batch3_pen(d_slots, lists[WL_PEN3], d_counts + WL_PEN3, grids[WL_PEN3], s);
-    if (live(WL_UPD3)) launch_batch3_upd(d_slots, lists[WL_UPD3], d_counts + WL_UPD3, grids[WL_UPD3], s);
-    hipLaunchKernelGGL(k_advance, dim3((n_slots + NT - 1) / NT), dim3(NT), 0, s, d_slots, n_slots);
+            launch_batch3q_bp(d_slots, lists[WL_BP3Q + k], d_counts + WL_BP3Q + k, grids[WL_BP3Q + k], step,
+                              k ? 64 : 32, bp3q_lds_bytes, s);
+    if (live(WL_PEN3)) launch_batch3_pen(d_slots, lists[WL_PEN3], d_counts + WL_PEN3, grids[WL_PEN3], step, s);
+    if (live(WL_UPD3)) launch_batch3_upd(d_slots, lists[WL_UPD3], d_counts + WL_UPD3, grids[WL_UPD3], step, s);
     PETOS_HIP(hipGetLastError());
     return PET_OS_OK;
 }

@@ -1110,20 +1110,22 @@ int launch_prep3(const pet_os_geom* G, const float* f, float* fz, Reduction red,
 
 // ------------------------------------------------------------------ batched (persistent) kernels
 
-__device__ __forceinline__ bool slot_live3(const SlotDev& d) { return d.active && d.J <= d.J_end; }
+__device__ __forceinline__ bool slot_live3(const SlotDev& d, int J) { return d.active && J <= d.J_end; }
 
 // Position of a persistent block in the item list: each XCD (blocks are
 // dealt to the 8 XCDs round-robin) takes contiguous runs of items.  The grid
 // is a multiple of 8.
 __device__ __forceinline__ int xcd_item(int block, int grid) { return (block % 8) * (grid / 8) + block / 8; }
 
-__global__ __launch_bounds__(NT) void k_fp3_batch(const SlotDev* __restrict__ S, const Item* __restrict__ items, const int* __restrict__ count) {
+__global__ __launch_bounds__(NT) void k_fp3_batch(const SlotDev* __restrict__ S, const Item* __restrict__ items,
+                                                    const int* __restrict__ count, int step) {
     const int n = *count;
     for (int it = xcd_item(blockIdx.x, gridDim.x); it < n; it += gridDim.x) {
         const Item I = items[it];
         const SlotDev& d = S[I.slot];
-        if (!slot_live3(d)) continue;
-        const int i = (d.J - 1) % d.g.n_subsets;
+        const int J = d.J + step;
+        if (!slot_live3(d, J)) continue;
+        const int i = (J - 1) % d.g.n_subsets;
         FP3Args A{};
         A.fz = d.fz;
         A.y = d.y;
@@ -1138,15 +1140,17 @@ __global__ __launch_bounds__(NT) void k_fp3_batch(const SlotDev* __restrict__ S,
 }
 
 template <int ZB, int NBS>
-__global__ __launch_bounds__(NT) void k_bp3_batch(const SlotDev* __restrict__ S, const Item* __restrict__ items, const int* __restrict__ count) {
+__global__ __launch_bounds__(NT) void k_bp3_batch(const SlotDev* __restrict__ S, const Item* __restrict__ items,
+                                                    const int* __restrict__ count, int step) {
     __shared__ BP3Shared sh;
     __shared__ __attribute__((aligned(16))) float s_w[BP3_LDS];
     const int n = *count;
     for (int it = xcd_item(blockIdx.x, gridDim.x); it < n; it += gridDim.x) {
         const Item I = items[it];
         const SlotDev& d = S[I.slot];
-        if (!slot_live3(d) || d.zb != ZB) continue;
-        const int i = (d.J - 1) % d.g.n_subsets;
+        const int J = d.J + step;
+        if (!slot_live3(d, J) || d.zb != ZB) continue;
+        const int i = (J - 1) % d.g.n_subsets;
         BP3Args A{};
         A.w = d.w;
         A.w_natural = 0;
@@ -1166,15 +1170,17 @@ __global__ __launch_bounds__(NT) void k_bp3_batch(const SlotDev* __restrict__ S,
     }
 }
 
-__global__ __launch_bounds__(NT) void k_pen3_batch(const SlotDev* __restrict__ S, const Item* __restrict__ items, const int* __restrict__ count) {
+__global__ __launch_bounds__(NT) void k_pen3_batch(const SlotDev* __restrict__ S, const Item* __restrict__ items,
+                                                    const int* __restrict__ count, int step) {
     __shared__ float s_f[PEN3_HALO];
     __shared__ double s_red[NT / 64];
     const int n = *count;
     for (int it = xcd_item(blockIdx.x, gridDim.x); it < n; it += gridDim.x) {
         const Item I = items[it];
         const SlotDev& d = S[I.slot];
-        if (!slot_live3(d)) continue;
-        const int nu_mode = d.sched_nu[d.J - 1];
+        const int J = d.J + step;
+        if (!slot_live3(d, J)) continue;
+        const int nu_mode = d.sched_nu[J - 1];
         Pen3Args A{};
         A.f = d.f;
         A.G = d.G;
@@ -1194,12 +1200,14 @@ __global__ __launch_bounds__(NT) void k_pen3_batch(const SlotDev* __restrict__ S
     }
 }
 
-__global__ __launch_bounds__(NT) void k_upd3_batch(const SlotDev* __restrict__ S, const Item* __restrict__ items, const int* __restrict__ count) {
+__global__ __launch_bounds__(NT) void k_upd3_batch(const SlotDev* __restrict__ S, const Item* __restrict__ items,
+                                                    const int* __restrict__ count, int step) {
     const int n = *count;
     for (int it = xcd_item(blockIdx.x, gridDim.x); it < n; it += gridDim.x) {
         const Item I = items[it];
         const SlotDev& d = S[I.slot];
-        if (!slot_live3(d)) continue;
+        const int J = d.J + step;
+        if (!slot_live3(d, J)) continue;
         Upd3Args A{};
         A.f = d.f;
         A.fz = d.fz;
@@ -1208,8 +1216,8 @@ __global__ __launch_bounds__(NT) void k_upd3_batch(const SlotDev* __restrict__ S
         A.mu = d.mu;
         A.pnorm = d.pnorm;
         A.nu_frozen = d.nu_frozen;
-        A.nu_mode = d.sched_nu[d.J - 1];
-        A.step = d.sched_step[d.J - 1];
+        A.nu_mode = d.sched_nu[J - 1];
+        A.step = d.sched_step[J - 1];
         A.nu1 = d.nu1;
         A.nu2 = d.nu2;
         A.box = d.box;
@@ -1227,18 +1235,19 @@ __global__ __launch_bounds__(NT) void k_upd3_batch(const SlotDev* __restrict__ S
 }
 
 // the 3D part of one batched subiteration (lists WL_FP3, WL_BP3_*, WL_PEN3, WL_UPD3)
-void launch_batch3_fp(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, hipStream_t s) {
-    hipLaunchKernelGGL(k_fp3_batch, dim3(grid), dim3(NT), 0, s, d_slots, list, cnt);
+void launch_batch3_fp(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, int step, hipStream_t s) {
+    hipLaunchKernelGGL(k_fp3_batch, dim3(grid), dim3(NT), 0, s, d_slots, list, cnt, step);
 }
 
-void launch_batch3_bp(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, int zb, int nbs,
+void launch_batch3_bp(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, int step, int zb, int nbs,
                       hipStream_t s) {
-    if (zb == 16 && nbs == 20) hipLaunchKernelGGL((k_bp3_batch<16, 20>), dim3(grid), dim3(NT), 0, s, d_slots, list, cnt);
-    else if (zb == 16) hipLaunchKernelGGL((k_bp3_batch<16, 40>), dim3(grid), dim3(NT), 0, s, d_slots, list, cnt);
-    else if (zb == 32 && nbs == 20) hipLaunchKernelGGL((k_bp3_batch<32, 20>), dim3(grid), dim3(NT), 0, s, d_slots, list, cnt);
-    else if (zb == 32) hipLaunchKernelGGL((k_bp3_batch<32, 40>), dim3(grid), dim3(NT), 0, s, d_slots, list, cnt);
-    else if (nbs == 20) hipLaunchKernelGGL((k_bp3_batch<64, 20>), dim3(grid), dim3(NT), 0, s, d_slots, list, cnt);
-    else hipLaunchKernelGGL((k_bp3_batch<64, 40>), dim3(grid), dim3(NT), 0, s, d_slots, list, cnt);
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), 0, s, d_slots, list, cnt, step); };
+    if (zb == 16 && nbs == 20) go(k_bp3_batch<16, 20>);
+    else if (zb == 16) go(k_bp3_batch<16, 40>);
+    else if (zb == 32 && nbs == 20) go(k_bp3_batch<32, 20>);
+    else if (zb == 32) go(k_bp3_batch<32, 40>);
+    else if (nbs == 20) go(k_bp3_batch<64, 20>);
+    else go(k_bp3_batch<64, 40>);
 }
 
 int bp3_nbs_of(const pet_os_geom* G) {
@@ -1247,12 +1256,12 @@ int bp3_nbs_of(const pet_os_geom* G) {
     return bp3_nbs(nb);
 }
 
-void launch_batch3_pen(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, hipStream_t s) {
-    hipLaunchKernelGGL(k_pen3_batch, dim3(grid), dim3(NT), 0, s, d_slots, list, cnt);
+void launch_batch3_pen(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, int step, hipStream_t s) {
+    hipLaunchKernelGGL(k_pen3_batch, dim3(grid), dim3(NT), 0, s, d_slots, list, cnt, step);
 }
 
-void launch_batch3_upd(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, hipStream_t s) {
-    hipLaunchKernelGGL(k_upd3_batch, dim3(grid), dim3(NT), 0, s, d_slots, list, cnt);
+void launch_batch3_upd(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, int step, hipStream_t s) {
+    hipLaunchKernelGGL(k_upd3_batch, dim3(grid), dim3(NT), 0, s, d_slots, list, cnt, step);
 }
 
 }  // namespace petos

@@ -996,13 +996,14 @@ int launch_bp3q(const pet_os_geom* G, const BPLaunch& L, hipStream_t s) {
 template <int KL>
 __global__ __launch_bounds__(FQ_W * 64, 4) void k_fp3q_batch(const SlotDev* __restrict__ S,
                                                                 const Item* __restrict__ items,
-                                                                const int* __restrict__ count) {
+                                                                const int* __restrict__ count, int step) {
     const int n = *count;
     for (int it = blockIdx.x; it < n; it += gridDim.x) {
         const Item I = items[it];
         const SlotDev& d = S[I.slot];
-        if (!(d.active && d.J <= d.J_end)) continue;
-        const int i = (d.J - 1) % d.g.n_subsets;
+        const int J = d.J + step;
+        if (!(d.active && J <= d.J_end)) continue;
+        const int i = (J - 1) % d.g.n_subsets;
         FP3QArgs A{};
         A.fz = d.fz;
         A.y = d.y;
@@ -1021,15 +1022,16 @@ __global__ __launch_bounds__(FQ_W * 64, 4) void k_fp3q_batch(const SlotDev* __re
 
 template <int KL>
 __global__ __launch_bounds__(NT, 5) void k_bp3q_batch(const SlotDev* __restrict__ S, const Item* __restrict__ items,
-                                                      const int* __restrict__ count) {
+                                                      const int* __restrict__ count, int step) {
     __shared__ BP3QShared sh;
     const int n = *count;
     for (int it = blockIdx.x; it < n; it += gridDim.x) {
         const Item I = items[it];
         const SlotDev& d = S[I.slot];
         int tile;
-        if (!(d.active && d.J <= d.J_end) || !bq_tile(d.g, I.block, tile)) continue;
-        const int i = (d.J - 1) % d.g.n_subsets;
+        const int J = d.J + step;
+        if (!(d.active && J <= d.J_end) || !bq_tile(d.g, I.block, tile)) continue;
+        const int i = (J - 1) % d.g.n_subsets;
         BP3QArgs A{};
         A.wq = reinterpret_cast<const float4*>(d.w);
         A.angles = d.subset_lists + (long long)i * d.max_sub;
@@ -1042,17 +1044,18 @@ __global__ __launch_bounds__(NT, 5) void k_bp3q_batch(const SlotDev* __restrict_
     }
 }
 
-void launch_batch3q_fp(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, int kl, hipStream_t s) {
+void launch_batch3q_fp(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, int step, int kl,
+                       hipStream_t s) {
     if (kl == 64)
-        hipLaunchKernelGGL((k_fp3q_batch<64>), dim3(grid), dim3(FQ_W * 64), fq_lds(64), s, d_slots, list, cnt);
+        hipLaunchKernelGGL((k_fp3q_batch<64>), dim3(grid), dim3(FQ_W * 64), fq_lds(64), s, d_slots, list, cnt, step);
     else
-        hipLaunchKernelGGL((k_fp3q_batch<32>), dim3(grid), dim3(FQ_W * 64), fq_lds(32), s, d_slots, list, cnt);
+        hipLaunchKernelGGL((k_fp3q_batch<32>), dim3(grid), dim3(FQ_W * 64), fq_lds(32), s, d_slots, list, cnt, step);
 }
 
-void launch_batch3q_bp(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, int kl, size_t lds,
+void launch_batch3q_bp(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, int step, int kl, size_t lds,
                        hipStream_t s) {
-    if (kl == 64) hipLaunchKernelGGL((k_bp3q_batch<64>), dim3(grid), dim3(NT), lds, s, d_slots, list, cnt);
-    else hipLaunchKernelGGL((k_bp3q_batch<32>), dim3(grid), dim3(NT), lds, s, d_slots, list, cnt);
+    if (kl == 64) hipLaunchKernelGGL((k_bp3q_batch<64>), dim3(grid), dim3(NT), lds, s, d_slots, list, cnt, step);
+    else hipLaunchKernelGGL((k_bp3q_batch<32>), dim3(grid), dim3(NT), lds, s, d_slots, list, cnt, step);
 }
 
 }  // namespace petos

@@ -5,8 +5,8 @@
 // own batch, stream and worker thread.  A lane admits the queued requests of
 // its class in arrival order as soon as a slot and the device-memory budget
 // allow; admitted requests join the lane's running batch between two steps,
-// and every step advances all of them by one subiteration (one replay of the
-// captured batched launch sequence).  A request that finishes leaves at once
+// and every step advances all of them by one subiteration (one batched
+// launch sequence).  A request that finishes leaves at once
 // and frees its memory, so later arrivals are admitted while others still
 // run.  The lanes run concurrently on the device, so a slow 3D subiteration
 // does not pace the 2D requests.  Geometries (tables, sensitivity,
@@ -232,10 +232,8 @@ struct pet_os_server {
     uint64_t use_clock = 0;
     uint64_t gen = 0;              // bumped on every submit, cancel and departure
     int admitting = 0;             // admissions in progress (slots reserved)
-    // Device API calls of the lanes (geometry creation, joining, the step that
-    // may capture a graph, objective, leaving) are serialized: a graph capture
-    // in one lane must not overlap default-stream work issued by the other
-    // (the runtime then invalidates the capture).  Waiting on a lane's own
+    // Device API calls of the lanes (geometry creation, joining, the queuing of
+    // a step, objective, leaving) are serialized.  Waiting on a lane's own
     // stream is not serialized.  Taken after mu when both are held.
     std::mutex api_mu;
     bool stop = false;
