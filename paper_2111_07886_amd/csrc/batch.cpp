@@ -41,6 +41,7 @@ struct BatchSlot {
     Work w;
     float* d_step = nullptr;
     int* d_nu = nullptr;
+    bool owned = true;               // w, d_step and d_nu are this slot's (else parts of the batch's slab)
     int fp_seg = 1, bp_kind = 0;
     size_t bytes = 0;
 };
@@ -52,10 +53,12 @@ struct pet_os_batch {
     std::vector<BatchSlot> slots;
     std::vector<SlotDev> h_slots;
     SlotDev* d_slots = nullptr;
+    // the work lists' counts and, behind them, the lists, in one allocation
+    char* d_lists = nullptr;
+    size_t lists_cap = 0;
     Item* d_items[WL_COUNT] = {};
-    int cap[WL_COUNT] = {};
-    int count[WL_COUNT] = {};
     int* d_counts = nullptr;
+    void* slab = nullptr;            // requests that came in one call: their scratch and schedules
     int grids[WL_COUNT] = {};
     size_t bp3q_lds = 0;             // dynamic LDS of the quad back-projection: the largest of the slots'
     bool lists_dirty = true;
@@ -67,9 +70,11 @@ namespace {
 constexpr int GRID_CAP = 8192;
 
 void slot_release(BatchSlot& s) {
-    work_free(&s.w);
-    if (s.d_step) (void)hipFree(s.d_step);
-    if (s.d_nu) (void)hipFree(s.d_nu);
+    if (s.owned) {
+        work_free(&s.w);
+        if (s.d_step) (void)hipFree(s.d_step);
+        if (s.d_nu) (void)hipFree(s.d_nu);
+    }
     s = BatchSlot{};
 }
 
@@ -86,13 +91,13 @@ int upload_slot_field(pet_os_batch* B, int idx, size_t offset, const T& v) {
     return PET_OS_OK;
 }
 
-int rebuild_lists(pet_os_batch* B) {
-    // The forward projector's threads per ray: a ray's sum does not depend
-    // on it (fp_body), so the batch takes the shape its total number of 2D
-    // rays calls for, not each request's single-request shape: about 2^22
-    // threads in all.  Fewer threads per ray repeat less set-up, more keep
-    // more loads in flight; measured on 96 uneven requests (~3.2e5 rays),
-    // 1 / 4 / 16 / 64 threads per ray gave 607 / 765 / 800 / 754 recons/s.
+// The forward projector's threads per ray: a ray's sum does not depend
+// on it (fp_body), so the batch takes the shape its total number of 2D
+// rays calls for, not each request's single-request shape: about 2^22
+// threads in all.  Fewer threads per ray repeat less set-up, more keep
+// more loads in flight; measured on 96 uneven requests (~3.2e5 rays),
+// 1 / 4 / 16 / 64 threads per ray gave 607 / 765 / 800 / 754 recons/s.
+int choose_segments(pet_os_batch* B, bool upload) {
     long long rays2d = 0;
     bool any2d = false;
     for (const BatchSlot& S : B->slots)
@@ -100,20 +105,26 @@ int rebuild_lists(pet_os_batch* B) {
             rays2d += (long long)S.g->max_sub_angles * S.g->n_planes * S.g->d.n_radial;
             any2d = true;
         }
-    if (any2d) {
-        const int seg = rays2d >= (1LL << 22) ? 1 : rays2d >= (1LL << 20) ? 4 : rays2d >= (1LL << 18) ? 16 : 64;
-        for (int s = 0; s < B->max_slots; ++s) {
-            BatchSlot& S = B->slots[s];
-            if (!S.used || S.g->d.dim != 2 || S.fp_seg == seg) continue;
-            S.fp_seg = seg;
-            SlotDev& D = B->h_slots[s];
-            D.fp_seg = seg;
-            D.n_fp = fp_grid_seg(S.g, S.g->max_sub_angles, seg);
-            int rc = upload_slot_field(B, s, offsetof(SlotDev, fp_seg), D.fp_seg);
-            if (!rc) rc = upload_slot_field(B, s, offsetof(SlotDev, n_fp), D.n_fp);
-            if (rc) return rc;
-        }
+    if (!any2d) return PET_OS_OK;
+    const int seg = rays2d >= (1LL << 22) ? 1 : rays2d >= (1LL << 20) ? 4 : rays2d >= (1LL << 18) ? 16 : 64;
+    for (int s = 0; s < B->max_slots; ++s) {
+        BatchSlot& S = B->slots[s];
+        if (!S.used || S.g->d.dim != 2 || S.fp_seg == seg) continue;
+        S.fp_seg = seg;
+        SlotDev& D = B->h_slots[s];
+        D.fp_seg = seg;
+        D.n_fp = fp_grid_seg(S.g, S.g->max_sub_angles, seg);
+        if (!upload) continue;
+        int rc = upload_slot_field(B, s, offsetof(SlotDev, fp_seg), D.fp_seg);
+        if (!rc) rc = upload_slot_field(B, s, offsetof(SlotDev, n_fp), D.n_fp);
+        if (rc) return rc;
     }
+    return PET_OS_OK;
+}
+
+int rebuild_lists(pet_os_batch* B) {
+    int rc = choose_segments(B, true);
+    if (rc) return rc;
     std::vector<Item> L[WL_COUNT];
     B->bp3q_lds = 0;
     for (int s = 0; s < B->max_slots; ++s) {
@@ -142,23 +153,161 @@ int rebuild_lists(pet_os_batch* B) {
             for (int b = 0; b < nup; ++b) L[WL_UPD3].push_back({s, b});
         }
     }
+    size_t at[WL_COUNT], bytes = 256;       // (the counts first)
+    static_assert(WL_COUNT * sizeof(int) <= 256, "the counts fit their place");
+    for (int k = 0; k < WL_COUNT; ++k) {
+        at[k] = bytes;
+        bytes += (L[k].size() * sizeof(Item) + 255) & ~(size_t)255;
+    }
+    if (bytes > B->lists_cap) {
+        if (B->d_lists) (void)hipFree(B->d_lists);
+        B->d_lists = nullptr;
+        const size_t cap = std::max(bytes, 2 * B->lists_cap);
+        B->lists_cap = 0;
+        if (hipMalloc(&B->d_lists, cap) != hipSuccess)
+            return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of the work lists failed");
+        B->lists_cap = cap;
+    }
+    std::vector<char> h(bytes, 0);
     for (int k = 0; k < WL_COUNT; ++k) {
         const int n = (int)L[k].size();
-        if (n > B->cap[k]) {
-            if (B->d_items[k]) (void)hipFree(B->d_items[k]);
-            B->d_items[k] = nullptr;
-            int c = std::max(n, 2 * B->cap[k]);
-            if (hipMalloc(&B->d_items[k], (size_t)std::max(c, 1) * sizeof(Item)) != hipSuccess)
-                return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of work list failed");
-            B->cap[k] = c;
-        }
-        if (n) PETOS_HIP(hipMemcpy(B->d_items[k], L[k].data(), (size_t)n * sizeof(Item), hipMemcpyHostToDevice));
-        B->count[k] = n;
+        reinterpret_cast<int*>(h.data())[k] = n;
+        if (n) std::memcpy(h.data() + at[k], L[k].data(), (size_t)n * sizeof(Item));
+        B->d_items[k] = reinterpret_cast<Item*>(B->d_lists + at[k]);
         // multiples of 8: the kernels deal contiguous item runs to each XCD
         B->grids[k] = 8 * ((std::min(n, GRID_CAP) + 7) / 8);
     }
-    PETOS_HIP(hipMemcpy(B->d_counts, B->count, sizeof(B->count), hipMemcpyHostToDevice));
+    B->d_counts = reinterpret_cast<int*>(B->d_lists);
+    PETOS_HIP(hipMemcpy(B->d_lists, h.data(), bytes, hipMemcpyHostToDevice));
     B->lists_dirty = false;
+    return PET_OS_OK;
+}
+
+int batchable(const pet_os_params* p, const pet_os_geom* g) {
+    if (p->mode == PET_OS_OSEM) return fail(PET_OS_ERR_INVALID_ARG, "OSEM runs on states only, not in a batch");
+    if (g->full_model)
+        return fail(PET_OS_ERR_INVALID_ARG, "sub-rays, PSF and attenuation run on states only, not in a batch");
+    return PET_OS_OK;
+}
+
+// the device record of a slot whose scratch and schedule are placed
+int slot_record(BatchSlot& S, const GeomExtra* ex, SlotDev& D) {
+    const pet_os_geom* g = S.g;
+    const pet_os_params* p = &S.p;
+    const long long nrays_sub = (long long)g->max_sub_angles * g->n_planes * g->d.n_radial;
+    S.fp_seg = fp_seg_for(g, nrays_sub, g->tuned_seg);
+    S.bp_kind = bp_kind_of(g);
+    D = SlotDev{};
+    D.g = g->k;
+    D.pnorm = g->pnorm;
+    D.f = S.f;
+    D.y = S.y;
+    D.r = S.r;
+    D.w = S.w.w;
+    D.G = S.w.G;
+    D.mu = S.w.mu;
+    D.nu_frozen = S.w.nu_frozen;
+    D.fz = S.w.fz;
+    D.fsnap = S.w.fsnap;
+    D.n_fp = g->d.dim == 3 ? 0 : fp_grid_seg(g, g->max_sub_angles, S.fp_seg);
+    D.part_f = S.w.red[RED_SUMF].part;
+    D.part_mu = S.w.red[RED_SUMMU].part;
+    D.n_part_f = sumf_grid(g);
+    D.n_part_mu = g->d.dim == 3 ? pen3_grid(g) : px_grid(g);
+    D.subset_lists = ex->subset_lists;
+    D.subset_count = ex->d_subset_count;
+    D.max_sub = g->max_sub_angles;
+    D.sched_step = S.d_step;
+    D.sched_nu = S.d_nu;
+    D.J = 1;
+    D.J_end = (int)S.J_end;
+    D.beta_over_M = (float)(p->beta / (double)g->d.n_subsets);
+    D.gamma_R = (float)p->gamma_R;
+    D.eps = (float)p->eps;
+    D.nu1 = (float)p->nu1;
+    D.nu2 = (float)p->nu2;
+    D.box = make_box(p->U, p->t_clip);
+    D.fp_seg = S.fp_seg;
+    D.bp_kind = S.bp_kind;
+    if (g->d.dim == 3 && quad_ok(g)) {
+        D.quad = 1;
+        D.rows_max = bp3q_rows(g);
+        D.chunk = bp3q_buf(g);
+    } else if (g->d.dim == 3) {
+        int rc = bp3_shape(g, D.nb_max, D.zb, D.rows_max, D.chunk);
+        if (rc) return rc;
+    } else {
+        size_t lds;
+        bp_stage_shape_kind(g, S.bp_kind, D.nb_max, D.rows_max, D.chunk, lds);
+    }
+    D.active = 1;
+    return PET_OS_OK;
+}
+
+// Admit the n requests of one call to the empty batch B: one allocation, one
+// wait for all data checks, one upload each of the schedules and the records.
+// (One by one, each request's allocations, checks and small copies took about
+// 120 us of the call.)  The error is that of the first request that has one.
+int add_together(pet_os_batch* B, int n, const pet_os_geom* const* geoms, const pet_os_params* params,
+                 float* const* f, const float* const* y, const float* const* r, const int32_t* n_iter, hipStream_t st) {
+    auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    // requests up to the first that does not go into a batch
+    int m = 0;
+    while (m < n && batchable(&params[m], geoms[m]) == PET_OS_OK) ++m;
+    if (m == 0) return batchable(&params[0], geoms[0]);
+    // the slab: the checks' totals, the schedules, each request's scratch
+    size_t subs = 0, bytes = up((size_t)m * 4 * sizeof(unsigned long long));
+    for (int k = 0; k < m; ++k) subs += (size_t)n_iter[k] * geoms[k]->d.n_subsets;
+    const size_t o_sched = bytes;
+    bytes += up(subs * (sizeof(float) + sizeof(int)));
+    std::vector<size_t> o_work(m);
+    auto need_nu = [&](int k) { return params[k].mode == PET_OS_P1 || params[k].mode == PET_OS_P2; };
+    for (int k = 0; k < m; ++k) {
+        o_work[k] = bytes;
+        bytes += up(work_bytes(geoms[k], need_nu(k)));
+    }
+    if (hipMalloc(&B->slab, bytes) != hipSuccess) return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of scratch failed");
+    char* base = (char*)B->slab;
+    auto* totals = (unsigned long long*)base;
+    std::vector<char> sched(subs * (sizeof(float) + sizeof(int)));
+    size_t at = 0;
+    std::vector<float> step;
+    std::vector<int> nu;
+    int rc = PET_OS_OK;
+    for (int k = 0; k < m && !rc; ++k) {
+        BatchSlot& S = B->slots[k];
+        S.owned = false;
+        S.g = geoms[k];
+        S.p = params[k];
+        S.f = f[k];
+        S.y = y[k];
+        S.r = r[k];
+        S.J_end = (int64_t)n_iter[k] * S.g->d.n_subsets;
+        work_carve_at(S.g, need_nu(k), base + o_work[k], &S.w);
+        rc = check_launch(S.g, &S.p, S.w.check_part, totals + 4 * (size_t)k, S.f, S.y, S.r, st);
+        if (!rc) rc = launch_sum_f(S.g, S.f, S.w.fz, S.w.red[RED_SUMF], st);
+        schedule_table(S.p, S.g->d.n_subsets, S.J_end, step, nu);
+        S.d_step = (float*)(base + o_sched + at);
+        std::memcpy(sched.data() + at, step.data(), step.size() * sizeof(float));
+        at += step.size() * sizeof(float);
+        S.d_nu = (int*)(base + o_sched + at);
+        std::memcpy(sched.data() + at, nu.data(), nu.size() * sizeof(int));
+        at += nu.size() * sizeof(int);
+        S.bytes = S.w.bytes + step.size() * (sizeof(float) + sizeof(int));
+        if (!rc) rc = slot_record(S, extra_of(S.g), B->h_slots[k]);
+        S.used = true;
+        B->bytes += S.bytes;
+    }
+    std::vector<unsigned long long> c((size_t)m * 4);
+    if (!rc && (hipMemcpyAsync(base + o_sched, sched.data(), sched.size(), hipMemcpyHostToDevice, st) != hipSuccess ||
+                hipMemcpyAsync(c.data(), totals, c.size() * sizeof(c[0]), hipMemcpyDeviceToHost, st) != hipSuccess))
+        rc = fail(PET_OS_ERR_DEVICE, "schedule upload failed");
+    if (hipStreamSynchronize(st) != hipSuccess && !rc) rc = fail(PET_OS_ERR_DEVICE, "synchronize failed");
+    for (int k = 0; k < m && !rc; ++k) rc = check_verdict(&params[k], &c[4 * (size_t)k]);
+    if (!rc && m < n) rc = batchable(&params[m], geoms[m]);
+    if (rc) return rc;
+    if ((rc = choose_segments(B, false))) return rc;
+    PETOS_HIP(hipMemcpy(B->d_slots, B->h_slots.data(), sizeof(SlotDev) * (size_t)n, hipMemcpyHostToDevice));
     return PET_OS_OK;
 }
 
@@ -174,17 +323,13 @@ int pet_os_batch_create(int32_t max_slots, pet_os_batch** out) {
     B->max_slots = max_slots;
     B->slots.resize(max_slots);
     B->h_slots.assign(max_slots, SlotDev{});
-    if (hipMalloc(&B->d_slots, sizeof(SlotDev) * (size_t)max_slots) != hipSuccess ||
-        hipMalloc(&B->d_counts, sizeof(int) * WL_COUNT) != hipSuccess) {
-        if (B->d_slots) (void)hipFree(B->d_slots);
+    if (hipMalloc(&B->d_slots, sizeof(SlotDev) * (size_t)max_slots) != hipSuccess) {
         delete B;
         return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of the slot table failed");
     }
     if (hipMemcpy(B->d_slots, B->h_slots.data(), sizeof(SlotDev) * (size_t)max_slots, hipMemcpyHostToDevice) !=
-            hipSuccess ||
-        hipMemset(B->d_counts, 0, sizeof(int) * WL_COUNT) != hipSuccess) {
+        hipSuccess) {
         (void)hipFree(B->d_slots);
-        (void)hipFree(B->d_counts);
         delete B;
         return fail(PET_OS_ERR_DEVICE, "batch initialisation failed");
     }
@@ -197,10 +342,9 @@ int pet_os_batch_destroy(pet_os_batch* B) {
     (void)hipDeviceSynchronize();
     for (auto& s : B->slots)
         if (s.used) slot_release(s);
-    for (int k = 0; k < WL_COUNT; ++k)
-        if (B->d_items[k]) (void)hipFree(B->d_items[k]);
+    if (B->d_lists) (void)hipFree(B->d_lists);
+    if (B->slab) (void)hipFree(B->slab);
     (void)hipFree(B->d_slots);
-    (void)hipFree(B->d_counts);
     delete B;
     return PET_OS_OK;
 }
@@ -212,10 +356,8 @@ int pet_os_batch_add(pet_os_batch* B, const pet_os_geom* g, const pet_os_params*
     GeomExtra* ex = extra_of(g);
     if (!ex) return fail(PET_OS_ERR_INVALID_ARG, "invalid geometry");
     int rc = validate_params(p, g);
+    if (!rc) rc = batchable(p, g);
     if (rc) return rc;
-    if (p->mode == PET_OS_OSEM) return fail(PET_OS_ERR_INVALID_ARG, "OSEM runs on states only, not in a batch");
-    if (g->full_model)
-        return fail(PET_OS_ERR_INVALID_ARG, "sub-rays, PSF and attenuation run on states only, not in a batch");
     int idx = -1;
     for (int s = 0; s < B->max_slots; ++s)
         if (!B->slots[s].used) { idx = s; break; }
@@ -253,58 +395,13 @@ int pet_os_batch_add(pet_os_batch* B, const pet_os_geom* g, const pet_os_params*
         return fail(PET_OS_ERR_DEVICE, "schedule upload failed");
     }
     S.bytes = S.w.bytes + step.size() * (sizeof(float) + sizeof(int));
-    const long long nrays_sub = (long long)g->max_sub_angles * g->n_planes * g->d.n_radial;
-    S.fp_seg = fp_seg_for(g, nrays_sub, g->tuned_seg);
-    S.bp_kind = bp_kind_of(g);
     // sum of f0 for mean f of the first adaptive subiteration (3D: and the
     // z-fastest copy of f0 read by the forward projector)
     rc = launch_sum_f(g, f, S.w.fz, S.w.red[RED_SUMF], st);
     if (rc) { slot_release(S); return rc; }
 
-    SlotDev D{};
-    D.g = g->k;
-    D.pnorm = g->pnorm;
-    D.f = f;
-    D.y = y;
-    D.r = r;
-    D.w = S.w.w;
-    D.G = S.w.G;
-    D.mu = S.w.mu;
-    D.nu_frozen = S.w.nu_frozen;
-    D.fz = S.w.fz;
-    D.fsnap = S.w.fsnap;
-    D.n_fp = g->d.dim == 3 ? 0 : fp_grid_seg(g, g->max_sub_angles, S.fp_seg);
-    D.part_f = S.w.red[RED_SUMF].part;
-    D.part_mu = S.w.red[RED_SUMMU].part;
-    D.n_part_f = sumf_grid(g);
-    D.n_part_mu = g->d.dim == 3 ? pen3_grid(g) : px_grid(g);
-    D.subset_lists = ex->subset_lists;
-    D.subset_count = ex->d_subset_count;
-    D.max_sub = g->max_sub_angles;
-    D.sched_step = S.d_step;
-    D.sched_nu = S.d_nu;
-    D.J = 1;
-    D.J_end = (int)S.J_end;
-    D.beta_over_M = (float)(p->beta / (double)M);
-    D.gamma_R = (float)p->gamma_R;
-    D.eps = (float)p->eps;
-    D.nu1 = (float)p->nu1;
-    D.nu2 = (float)p->nu2;
-    D.box = make_box(p->U, p->t_clip);
-    D.fp_seg = S.fp_seg;
-    D.bp_kind = S.bp_kind;
-    if (g->d.dim == 3 && quad_ok(g)) {
-        D.quad = 1;
-        D.rows_max = bp3q_rows(g);
-        D.chunk = bp3q_buf(g);
-    } else if (g->d.dim == 3) {
-        rc = bp3_shape(g, D.nb_max, D.zb, D.rows_max, D.chunk);
-        if (rc) { slot_release(S); return rc; }
-    } else {
-        size_t lds;
-        bp_stage_shape_kind(g, S.bp_kind, D.nb_max, D.rows_max, D.chunk, lds);
-    }
-    D.active = 1;
+    SlotDev D;
+    if ((rc = slot_record(S, ex, D))) { slot_release(S); return rc; }
     S.used = true;
     B->slots[idx] = S;
     B->h_slots[idx] = D;
@@ -388,7 +485,7 @@ int pet_os_reconstruct_batch(int32_t n, const pet_os_geom* const* geoms, const p
     }
     pet_os_batch* B = nullptr;
     int rc = pet_os_batch_create(n, &B);
-    for (int k = 0; k < n && !rc; ++k) rc = pet_os_batch_add(B, geoms[k], &params[k], f[k], y[k], r[k], n_iter[k], stream, nullptr);
+    if (!rc) rc = add_together(B, n, geoms, params, f, y, r, n_iter, (hipStream_t)stream);
     if (!rc) rc = pet_os_batch_run(B, stream);
     if (!rc && hipStreamSynchronize((hipStream_t)stream) != hipSuccess) rc = fail(PET_OS_ERR_DEVICE, "synchronize failed");
     if (B) pet_os_batch_destroy(B);

@@ -429,6 +429,7 @@ int pet_os_destroy_geometry(pet_os_geom* geom) {
         g_geo_extra.erase(geom);
     }
     if (geom->dev_block) (void)hipFree(geom->dev_block);
+    scratch_drop(geom);
     delete geom;
     return PET_OS_OK;
 }
@@ -520,10 +521,79 @@ static void work_carve(const WorkLayout& L, char* blk, Work* w) {
 
 size_t work_bytes(const pet_os_geom* g, bool need_nu) { return work_layout(g, need_nu, false).bytes; }
 
-int work_alloc(const pet_os_geom* g, bool need_nu, Work* w, bool sums) {
+void work_carve_at(const pet_os_geom* g, bool need_nu, void* base, Work* w) {
+    work_carve(work_layout(g, need_nu, false), (char*)base, w);
+}
+
+// An allocation and its release cost a short call more than its kernels do
+// (they also wait for the whole device): a 128x128x32 forward projection took
+// 97 us with them for 39 us of kernels.
+void* scratch_take(const pet_os_geom* g, size_t bytes, size_t* got) {
+    int dev = -1;
+    if (hipGetDevice(&dev) == hipSuccess && dev == g->device) {
+        std::lock_guard<std::mutex> lk(g->kept_mu);
+        auto best = g->kept.end();
+        for (auto it = g->kept.begin(); it != g->kept.end(); ++it)
+            if (it->bytes >= bytes && (best == g->kept.end() || it->bytes < best->bytes)) best = it;
+        if (best != g->kept.end()) {
+            void* p = best->p;
+            *got = best->bytes;
+            g->kept.erase(best);
+            return p;
+        }
+    }
+    void* p = nullptr;
+    *got = bytes;
+    if (hipMalloc(&p, bytes) == hipSuccess) return p;
+    (void)hipGetLastError();
+    scratch_drop(g);        // what the geometry keeps may be what is missing
+    return hipMalloc(&p, bytes) == hipSuccess ? p : nullptr;
+}
+
+void scratch_drop(const pet_os_geom* g) {
+    std::vector<pet_os_geom::Kept> old;
+    {
+        std::lock_guard<std::mutex> lk(g->kept_mu);
+        old.swap(g->kept);
+    }
+    for (auto& k : old) (void)hipFree(k.p);
+}
+
+void scratch_give(const pet_os_geom* g, void* p, size_t bytes) {
+    int dev = -1;
+    if (hipGetDevice(&dev) == hipSuccess && dev == g->device && bytes <= KEPT_MAX) {
+        std::lock_guard<std::mutex> lk(g->kept_mu);
+        // a larger block takes the place of the smallest
+        size_t total = bytes, least = 0;
+        for (size_t i = 0; i < g->kept.size(); ++i) {
+            total += g->kept[i].bytes;
+            if (g->kept[i].bytes < g->kept[least].bytes) least = i;
+        }
+        if (g->kept.size() < 2 && total <= KEPT_MAX) {
+            g->kept.push_back({p, bytes});
+            return;
+        }
+        if (!g->kept.empty() && g->kept[least].bytes < bytes && total - g->kept[least].bytes <= KEPT_MAX) {
+            std::swap(g->kept[least].p, p);
+            g->kept[least].bytes = bytes;
+        }
+    }
+    (void)hipFree(p);
+}
+
+int work_alloc(const pet_os_geom* g, bool need_nu, Work* w, bool sums, bool keep) {
     *w = Work{};
     const WorkLayout L = work_layout(g, need_nu, sums);
     char* blk = nullptr;
+    if (keep) {
+        size_t got = 0;
+        blk = (char*)scratch_take(g, L.bytes, &got);
+        if (!blk) return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of scratch failed");
+        work_carve(L, blk, w);
+        w->bytes = got;
+        w->keeper = g;
+        return PET_OS_OK;
+    }
     if (hipMalloc(&blk, L.bytes) != hipSuccess) return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of scratch failed");
     work_carve(L, blk, w);
     if (hipMemset(blk + L.o_tot, 0, RED_COUNT * sizeof(double)) != hipSuccess) {
@@ -551,7 +621,8 @@ int work_place(const pet_os_geom* g, bool need_nu, void* base, size_t cap, size_
 }
 
 void work_free(Work* w) {
-    if (w->red_block) (void)hipFree(w->red_block);
+    if (w->keeper) scratch_give(w->keeper, w->red_block, w->bytes);
+    else if (w->red_block) (void)hipFree(w->red_block);
     *w = Work{};
 }
 
@@ -615,18 +686,27 @@ BoxK make_box(double U, double t) {
 // B = [0, U]^q (OSEM: f >= 0), every entry finite; with the adaptive nu of
 // eq:nuki from the first subiteration (P1/P2, J0 = 0) the mean of f must be
 // > 0 (it divides the gradient magnitude in mu).
-int check_data(const pet_os_geom* g, const pet_os_params* p, Work* w, const float* f, const float* y,
-               const float* r, hipStream_t s) {
+int check_launch(const pet_os_geom* g, const pet_os_params* p, unsigned* part, unsigned long long* total,
+                 const float* f, const float* y, const float* r, hipStream_t s) {
     float f_lim = std::numeric_limits<float>::infinity();
     if (p->mode != PET_OS_OSEM) {
         f_lim = (float)p->U;
         if ((double)f_lim <= p->U) f_lim = std::nextafter(f_lim, std::numeric_limits<float>::infinity());
     }
-    int rc = launch_check_data(y, r, g->n_bins, f, g->n_vox, f_lim, w->check_part, w->check_total, s);
+    return launch_check_data(y, r, g->n_bins, f, g->n_vox, f_lim, part, total, s);
+}
+
+int check_data(const pet_os_geom* g, const pet_os_params* p, Work* w, const float* f, const float* y,
+               const float* r, hipStream_t s) {
+    int rc = check_launch(g, p, w->check_part, w->check_total, f, y, r, s);
     if (rc) return rc;
     unsigned long long c[4] = {0, 0, 0, 0};
     PETOS_HIP(hipMemcpyAsync(c, w->check_total, sizeof(c), hipMemcpyDeviceToHost, s));
     PETOS_HIP(hipStreamSynchronize(s));
+    return check_verdict(p, c);
+}
+
+int check_verdict(const pet_os_params* p, const unsigned long long* c) {
     if (c[0]) return fail(PET_OS_ERR_INVALID_ARG, "y: " + std::to_string(c[0]) + " entries negative or not finite");
     if (c[1])
         return fail(PET_OS_ERR_INVALID_ARG, "r: " + std::to_string(c[1]) + " entries not > 0 or not finite");
@@ -735,10 +815,15 @@ static int ensure_yr(pet_os_state* st, const float* y, const float* r, hipStream
     if (st->yr != nullptr && st->yr_y == y && st->yr_r == r) return PET_OS_OK;
     if (st->yr == nullptr) {
         void* p = nullptr;
-        if (hipMalloc(&p, (size_t)g->n_bins * sizeof(float2)) != hipSuccess) {
-            (void)hipGetLastError();    // the natural layout serves
-            return PET_OS_OK;
+        st->yr_bytes = (size_t)g->n_bins * sizeof(float2);
+        if (st->w.keeper) {
+            p = scratch_take(g, st->yr_bytes, &st->yr_bytes);
+            if (!p) (void)hipGetLastError();
+        } else if (hipMalloc(&p, st->yr_bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            p = nullptr;
         }
+        if (!p) return PET_OS_OK;       // the natural layout serves
         st->yr = (float2*)p;
     }
     st->yr_y = st->yr_r = nullptr;
@@ -893,7 +978,7 @@ static int queue_objective(const pet_os_geom* g, const pet_os_params* p, Work* w
 
 extern "C" {
 
-int pet_os_state_create(const pet_os_geom* g, const pet_os_params* p, pet_os_state** out) {
+static int state_create(const pet_os_geom* g, const pet_os_params* p, bool keep, pet_os_state** out) {
     if (!out) return fail(PET_OS_ERR_INVALID_ARG, "out is NULL");
     *out = nullptr;
     if (!g || !extra_of(g)) return fail(PET_OS_ERR_INVALID_ARG, "invalid geometry");
@@ -907,7 +992,7 @@ int pet_os_state_create(const pet_os_geom* g, const pet_os_params* p, pet_os_sta
     st->t_nest = 1.0;
     st->have_frozen = 0;
     const bool need_nu = p->mode == PET_OS_P1 || p->mode == PET_OS_P2;
-    rc = work_alloc(g, need_nu, &st->w);
+    rc = work_alloc(g, need_nu, &st->w, false, keep);
     if (rc) { delete st; return rc; }
     if (p->mode == PET_OS_OSEM) {
         // the M subset sensitivities A_i^T 1 of the EM update
@@ -942,12 +1027,17 @@ int pet_os_state_create(const pet_os_geom* g, const pet_os_params* p, pet_os_sta
     return PET_OS_OK;
 }
 
+int pet_os_state_create(const pet_os_geom* g, const pet_os_params* p, pet_os_state** out) {
+    return state_create(g, p, false, out);
+}
+
 int pet_os_state_destroy(pet_os_state* st) {
     if (!st) return fail(PET_OS_ERR_INVALID_ARG, "state is NULL");
+    if (st->yr && st->w.keeper) scratch_give(st->w.keeper, st->yr, st->yr_bytes);
+    else if (st->yr) (void)hipFree(st->yr);
     work_free(&st->w);
     if (st->osem_sens) (void)hipFree(st->osem_sens);
     if (st->obj_dev) (void)hipFree(st->obj_dev);
-    if (st->yr) (void)hipFree(st->yr);
     for (auto& pr : st->prof_ev) {
         (void)hipEventDestroy(pr.first);
         (void)hipEventDestroy(pr.second);
@@ -992,24 +1082,24 @@ int pet_os_forward(const pet_os_geom* g, const float* f, int32_t subset, float* 
     F.angles = subset == 0 ? ex->all_angles : ex->subset_lists + (size_t)(subset - 1) * g->max_sub_angles;
     F.n_al = subset == 0 ? g->d.n_angles : ex->subset_count[subset - 1];
     if (g->d.dim == 2 && g->k.psf_kx > 0) {
-        // the PSF-blurred image, in scratch released before returning
+        // the PSF-blurred image, in scratch given back before returning
         hipStream_t s = (hipStream_t)stream;
-        float* tmp = nullptr;
-        if (hipMalloc(&tmp, sizeof(float) * (size_t)g->n_vox) != hipSuccess)
-            return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc failed");
+        size_t got = 0;
+        float* tmp = (float*)scratch_take(g, sizeof(float) * (size_t)g->n_vox, &got);
+        if (!tmp) return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc failed");
         int rc = launch_blur(g, f, tmp, s);
         F.f = tmp;
         if (!rc) rc = launch_fp(g, F, s);
         if (hipStreamSynchronize(s) != hipSuccess && !rc) rc = fail(PET_OS_ERR_DEVICE, "stream synchronize failed");
-        (void)hipFree(tmp);
+        scratch_give(g, tmp, got);
         return rc;
     }
     if (g->d.dim == 2) return launch_fp(g, F, (hipStream_t)stream);
     // 3D: the projector reads a z-fastest copy of f, made in scratch that is
-    // released before returning (this call waits for the stream)
+    // given back before returning (this call waits for the stream)
     hipStream_t s = (hipStream_t)stream;
     Work w;
-    int rc = work_alloc(g, false, &w);
+    int rc = work_alloc(g, false, &w, false, true);
     if (rc) return rc;
     rc = launch_prep3(g, f, w.fz, w.red[RED_SUMF], s);
     F.fz = w.fz;
@@ -1031,14 +1121,14 @@ int pet_os_back(const pet_os_geom* g, const float* w, int32_t subset, float* out
     if (g->d.dim == 2 && g->k.psf_kx > 0) {
         // back-projection into scratch, then the (symmetric) PSF into out
         hipStream_t s = (hipStream_t)stream;
-        float* tmp = nullptr;
-        if (hipMalloc(&tmp, sizeof(float) * (size_t)g->n_vox) != hipSuccess)
-            return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc failed");
+        size_t got = 0;
+        float* tmp = (float*)scratch_take(g, sizeof(float) * (size_t)g->n_vox, &got);
+        if (!tmp) return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc failed");
         B.out = tmp;
         int rc = launch_bp(g, B, s);
         if (!rc) rc = launch_blur(g, tmp, out, s);
         if (hipStreamSynchronize(s) != hipSuccess && !rc) rc = fail(PET_OS_ERR_DEVICE, "stream synchronize failed");
-        (void)hipFree(tmp);
+        scratch_give(g, tmp, got);
         return rc;
     }
     return launch_bp(g, B, (hipStream_t)stream);
@@ -1064,22 +1154,15 @@ int pet_os_objective(const pet_os_geom* g, const pet_os_params* p, const float* 
     if (!g || !p || !f || !y || !r || !phi) return fail(PET_OS_ERR_INVALID_ARG, "NULL argument");
     if (!extra_of(g)) return fail(PET_OS_ERR_INVALID_ARG, "invalid geometry");
     Work w;
-    int rc = work_alloc(g, false, &w);
+    int rc = work_alloc(g, false, &w, false, true);
     if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
-    double* dst = nullptr;
-    if (hipMalloc(&dst, 2 * sizeof(double)) != hipSuccess) {
-        work_free(&w);
-        return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc failed");
-    }
+    double* dst = (double*)w.check_total;      // (two of its four words; no data check here)
     rc = queue_objective(g, p, &w, f, y, r, dst, s);
     double h[2] = {0, 0};
-    if (!rc) {
-        if (hipMemcpyAsync(h, dst, sizeof(h), hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess)
-            rc = fail(PET_OS_ERR_DEVICE, "objective read-back failed");
-    }
-    (void)hipFree(dst);
+    if (!rc && hipMemcpyAsync(h, dst, sizeof(h), hipMemcpyDeviceToHost, s) != hipSuccess)
+        rc = fail(PET_OS_ERR_DEVICE, "objective read-back failed");
+    if (hipStreamSynchronize(s) != hipSuccess && !rc) rc = fail(PET_OS_ERR_DEVICE, "objective read-back failed");
     work_free(&w);
     if (rc) return rc;
     *phi = h[0] + p->beta * h[1];
@@ -1129,15 +1212,17 @@ int pet_os_subset_gradient(const pet_os_geom* g, const pet_os_params* p, const f
     const int* angles = subset == 0 ? ex->all_angles : ex->subset_lists + (size_t)(subset - 1) * g->max_sub_angles;
     const int n_al = subset == 0 ? g->d.n_angles : ex->subset_count[subset - 1];
     Work w;
-    int rc = work_alloc(g, false, &w);
+    int rc = work_alloc(g, false, &w, false, true);
     if (rc) return rc;
     // the ratio sinogram of every ray does not fit the subset-sized scratch
     float* wsino = w.w;
     float* big = nullptr;
+    size_t big_bytes = 0;
     if (n_al > g->max_sub_angles) {
         // + 4 floats of padding for the 3D back-projector's 16-byte staging loads
         const size_t n = quad_ok(g) ? quad_floats(g, n_al) : (size_t)n_al * g->n_planes * g->d.n_radial + 4;
-        if (hipMalloc(&big, sizeof(float) * n) != hipSuccess) {
+        big = (float*)scratch_take(g, sizeof(float) * n, &big_bytes);
+        if (!big) {
             work_free(&w);
             return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of the ratio sinogram failed");
         }
@@ -1186,7 +1271,7 @@ int pet_os_subset_gradient(const pet_os_geom* g, const pet_os_params* p, const f
         rc = launch_bp(g, B, s);
     }
     if (hipStreamSynchronize(s) != hipSuccess && !rc) rc = fail(PET_OS_ERR_DEVICE, "stream synchronize failed");
-    if (big) (void)hipFree(big);
+    if (big) scratch_give(g, big, big_bytes);
     work_free(&w);
     return rc;
 }
@@ -1305,10 +1390,11 @@ int pet_os_reconstruct(const pet_os_geom* g, const pet_os_params* p, float* f, c
     if (n_iter < 0) return fail(PET_OS_ERR_INVALID_ARG, "n_iter must be >= 0");
     if (obj && p->objective_every < 1) return fail(PET_OS_ERR_INVALID_ARG, "objective_every must be >= 1");
     pet_os_state* st = nullptr;
-    int rc = pet_os_state_create(g, p, &st);
+    int rc = state_create(g, p, true, &st);
     if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
     if ((rc = check_state_data(st, f, y, r, s))) {
+        (void)hipStreamSynchronize(s);
         pet_os_state_destroy(st);
         return rc;
     }
@@ -1323,7 +1409,7 @@ int pet_os_reconstruct(const pet_os_geom* g, const pet_os_params* p, float* f, c
         rc = read_objectives(st, n_iter + 1, have, obj, 0, s);
         if (!rc && !std::isfinite(obj[n_iter])) rc = fail(PET_OS_ERR_NUMERIC, "objective is not finite");
     }
-    // the state's scratch is released below: wait for the queued work first
+    // the state's scratch is given back below: wait for the queued work first
     if (hipStreamSynchronize(s) != hipSuccess && !rc) rc = fail(PET_OS_ERR_DEVICE, "stream synchronize failed");
     pet_os_state_destroy(st);
     return rc;

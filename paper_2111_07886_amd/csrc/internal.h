@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include <string>
+#include <mutex>
 #include <vector>
 
 #include "../../include/pet_os.h"
@@ -77,6 +78,13 @@ struct pet_os_geom {
     int tuned_dpg = 0;                  // 3D ring differences per staging group (0: default)
     bool full_model = false;            // sub-rays, PSF or attenuation (2D; single-request paths only)
     std::vector<int> subset_angles(int subset) const;   // subset in 1..M, 0 = all
+    // scratch of whole calls kept between them (scratch_take, scratch_give)
+    struct Kept {
+        void* p;
+        size_t bytes;
+    };
+    mutable std::mutex kept_mu;
+    mutable std::vector<Kept> kept;
 };
 
 namespace petos {
@@ -97,16 +105,28 @@ struct Work {
     unsigned* check_part = nullptr;            // data check: per-block counts [CHECK_GRID][4]
     unsigned long long* check_total = nullptr; // data check: the four totals
     size_t bytes = 0;
+    const pet_os_geom* keeper = nullptr;       // work_free leaves the scratch with this geometry
 };
 
+// Device memory that a whole call uses and has finished with (its stream
+// synchronized) when it gives it back: a geometry keeps up to two blocks of
+// KEPT_MAX bytes together for its next calls, on any thread or stream, and
+// frees them with itself.  A block taken holds whatever the last call left.
+constexpr size_t KEPT_MAX = (size_t)256 << 20;
+void* scratch_take(const pet_os_geom* g, size_t bytes, size_t* got);
+void scratch_give(const pet_os_geom* g, void* p, size_t bytes);
+void scratch_drop(const pet_os_geom* g);      // free what is kept
+
 // sums: with the partials of the sums over all bins (default U, nnz)
-int work_alloc(const pet_os_geom* g, bool need_nu, Work* w, bool sums = false);
+// (keep: the scratch of a whole call, from and to the geometry's kept blocks)
+int work_alloc(const pet_os_geom* g, bool need_nu, Work* w, bool sums = false, bool keep = false);
 void work_free(Work* w);
 // bytes of one request's scratch, and the same scratch placed in caller
 // memory at base (cap bytes, 256-byte aligned): no allocation; the reduction
 // totals are cleared by a fill kernel on s.  Requests of more than `most`
 // bytes with the subset sinogram bin by bin are refused, whatever its layout.
 size_t work_bytes(const pet_os_geom* g, bool need_nu);
+void work_carve_at(const pet_os_geom* g, bool need_nu, void* base, Work* w);   // (work_bytes there, nothing cleared)
 int work_place(const pet_os_geom* g, bool need_nu, void* base, size_t cap, size_t most, Work* w, hipStream_t s);
 
 // device angle lists of a geometry
@@ -240,6 +260,11 @@ int launch_check_data(const float* y, const float* r, int64_t nb, const float* f
 // returns INVALID_ARG with the rule that failed (capi.cpp)
 int check_data(const pet_os_geom* g, const pet_os_params* p, Work* w, const float* f, const float* y,
                const float* r, hipStream_t s);
+// its halves: the kernels queued, and the error (or none) that totals read
+// back from total[4] stand for
+int check_launch(const pet_os_geom* g, const pet_os_params* p, unsigned* part, unsigned long long* total,
+                 const float* f, const float* y, const float* r, hipStream_t s);
+int check_verdict(const pet_os_params* p, const unsigned long long* total);
 int launch_rdp_value(const pet_os_geom* g, const float* f, float gamma_R, float eps, Reduction red,
                      hipStream_t s);
 int launch_fill(float* x, int64_t n, float v, hipStream_t s);
@@ -398,6 +423,7 @@ struct pet_os_state {
     // 3D: bin-major copy of the (y, r) buffers yr_y, yr_r (made with the data
     // check, when the state may allocate)
     float2* yr = nullptr;
+    size_t yr_bytes = 0;
     const float* yr_y = nullptr;
     const float* yr_r = nullptr;
     bool may_allocate = true;
