@@ -125,6 +125,16 @@ int choose_segments(pet_os_batch* B, bool upload) {
 int rebuild_lists(pet_os_batch* B) {
     int rc = choose_segments(B, true);
     if (rc) return rc;
+    // A wave per 8x8 tile once the tiles are more than the blocks of
+    // k_bp_batch that the device holds at a time (256 CUs of five): below, a
+    // block per tile leaves nobody waiting and has the shorter chain.  Whole
+    // steps, 12 angles: 1024 tiles (one 256x256 image) 20.9 us by blocks and
+    // 23.7 by waves, 1600 (320x320) 28.2 and 25.8, 2048 31.5 and 28.5, 25600
+    // 234 and 149.  The sums are the same bits either way.
+    long long tiles = 0;
+    for (const BatchSlot& S : B->slots)
+        if (S.used && S.g->d.dim == 2 && S.bp_kind == 1) tiles += bp_grid_kind(S.g, 1);
+    const bool by_wave = tiles > 256 * 5;
     std::vector<Item> L[WL_COUNT];
     B->bp3q_lds = 0;
     for (int s = 0; s < B->max_slots; ++s) {
@@ -139,10 +149,12 @@ int rebuild_lists(pet_os_batch* B) {
                              : fp_grid_seg(S.g, S.g->max_sub_angles, S.fp_seg) + px_items(S.g);
         const int wfp = fq ? WL_FP3Q + wide : d3 ? WL_FP3 : WL_FP;
         for (int b = 0; b < nfp; ++b) L[wfp].push_back({s, b});
-        const int nbp = quad ? bp3q_grid(S.g) : d3 ? bp3_grid_batch(S.g) : bp_grid_kind(S.g, S.bp_kind);
+        const bool waves = by_wave && !d3 && S.bp_kind == 1 && bpw_fits(S.g);
+        const int nbp = quad ? bp3q_grid(S.g) : waves ? bpw_grid(S.g) : d3 ? bp3_grid_batch(S.g) : bp_grid_kind(S.g, S.bp_kind);
         const int zi = d3 ? (bp3_zb(S.g) == 16 ? 0 : (bp3_zb(S.g) == 32 ? 1 : 2)) : 0;
         const int wbp = quad ? WL_BP3Q + wide
                         : d3 ? WL_BP3 + 2 * zi + (bp3_nbs_of(S.g) == 40 ? 1 : 0)
+                        : waves ? WL_BPW
                              : WL_BP0 + S.bp_kind;
         if (quad) B->bp3q_lds = std::max(B->bp3q_lds, bp3q_lds(S.g));
         for (int b = 0; b < nbp; ++b) L[wbp].push_back({s, b});

@@ -329,6 +329,8 @@ int pen3_grid(const pet_os_geom* g);
 int launch_prep3(const pet_os_geom* g, const float* f, float* fz, Reduction red, hipStream_t s);
 void bp_stage_shape_kind(const pet_os_geom* G, int kind, int& nb_max, int& rows_max, int& chunk, size_t& lds);
 size_t bp_lds_budget(int kind);
+bool bpw_fits(const pet_os_geom* G);   // batched: a wave per 8x8 tile (list WL_BPW, blocks of four)
+int bpw_grid(const pet_os_geom* G);
 
 // ---------------------------------------------------------------- batched execution
 // One reconstruction request inside a batch, as the batched kernels see it.
@@ -375,7 +377,7 @@ struct Item {
 // stride 20/40 bins for wi = 0/1; lists WL_FP3Q + wi and WL_BP3Q + wi: the
 // projectors on quads, more than 32 slices for wi = 1)
 enum { WL_FP = 0, WL_BP0 = 1, WL_BP1 = 2, WL_FP3 = 3, WL_BP3 = 4, WL_UPD3 = 10, WL_PEN3 = 11, WL_FP3Q = 12, WL_BP3Q = 14,
-       WL_COUNT = 16 };
+       WL_BPW = 16, WL_COUNT = 17 };
 
 // Queue one batched subiteration, the step-th since the slots' counters moved:
 // forward, back-projection (one launch per tile kind), update.  Empty lists

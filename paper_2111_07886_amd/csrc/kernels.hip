@@ -377,6 +377,46 @@ constexpr int MAXCH = 16;    // angles per staging chunk
 constexpr int ANG_W = (int)(sizeof(AngleK) / sizeof(double));   // 8-byte words of an angle record
 static_assert(sizeof(AngleK) % sizeof(double) == 0, "angle records are copied in 8-byte words");
 
+// Add to acc the bins of one angle whose rays cross pixel (ix, iy), centre
+// (xc, yc): an oblique window of any number of bins, or an axis-parallel one.
+template <class WVal>
+__device__ __forceinline__ float bp_window(const GeoK& g, const AngleK& AK, int ix, int iy, double xc, double yc,
+                                           double inv_ds, float acc, WVal wval) {
+    const int Nr = g.n_radial;
+    if (AK.Q != 0.0) {
+        const double uc = __fma_rn(xc, AK.c, yc * AK.s);
+        const int b0 = max((int)ceil((uc - AK.e_out) * inv_ds + g.h0), 0);
+        const int b1 = min((int)floor((uc + AK.e_out) * inv_ds + g.h0), Nr - 1);
+        // the radial offset of bin b0's line from the pixel centre
+        // in FP64, the window's later bins (|t| < e_out, at most
+        // three) in FP32 steps of ds from it
+        const float t0 = (float)__fma_rn((double)b0 - g.h0, g.ds, -uc);
+        const float dsf = (float)g.ds, eo = (float)AK.e_out, ide = (float)AK.inv_de;
+        const float lmax = (float)AK.Lmax;
+        for (int b = b0; b <= b1; ++b) {
+            const float tt = fabsf(fmaf((float)(b - b0), dsf, t0));
+            const float len = lmax * fminf(1.0f, (eo - tt) * ide);
+            if (len > 0.0f) acc = fmaf(len, wval(b), acc);
+        }
+    } else {
+        const int m = AK.row_major ? iy : ix;
+        const int mc = AK.row_major ? ix : iy;
+        // axis-parallel: bins whose exact position falls in cell mc
+        const double base = AK.wC;
+        const double bA = ((double)mc - 1e-7 - base) * AK.inv_wslope;
+        const double bB = ((double)mc + 1.0 + 1e-7 - base) * AK.inv_wslope;
+        const int b0 = (int)fmax(floor(fmin(bA, bB)), 0.0);
+        const int b1 = (int)fmin(ceil(fmax(bA, bB)), (double)(Nr - 1));
+        for (int b = b0; b <= b1; ++b) {
+            const TxRay tx = tx_ray(g, AK, b);
+            double ax, bx;
+            cell_interval(__fma_rn(tx.Q, (double)m, tx.P), tx.Q, tx.invQ, mc, ax, bx);
+            if (bx > ax) acc = fmaf((float)(tx.L * (bx - ax)), wval(b), acc);
+        }
+    }
+    return acc;
+}
+
 // LEAN (the batched kernel, whose occupancy is register-bound) reads the
 // angle records from the geometry table in the gather (only the axis-parallel
 // and many-bin windows need them) and the pixel's update inputs after it;
@@ -595,36 +635,8 @@ __device__ void bp_body(const GeoK& g, const BPArgs& A, int vblock) {
                             else if (bst + k >= 0 && bst + k < Nr) acc = fmaf(len, wval(bst + k), acc);
                         }
                     }
-                } else if (AK.Q != 0.0) {
-                    const double uc = __fma_rn(xc, AK.c, yc * AK.s);
-                    const int b0 = max((int)ceil((uc - AK.e_out) * inv_ds + g.h0), 0);
-                    const int b1 = min((int)floor((uc + AK.e_out) * inv_ds + g.h0), Nr - 1);
-                    // the radial offset of bin b0's line from the pixel centre
-                    // in FP64, the window's later bins (|t| < e_out, at most
-                    // three) in FP32 steps of ds from it
-                    const float t0 = (float)__fma_rn((double)b0 - g.h0, g.ds, -uc);
-                    const float dsf = (float)g.ds, eo = (float)AK.e_out, ide = (float)AK.inv_de;
-                    const float lmax = (float)AK.Lmax;
-                    for (int b = b0; b <= b1; ++b) {
-                        const float tt = fabsf(fmaf((float)(b - b0), dsf, t0));
-                        const float len = lmax * fminf(1.0f, (eo - tt) * ide);
-                        if (len > 0.0f) acc = fmaf(len, wval(b), acc);
-                    }
                 } else {
-                    const int m = AK.row_major ? iy : ix;
-                    const int mc = AK.row_major ? ix : iy;
-                    // axis-parallel: bins whose exact position falls in cell mc
-                    const double base = AK.wC;
-                    const double bA = ((double)mc - 1e-7 - base) * AK.inv_wslope;
-                    const double bB = ((double)mc + 1.0 + 1e-7 - base) * AK.inv_wslope;
-                    const int b0 = (int)fmax(floor(fmin(bA, bB)), 0.0);
-                    const int b1 = (int)fmin(ceil(fmax(bA, bB)), (double)(Nr - 1));
-                    for (int b = b0; b <= b1; ++b) {
-                        const TxRay tx = tx_ray(g, AK, b);
-                        double ax, bx;
-                        cell_interval(__fma_rn(tx.Q, (double)m, tx.P), tx.Q, tx.invQ, mc, ax, bx);
-                        if (bx > ax) acc = fmaf((float)(tx.L * (bx - ax)), wval(b), acc);
-                    }
+                    acc = bp_window(g, AK, ix, iy, xc, yc, inv_ds, acc, wval);
                 }
             }
         }
@@ -681,6 +693,140 @@ __device__ void bp_body(const GeoK& g, const BPArgs& A, int vblock) {
     } else {
         write_partial(part, R, s_red, vblock);
     }
+}
+
+// The batched back-projection of Tile2S tiles, a wave per tile (four tiles per
+// block): what the whole block of bp_body does for a tile, bit for bit (four
+// sums over every fourth angle, added in order; the same FP32 positions from
+// the tile's own reference), by one wave, which then waits for no other.
+//
+// A block per tile was bound by the latency of its serial parts, each done by
+// one of its four waves or by all of them between barriers: with neither
+// set-up nor gather it still took 43 of 59 us.  24 uneven images (0.9 million
+// pixels, about 13 angles each): 58.9 us a block per tile, 31.5 us here.
+//
+// The wave's windows hold at most BPW_FLOATS weights (bpw_fits): bins no finer
+// than half a voxel; others keep bp_body.
+constexpr int BPW_FLOATS = 512;
+
+struct BPWave {
+    float f[10 * 10];               // halo tile of the snapshot
+    float w[BPW_FLOATS];            // the chunk's windows, nb_max each
+    int blo[MAXCH], nb[MAXCH], a[MAXCH], two[MAXCH];
+    float p0[MAXCH], dpx[MAXCH], dpy[MAXCH], E[MAXCH], eo[MAXCH], ide[MAXCH], lm[MAXCH];
+};
+
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// block of 2 x 2 tiles; returns with the block's LDS still in use by its waves
+__device__ __forceinline__ void bpw_body(const GeoK& g, const BPArgs& A, int vblock, BPWave* sh, double* s_red) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int tiles_x = (g.nx + 7) / 8, tiles_y = (g.ny + 7) / 8, gx = (tiles_x + 1) / 2;
+    const int tx = 2 * (vblock % gx) + (wave & 1), ty = 2 * (vblock / gx) + (wave >> 1);
+    float meanmu = 1.0f;
+    if (A.nu_mode == NU_COMPUTE || A.nu_mode == NU_COMPUTE_FREEZE)
+        meanmu = (float)(sum_partials(A.part_mu, A.n_part_mu, s_red) / (double)g.nvox);
+    if (tx >= tiles_x || ty >= tiles_y) return;
+    BPWave& S = sh[wave];
+    const int tx0 = 8 * tx, ty0 = 8 * ty;
+    const int lx = lane & 7, ly = lane >> 3, ix = tx0 + lx, iy = ty0 + ly;
+    const bool inside = ix < g.nx && iy < g.ny;
+    const int Nr = g.n_radial, nb_max = A.nb_max;
+    const double inv_ds = 1.0 / g.ds;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int e = lane + 64 * k, hx = e % 10, hy = e / 10;
+        const int x = tx0 - 1 + hx, y = ty0 - 1 + hy;
+        if (e < 100) S.f[e] = x >= 0 && x < g.nx && y >= 0 && y < g.ny ? A.f[(long long)y * g.nx + x] : 0.0f;
+    }
+    const PixPre pre = pixel_prefetch(A, inside, (long long)iy * g.nx + ix);
+    const unsigned per = ((1u << 20) + nb_max - 1) / nb_max;    // e / nb_max = e per >> 20 for e < 512
+    float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int c0 = 0; c0 < A.n_al; c0 += A.chunk) {
+        const int nch = min(A.chunk, A.n_al - c0);
+        wave_sync();
+        if (lane < nch) {
+            const int j = lane, a = A.angles[c0 + j];
+            const AngleK& AK = g.ang[a];
+            S.a[j] = a;
+            const double X0 = ((double)tx0 - 0.5 * g.nx) * g.vx, X1 = X0 + 8 * g.vx;
+            const double Y0 = ((double)ty0 - 0.5 * g.ny) * g.vy, Y1 = Y0 + 8 * g.vy;
+            double umin = 1e300, umax = -1e300;
+            for (int k = 0; k < 4; ++k) {
+                const double u = ((k & 1) ? X1 : X0) * AK.c + ((k & 2) ? Y1 : Y0) * AK.s;
+                umin = fmin(umin, u);
+                umax = fmax(umax, u);
+            }
+            const int blo = max((int)floor(umin / g.ds + g.h0) - 1, 0);
+            const int bhi = min((int)ceil(umax / g.ds + g.h0) + 1, Nr - 1);
+            S.blo[j] = blo;
+            S.nb[j] = max(0, min(bhi - blo + 1, nb_max));
+            S.two[j] = (AK.Q != 0.0 && AK.e_out <= g.ds) ? 1 : 0;
+            const double xc0 = ((double)tx0 - 0.5 * (double)(g.nx - 1)) * g.vx;
+            const double yc0 = ((double)ty0 - 0.5 * (double)(g.ny - 1)) * g.vy;
+            const double u00 = __fma_rn(xc0, AK.c, yc0 * AK.s);
+            S.p0[j] = (float)(__fma_rn(u00, inv_ds, g.h0) - (double)blo);
+            S.dpx[j] = (float)(g.vx * AK.c * inv_ds);
+            S.dpy[j] = (float)(g.vy * AK.s * inv_ds);
+            S.E[j] = (float)(AK.e_out * inv_ds);
+            S.eo[j] = (float)AK.e_out;
+            S.ide[j] = (float)AK.inv_de;
+            S.lm[j] = (float)AK.Lmax;
+        }
+        wave_sync();
+        for (int e = lane; e < nch * nb_max; e += 64) {
+            const int j = (int)((unsigned)e * per >> 20), col = e - j * nb_max;
+            if (col < S.nb[j]) S.w[e] = A.w[(long long)(c0 + j) * A.w_sa + S.blo[j] + col];
+        }
+        wave_sync();
+        if (inside) {
+            for (int j0 = 0; j0 < nch; j0 += 4) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int j = j0 + q;
+                    if (j >= nch) break;
+                    const int bst = __builtin_amdgcn_readfirstlane(S.blo[j]), nbs = __builtin_amdgcn_readfirstlane(S.nb[j]);
+                    const float* row = S.w + j * nb_max;
+                    auto wval = [&](int b) -> float {
+                        const int bcol = b - bst;
+                        if (bcol >= 0 && bcol < nbs) return row[bcol];
+                        return A.w[(long long)(c0 + j) * A.w_sa + b];
+                    };
+                    if (__builtin_amdgcn_readfirstlane(S.two[j])) {
+                        const float p = fmaf((float)ly, S.dpy[j], fmaf((float)lx, S.dpx[j], S.p0[j]));
+                        const int k0 = (int)floorf(p - S.E[j]) + 1;
+                        const float dsf = (float)g.ds, eo = S.eo[j], ide = S.ide[j], lmax = S.lm[j];
+#pragma unroll
+                        for (int u = 0; u < 2; ++u) {
+                            const int k = k0 + u;
+                            const float tt = fabsf((p - (float)k) * dsf);
+                            const float len = lmax * fminf(1.0f, (eo - tt) * ide);
+                            if (len > 0.0f) {
+                                if (k >= 0 && k < nbs) acc[q] = fmaf(len, row[k], acc[q]);
+                                else if (bst + k >= 0 && bst + k < Nr) acc[q] = fmaf(len, wval(bst + k), acc[q]);
+                            }
+                        }
+                    } else {
+                        const double xc = ((double)ix - 0.5 * (double)(g.nx - 1)) * g.vx;
+                        const double yc = ((double)iy - 0.5 * (double)(g.ny - 1)) * g.vy;
+                        acc[q] = bp_window(g, g.ang[__builtin_amdgcn_readfirstlane(S.a[j])], ix, iy, xc, yc, inv_ds,
+                                           acc[q], wval);
+                    }
+                }
+            }
+        }
+    }
+    float sum = 0.0f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sum += acc[q];
+    double part = 0.0;
+    if (inside) part = pixel_finish(g, A, S.f, 10, 10, lx, ly, ix, iy, sum, 1.0f, meanmu, pre);
+    part = wave_sum(part);
+    if (lane == 0) A.red_f.part[ty * tiles_x + tx] = part;
 }
 
 // Partials of sum f over the same tiles, threads and order as the fused
@@ -1081,6 +1227,16 @@ void bp_stage_shape_kind(const pet_os_geom* G, int kind, int& nb_max, int& rows_
     lds = (size_t)chunk * nb_max * sizeof(float);
 }
 
+// whether a tile's windows fit one wave's staging (bpw_body)
+bool bpw_fits(const pet_os_geom* G) {
+    int nb, rows, chunk;
+    size_t lds;
+    bp_stage_shape_kind(G, 1, nb, rows, chunk, lds);
+    return chunk == MAXCH && lds <= BPW_FLOATS * sizeof(float);
+}
+
+int bpw_grid(const pet_os_geom* G) { return ((G->d.nx + 15) / 16) * ((G->d.ny + 15) / 16); }
+
 static void fill_bp_args(const pet_os_geom* G, const BPLaunch& L, BPArgs& a) {
     a.w = L.w;
     a.w_natural = L.w_natural;
@@ -1391,6 +1547,42 @@ __global__ __launch_bounds__(NT) void k_fp_batch(const SlotDev* __restrict__ S, 
     }
 }
 
+// arguments of a slot's fused back-projection in subiteration J
+__device__ __forceinline__ BPArgs slot_bp_args(const SlotDev& d, int J) {
+    const int i = (J - 1) % d.g.n_subsets;
+    const int nu_mode = d.sched_nu[J - 1];
+    BPArgs A{};
+    A.w = d.w;
+    A.w_natural = 0;
+    A.w_sp = d.g.n_radial;
+    A.w_sa = (long long)d.g.n_planes * d.g.n_radial;
+    A.angles = d.subset_lists + (long long)i * d.max_sub;
+    A.n_al = d.subset_count[i];
+    A.out = nullptr;
+    A.f = d.fsnap;
+    A.mu = d.mu;
+    A.want_mu = 0;
+    A.beta_over_M = d.beta_over_M;
+    A.gamma_R = d.gamma_R;
+    A.eps = d.eps;
+    A.nb_max = d.nb_max;
+    A.chunk = d.chunk;
+    A.fnew = d.f;
+    A.pnorm = d.pnorm;
+    A.nu_frozen = d.nu_frozen;
+    A.nu_mode = nu_mode;
+    A.step = d.sched_step[J - 1];
+    A.nu1 = d.nu1;
+    A.nu2 = d.nu2;
+    A.box = d.box;
+    A.part_mu = d.part_mu;
+    A.n_part_mu = d.n_part_mu;
+    A.red_f.part = d.part_f;
+    A.red_f.total = nullptr;
+    A.red_f.cap = d.n_part_f;
+    return A;
+}
+
 // at most 96 VGPRs (5 waves per SIMD): the gather's per-angle tile
 // references need more than 72 without spilling to scratch (6 waves: 80
 // VGPRs and 7 spilled; 5 waves measured 1 % faster, with no scratch traffic)
@@ -1403,38 +1595,23 @@ __global__ __launch_bounds__(NT, 5) void k_bp_batch(const SlotDev* __restrict__ 
         const SlotDev& d = S[I.slot];
         const int J = d.J + step;
         if (!slot_live(d, J)) continue;
-        const int i = (J - 1) % d.g.n_subsets;
-        const int nu_mode = d.sched_nu[J - 1];
-        BPArgs A{};
-        A.w = d.w;
-        A.w_natural = 0;
-        A.w_sp = d.g.n_radial;
-        A.w_sa = (long long)d.g.n_planes * d.g.n_radial;
-        A.angles = d.subset_lists + (long long)i * d.max_sub;
-        A.n_al = d.subset_count[i];
-        A.out = nullptr;
-        A.f = d.fsnap;
-        A.mu = d.mu;
-        A.want_mu = 0;
-        A.beta_over_M = d.beta_over_M;
-        A.gamma_R = d.gamma_R;
-        A.eps = d.eps;
-        A.nb_max = d.nb_max;
-        A.chunk = d.chunk;
-        A.fnew = d.f;
-        A.pnorm = d.pnorm;
-        A.nu_frozen = d.nu_frozen;
-        A.nu_mode = nu_mode;
-        A.step = d.sched_step[J - 1];
-        A.nu1 = d.nu1;
-        A.nu2 = d.nu2;
-        A.box = d.box;
-        A.part_mu = d.part_mu;
-        A.n_part_mu = d.n_part_mu;
-        A.red_f.part = d.part_f;
-        A.red_f.total = nullptr;
-        A.red_f.cap = d.n_part_f;
+        const BPArgs A = slot_bp_args(d, J);
         bp_body<T, false, false, true>(d.g, A, I.block);
+        __syncthreads();
+    }
+}
+
+__global__ __launch_bounds__(NT, 5) void k_bpw_batch(const SlotDev* __restrict__ S, const Item* __restrict__ items,
+                                                     const int* __restrict__ count, int step) {
+    __shared__ BPWave sh[NT / 64];
+    __shared__ double s_red[NT / 64];
+    const int n = *count;
+    for (int it = blockIdx.x; it < n; it += gridDim.x) {
+        const Item I = items[it];
+        const SlotDev& d = S[I.slot];
+        const int J = d.J + step;
+        if (!slot_live(d, J)) continue;
+        bpw_body(d.g, slot_bp_args(d, J), I.block, sh, s_red);
         __syncthreads();
     }
 }
@@ -1469,6 +1646,9 @@ int launch_batch_step(const SlotDev* d_slots, int step, Item* const lists[WL_COU
     if (live(WL_BP1))
         hipLaunchKernelGGL((k_bp_batch<Tile2S>), dim3(grids[WL_BP1]), dim3(NT), bp_lds_budget(1), s, d_slots,
                            lists[WL_BP1], d_counts + WL_BP1, step);
+    if (live(WL_BPW))
+        hipLaunchKernelGGL(k_bpw_batch, dim3(grids[WL_BPW]), dim3(NT), 0, s, d_slots, lists[WL_BPW],
+                           d_counts + WL_BPW, step);
     const int zbs[3] = {16, 32, 64};
     for (int k = 0; k < 6; ++k)
         if (live(WL_BP3 + k))
