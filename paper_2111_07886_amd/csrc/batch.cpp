@@ -129,8 +129,8 @@ int rebuild_lists(pet_os_batch* B) {
     // k_bp_batch that the device holds at a time (256 CUs of five): below, a
     // block per tile leaves nobody waiting and has the shorter chain.  Whole
     // steps, 12 angles: 1024 tiles (one 256x256 image) 20.9 us by blocks and
-    // 23.7 by waves, 1600 (320x320) 28.2 and 25.8, 2048 31.5 and 28.5, 25600
-    // 234 and 149.  The sums are the same bits either way.
+    // 23.7 by waves, 1600 (320x320) 28.2 and 24.0, 3200 42.1 and 32.3, 25600
+    // 234 and 142.  The sums are the same bits either way.
     long long tiles = 0;
     for (const BatchSlot& S : B->slots)
         if (S.used && S.g->d.dim == 2 && S.bp_kind == 1) tiles += bp_grid_kind(S.g, 1);

@@ -695,25 +695,33 @@ __device__ void bp_body(const GeoK& g, const BPArgs& A, int vblock) {
     }
 }
 
-// The batched back-projection of Tile2S tiles, a wave per tile (four tiles per
-// block): what the whole block of bp_body does for a tile, bit for bit (four
-// sums over every fourth angle, added in order; the same FP32 positions from
-// the tile's own reference), by one wave, which then waits for no other.
+// The back-projection of Tile2S tiles, a wave per tile (four tiles per block):
+// what the whole block of bp_body does for a tile, bit for bit (four sums over
+// every fourth angle, added in order; the same FP32 positions from the tile's
+// own reference), by one wave, which then waits for no other.
 //
 // A block per tile was bound by the latency of its serial parts, each done by
-// one of its four waves or by all of them between barriers: with neither
-// set-up nor gather it still took 43 of 59 us.  24 uneven images (0.9 million
-// pixels, about 13 angles each): 58.9 us a block per tile, 31.5 us here.
+// one of its four waves or by all of them between barriers: in a batch of 24
+// uneven images (0.9 million pixels, about 13 angles each) it took 43 of 59 us
+// with neither set-up nor gather.  A wave per tile takes 29.4 us: 16 without
+// both, 2 of set-up, 3 of staging, and the gather, which is bound by its
+// instructions (35 per angle and pixel).  One image of 320x320: 22 angles 18.7
+// and 14.8 us, 11 angles 15.3 and 12.2; 448x448, 45 angles: 53 and 28.  While
+// the tiles leave compute units free a block per tile has the shorter chain:
+// the callers' rules say where.
 //
 // The wave's windows hold at most BPW_FLOATS weights (bpw_fits): bins no finer
 // than half a voxel; others keep bp_body.
 constexpr int BPW_FLOATS = 512;
+constexpr int BPW_Q = 2;            // angles gathered together
 
 struct BPWave {
     float f[10 * 10];               // halo tile of the snapshot
     float w[BPW_FLOATS];            // the chunk's windows, nb_max each
-    int blo[MAXCH], nb[MAXCH], a[MAXCH], two[MAXCH];
-    float p0[MAXCH], dpx[MAXCH], dpy[MAXCH], E[MAXCH], eo[MAXCH], ide[MAXCH], lm[MAXCH];
+    // per angle: the window (first bin, bins), whether it has the closed form,
+    // the angle; its positions (bp_body's s_p0, s_dpx, s_dpy, s_E); its trapezoid
+    int4 win[MAXCH];
+    float4 pos[MAXCH], trap[MAXCH];
 };
 
 __device__ __forceinline__ void wave_sync() {
@@ -728,7 +736,7 @@ __device__ __forceinline__ void bpw_body(const GeoK& g, const BPArgs& A, int vbl
     const int tiles_x = (g.nx + 7) / 8, tiles_y = (g.ny + 7) / 8, gx = (tiles_x + 1) / 2;
     const int tx = 2 * (vblock % gx) + (wave & 1), ty = 2 * (vblock / gx) + (wave >> 1);
     float meanmu = 1.0f;
-    if (A.nu_mode == NU_COMPUTE || A.nu_mode == NU_COMPUTE_FREEZE)
+    if (A.fnew != nullptr && (A.nu_mode == NU_COMPUTE || A.nu_mode == NU_COMPUTE_FREEZE))
         meanmu = (float)(sum_partials(A.part_mu, A.n_part_mu, s_red) / (double)g.nvox);
     if (tx >= tiles_x || ty >= tiles_y) return;
     BPWave& S = sh[wave];
@@ -741,10 +749,12 @@ __device__ __forceinline__ void bpw_body(const GeoK& g, const BPArgs& A, int vbl
     for (int k = 0; k < 2; ++k) {
         const int e = lane + 64 * k, hx = e % 10, hy = e / 10;
         const int x = tx0 - 1 + hx, y = ty0 - 1 + hy;
-        if (e < 100) S.f[e] = x >= 0 && x < g.nx && y >= 0 && y < g.ny ? A.f[(long long)y * g.nx + x] : 0.0f;
+        if (A.f != nullptr && e < 100)
+            S.f[e] = x >= 0 && x < g.nx && y >= 0 && y < g.ny ? A.f[(long long)y * g.nx + x] : 0.0f;
     }
     const PixPre pre = pixel_prefetch(A, inside, (long long)iy * g.nx + ix);
     const unsigned per = ((1u << 20) + nb_max - 1) / nb_max;    // e / nb_max = e per >> 20 for e < 512
+    const float dsf = (float)g.ds;
     float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     for (int c0 = 0; c0 < A.n_al; c0 += A.chunk) {
         const int nch = min(A.chunk, A.n_al - c0);
@@ -752,7 +762,6 @@ __device__ __forceinline__ void bpw_body(const GeoK& g, const BPArgs& A, int vbl
         if (lane < nch) {
             const int j = lane, a = A.angles[c0 + j];
             const AngleK& AK = g.ang[a];
-            S.a[j] = a;
             const double X0 = ((double)tx0 - 0.5 * g.nx) * g.vx, X1 = X0 + 8 * g.vx;
             const double Y0 = ((double)ty0 - 0.5 * g.ny) * g.vy, Y1 = Y0 + 8 * g.vy;
             double umin = 1e300, umax = -1e300;
@@ -763,58 +772,86 @@ __device__ __forceinline__ void bpw_body(const GeoK& g, const BPArgs& A, int vbl
             }
             const int blo = max((int)floor(umin / g.ds + g.h0) - 1, 0);
             const int bhi = min((int)ceil(umax / g.ds + g.h0) + 1, Nr - 1);
-            S.blo[j] = blo;
-            S.nb[j] = max(0, min(bhi - blo + 1, nb_max));
-            S.two[j] = (AK.Q != 0.0 && AK.e_out <= g.ds) ? 1 : 0;
+            S.win[j] = make_int4(blo, max(0, min(bhi - blo + 1, nb_max)), (AK.Q != 0.0 && AK.e_out <= g.ds) ? 1 : 0, a);
             const double xc0 = ((double)tx0 - 0.5 * (double)(g.nx - 1)) * g.vx;
             const double yc0 = ((double)ty0 - 0.5 * (double)(g.ny - 1)) * g.vy;
             const double u00 = __fma_rn(xc0, AK.c, yc0 * AK.s);
-            S.p0[j] = (float)(__fma_rn(u00, inv_ds, g.h0) - (double)blo);
-            S.dpx[j] = (float)(g.vx * AK.c * inv_ds);
-            S.dpy[j] = (float)(g.vy * AK.s * inv_ds);
-            S.E[j] = (float)(AK.e_out * inv_ds);
-            S.eo[j] = (float)AK.e_out;
-            S.ide[j] = (float)AK.inv_de;
-            S.lm[j] = (float)AK.Lmax;
+            S.pos[j] = make_float4((float)(__fma_rn(u00, inv_ds, g.h0) - (double)blo), (float)(g.vx * AK.c * inv_ds),
+                                   (float)(g.vy * AK.s * inv_ds), (float)(AK.e_out * inv_ds));
+            S.trap[j] = make_float4((float)AK.e_out, (float)AK.inv_de, (float)AK.Lmax, 0.0f);
+        } else if (lane < MAXCH) {
+            // (no angle: no length anywhere)
+            S.win[lane] = make_int4(0, 0, 1, 0);
+            S.pos[lane] = S.trap[lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         }
         wave_sync();
         for (int e = lane; e < nch * nb_max; e += 64) {
             const int j = (int)((unsigned)e * per >> 20), col = e - j * nb_max;
-            if (col < S.nb[j]) S.w[e] = A.w[(long long)(c0 + j) * A.w_sa + S.blo[j] + col];
+            const int4 W = S.win[j];
+            if (col < W.y) S.w[e] = A.w[(long long)(A.w_natural ? W.w : c0 + j) * A.w_sa + W.x + col];
         }
         wave_sync();
-        if (inside) {
-            for (int j0 = 0; j0 < nch; j0 += 4) {
+        // four angles at a time.  Closed forms, every bin that counts in its
+        // window (unless a pixel's bins leave the detector): without a branch,
+        // so that the four angles' LDS reads are under way together
+        for (int jj = 0; jj < nch; jj += 4)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
+        for (int h = 0; h < 4; h += BPW_Q) {
+            const int j0 = jj + h;
+            int4 W[BPW_Q];
+            float len[BPW_Q][2], w[BPW_Q][2];
+            int closed = 1;
+            bool beyond = false, on[BPW_Q][2];
+#pragma unroll
+            for (int q = 0; q < BPW_Q; ++q) {
+                W[q] = S.win[j0 + q];
+                const float4 P = S.pos[j0 + q], T = S.trap[j0 + q];
+                closed &= W[q].z;
+                const float p = fmaf((float)ly, P.z, fmaf((float)lx, P.y, P.x));
+                const float* row = S.w + (j0 + q) * nb_max;
+                const float f0 = floorf(p - P.w) + 1.0f;
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int k = (int)f0 + u;
+                    const float tt = fabsf((p - (f0 + (float)u)) * dsf);
+                    len[q][u] = T.z * fminf(1.0f, (T.x - tt) * T.y);
+                    w[q][u] = row[min((unsigned)k, (unsigned)(nb_max - 1))];
+                    const bool in = (unsigned)k < (unsigned)W[q].y;
+                    on[q][u] = len[q][u] > 0.0f && in;
+                    beyond |= len[q][u] > 0.0f && !in;
+                }
+            }
+            if (__builtin_amdgcn_readfirstlane(closed) && __ballot(beyond && inside) == 0) {
+#pragma unroll
+                for (int q = 0; q < BPW_Q; ++q)
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) acc[h + q] = on[q][u] ? fmaf(len[q][u], w[q][u], acc[h + q]) : acc[h + q];
+            } else if (inside) {
+#pragma unroll
+                for (int q = 0; q < BPW_Q; ++q) {
                     const int j = j0 + q;
                     if (j >= nch) break;
-                    const int bst = __builtin_amdgcn_readfirstlane(S.blo[j]), nbs = __builtin_amdgcn_readfirstlane(S.nb[j]);
+                    const int bst = W[q].x, nbs = W[q].y;
                     const float* row = S.w + j * nb_max;
                     auto wval = [&](int b) -> float {
                         const int bcol = b - bst;
                         if (bcol >= 0 && bcol < nbs) return row[bcol];
-                        return A.w[(long long)(c0 + j) * A.w_sa + b];
+                        return A.w[(long long)(A.w_natural ? W[q].w : c0 + j) * A.w_sa + b];
                     };
-                    if (__builtin_amdgcn_readfirstlane(S.two[j])) {
-                        const float p = fmaf((float)ly, S.dpy[j], fmaf((float)lx, S.dpx[j], S.p0[j]));
-                        const int k0 = (int)floorf(p - S.E[j]) + 1;
-                        const float dsf = (float)g.ds, eo = S.eo[j], ide = S.ide[j], lmax = S.lm[j];
-#pragma unroll
-                        for (int u = 0; u < 2; ++u) {
-                            const int k = k0 + u;
+                    if (__builtin_amdgcn_readfirstlane(W[q].z)) {
+                        const float4 P = S.pos[j], T = S.trap[j];
+                        const float p = fmaf((float)ly, P.z, fmaf((float)lx, P.y, P.x));
+                        const int k0 = (int)floorf(p - P.w) + 1;
+                        for (int k = k0; k < k0 + 2; ++k) {
                             const float tt = fabsf((p - (float)k) * dsf);
-                            const float len = lmax * fminf(1.0f, (eo - tt) * ide);
-                            if (len > 0.0f) {
-                                if (k >= 0 && k < nbs) acc[q] = fmaf(len, row[k], acc[q]);
-                                else if (bst + k >= 0 && bst + k < Nr) acc[q] = fmaf(len, wval(bst + k), acc[q]);
-                            }
+                            const float l = T.z * fminf(1.0f, (T.x - tt) * T.y);
+                            if (l > 0.0f && bst + k >= 0 && bst + k < Nr) acc[h + q] = fmaf(l, wval(bst + k), acc[h + q]);
                         }
                     } else {
                         const double xc = ((double)ix - 0.5 * (double)(g.nx - 1)) * g.vx;
                         const double yc = ((double)iy - 0.5 * (double)(g.ny - 1)) * g.vy;
-                        acc[q] = bp_window(g, g.ang[__builtin_amdgcn_readfirstlane(S.a[j])], ix, iy, xc, yc, inv_ds,
-                                           acc[q], wval);
+                        acc[h + q] = bp_window(g, g.ang[__builtin_amdgcn_readfirstlane(W[q].w)], ix, iy, xc, yc, inv_ds,
+                                           acc[h + q], wval);
                     }
                 }
             }
@@ -823,10 +860,20 @@ __device__ __forceinline__ void bpw_body(const GeoK& g, const BPArgs& A, int vbl
     float sum = 0.0f;
 #pragma unroll
     for (int q = 0; q < 4; ++q) sum += acc[q];
+    if (A.f == nullptr) {
+        if (inside) A.out[(long long)iy * g.nx + ix] = sum;
+        return;
+    }
     double part = 0.0;
     if (inside) part = pixel_finish(g, A, S.f, 10, 10, lx, ly, ix, iy, sum, 1.0f, meanmu, pre);
     part = wave_sum(part);
-    if (lane == 0) A.red_f.part[ty * tiles_x + tx] = part;
+    if (lane == 0 && A.fnew != nullptr) A.red_f.part[ty * tiles_x + tx] = part;
+}
+
+__global__ __launch_bounds__(NT) void k_bpw(GeoK g, BPArgs A) {
+    __shared__ BPWave sh[NT / 64];
+    __shared__ double s_red[NT / 64];
+    bpw_body(g, A, blockIdx.x, sh, s_red);
 }
 
 // Partials of sum f over the same tiles, threads and order as the fused
@@ -1237,6 +1284,14 @@ bool bpw_fits(const pet_os_geom* G) {
 
 int bpw_grid(const pet_os_geom* G) { return ((G->d.nx + 15) / 16) * ((G->d.ny + 15) / 16); }
 
+// One image goes by waves once its tiles are more than the blocks of k_bp that
+// the device holds at a time (256 CUs of four): 256x256 (1024 tiles), 12 angles
+// 10.2 us by blocks and 11.3 by waves, 45 angles 17.9 and 21.8; 280x280 (1225)
+// 14.0 and 12.1, 28.4 and 23.6.
+static bool bpw_single(const pet_os_geom* G) {
+    return bp_grid_kind(G, 1) > 256 * 4 && bpw_fits(G);
+}
+
 static void fill_bp_args(const pet_os_geom* G, const BPLaunch& L, BPArgs& a) {
     a.w = L.w;
     a.w_natural = L.w_natural;
@@ -1291,7 +1346,9 @@ int launch_bp(const pet_os_geom* G, const BPLaunch& L, hipStream_t s) {
     // compiled only into the kernels that need them
     const bool sub = G->k.n_sub > 1, att = a.att != nullptr;
     const dim3 gr(grid), bl(NT);
-    if (kind == 0) {
+    if (kind == 1 && bpw_single(G) && L.w != nullptr && !sub && !att && !L.want_mu) {
+        petos_launch(k_bpw, dim3(bpw_grid(G)), bl, 0, s, G->k, a);
+    } else if (kind == 0) {
         if (sub && att) petos_launch(k_bp<Tile2L, true, true>, gr, bl, lds, s, G->k, a);
         else if (sub) petos_launch(k_bp<Tile2L, true, false>, gr, bl, lds, s, G->k, a);
         else if (att) petos_launch(k_bp<Tile2L, false, true>, gr, bl, lds, s, G->k, a);
