@@ -528,7 +528,7 @@ void work_carve_at(const pet_os_geom* g, bool need_nu, void* base, Work* w) {
 // An allocation and its release cost a short call more than its kernels do
 // (they also wait for the whole device): a 128x128x32 forward projection took
 // 97 us with them for 39 us of kernels.
-void* scratch_take(const pet_os_geom* g, size_t bytes, size_t* got) {
+void* scratch_take(const pet_os_geom* g, size_t bytes, size_t* got, const hipStream_t* s) {
     int dev = -1;
     if (hipGetDevice(&dev) == hipSuccess && dev == g->device) {
         std::lock_guard<std::mutex> lk(g->kept_mu);
@@ -536,10 +536,15 @@ void* scratch_take(const pet_os_geom* g, size_t bytes, size_t* got) {
         for (auto it = g->kept.begin(); it != g->kept.end(); ++it)
             if (it->bytes >= bytes && (best == g->kept.end() || it->bytes < best->bytes)) best = it;
         if (best != g->kept.end()) {
-            void* p = best->p;
-            *got = best->bytes;
+            const pet_os_geom::Kept k = *best;
+            *got = k.bytes;
             g->kept.erase(best);
-            return p;
+            if (k.done) {
+                const hipError_t e = s ? hipStreamWaitEvent(*s, k.done, 0) : hipEventSynchronize(k.done);
+                if (e != hipSuccess) (void)hipDeviceSynchronize();
+                (void)hipEventDestroy(k.done);
+            }
+            return k.p;
         }
     }
     void* p = nullptr;
@@ -556,11 +561,24 @@ void scratch_drop(const pet_os_geom* g) {
         std::lock_guard<std::mutex> lk(g->kept_mu);
         old.swap(g->kept);
     }
-    for (auto& k : old) (void)hipFree(k.p);
+    for (auto& k : old) {
+        if (k.done) {
+            (void)hipEventSynchronize(k.done);
+            (void)hipEventDestroy(k.done);
+        }
+        (void)hipFree(k.p);
+    }
 }
 
-void scratch_give(const pet_os_geom* g, void* p, size_t bytes) {
+void scratch_give(const pet_os_geom* g, void* p, size_t bytes, const hipStream_t* after) {
     int dev = -1;
+    hipEvent_t done = nullptr;
+    if (after && (hipEventCreateWithFlags(&done, hipEventDisableTiming) != hipSuccess ||
+                  hipEventRecord(done, *after) != hipSuccess)) {
+        (void)hipStreamSynchronize(*after);
+        if (done) (void)hipEventDestroy(done);
+        done = nullptr;
+    }
     if (hipGetDevice(&dev) == hipSuccess && dev == g->device && bytes <= KEPT_MAX) {
         std::lock_guard<std::mutex> lk(g->kept_mu);
         // a larger block takes the place of the smallest
@@ -570,24 +588,29 @@ void scratch_give(const pet_os_geom* g, void* p, size_t bytes) {
             if (g->kept[i].bytes < g->kept[least].bytes) least = i;
         }
         if (g->kept.size() < 2 && total <= KEPT_MAX) {
-            g->kept.push_back({p, bytes});
+            g->kept.push_back({p, bytes, done});
             return;
         }
         if (!g->kept.empty() && g->kept[least].bytes < bytes && total - g->kept[least].bytes <= KEPT_MAX) {
             std::swap(g->kept[least].p, p);
+            std::swap(g->kept[least].done, done);
             g->kept[least].bytes = bytes;
         }
+    }
+    if (done) {
+        (void)hipEventSynchronize(done);
+        (void)hipEventDestroy(done);
     }
     (void)hipFree(p);
 }
 
-int work_alloc(const pet_os_geom* g, bool need_nu, Work* w, bool sums, bool keep) {
+int work_alloc(const pet_os_geom* g, bool need_nu, Work* w, bool sums, bool keep, const hipStream_t* s) {
     *w = Work{};
     const WorkLayout L = work_layout(g, need_nu, sums);
     char* blk = nullptr;
     if (keep) {
         size_t got = 0;
-        blk = (char*)scratch_take(g, L.bytes, &got);
+        blk = (char*)scratch_take(g, L.bytes, &got, s);
         if (!blk) return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of scratch failed");
         work_carve(L, blk, w);
         w->bytes = got;
@@ -817,7 +840,7 @@ static int ensure_yr(pet_os_state* st, const float* y, const float* r, hipStream
         void* p = nullptr;
         st->yr_bytes = (size_t)g->n_bins * sizeof(float2);
         if (st->w.keeper) {
-            p = scratch_take(g, st->yr_bytes, &st->yr_bytes);
+            p = scratch_take(g, st->yr_bytes, &st->yr_bytes, &s);
             if (!p) (void)hipGetLastError();
         } else if (hipMalloc(&p, st->yr_bytes) != hipSuccess) {
             (void)hipGetLastError();
@@ -1085,7 +1108,7 @@ int pet_os_forward(const pet_os_geom* g, const float* f, int32_t subset, float* 
         // the PSF-blurred image, in scratch given back before returning
         hipStream_t s = (hipStream_t)stream;
         size_t got = 0;
-        float* tmp = (float*)scratch_take(g, sizeof(float) * (size_t)g->n_vox, &got);
+        float* tmp = (float*)scratch_take(g, sizeof(float) * (size_t)g->n_vox, &got, &s);
         if (!tmp) return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc failed");
         int rc = launch_blur(g, f, tmp, s);
         F.f = tmp;
@@ -1099,7 +1122,7 @@ int pet_os_forward(const pet_os_geom* g, const float* f, int32_t subset, float* 
     // given back before returning (this call waits for the stream)
     hipStream_t s = (hipStream_t)stream;
     Work w;
-    int rc = work_alloc(g, false, &w, false, true);
+    int rc = work_alloc(g, false, &w, false, true, &s);
     if (rc) return rc;
     rc = launch_prep3(g, f, w.fz, w.red[RED_SUMF], s);
     F.fz = w.fz;
@@ -1122,7 +1145,7 @@ int pet_os_back(const pet_os_geom* g, const float* w, int32_t subset, float* out
         // back-projection into scratch, then the (symmetric) PSF into out
         hipStream_t s = (hipStream_t)stream;
         size_t got = 0;
-        float* tmp = (float*)scratch_take(g, sizeof(float) * (size_t)g->n_vox, &got);
+        float* tmp = (float*)scratch_take(g, sizeof(float) * (size_t)g->n_vox, &got, &s);
         if (!tmp) return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc failed");
         B.out = tmp;
         int rc = launch_bp(g, B, s);
@@ -1131,7 +1154,28 @@ int pet_os_back(const pet_os_geom* g, const float* w, int32_t subset, float* out
         scratch_give(g, tmp, got);
         return rc;
     }
-    return launch_bp(g, B, (hipStream_t)stream);
+    hipStream_t s = (hipStream_t)stream;
+    // By quads, in the geometry's scratch (launch_back3q), but for the smallest
+    // calls, which three kernels cannot help: 2 angles of a 41x38x8 image with
+    // 15 planes of 61 bins 14.0 us by k_bp3 and 21.3 by quads, with 64 planes
+    // (7808 weights) 22.6 and 24.1; 6 angles at 100x97x24 with 70 planes of 144
+    // bins (60480) 30.1 and 27.3, at 53x50x46 (64464) 36.3 and 27.5.
+    if (g->d.dim == 3 && quad_ok(g) && (int64_t)B.n_al * g->n_planes * g->d.n_radial >= 32768) {
+        // A call under capture, whose launches would use the scratch again and
+        // again, and one that finds no memory keep the kernel that needs none.
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        size_t got = 0;
+        void* tmp = hipStreamIsCapturing(s, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone
+                        ? scratch_take(g, back3q_bytes(g, B.n_al), &got, &s)
+                        : nullptr;
+        if (tmp) {
+            const int rc = launch_back3q(g, B, tmp, s);
+            scratch_give(g, tmp, got, &s);
+            return rc;
+        }
+        (void)hipGetLastError();
+    }
+    return launch_bp(g, B, s);
 }
 
 int pet_os_attenuation_factors(const pet_os_geom* g, const float* mu, float* att, pet_os_stream stream) {
@@ -1154,9 +1198,9 @@ int pet_os_objective(const pet_os_geom* g, const pet_os_params* p, const float* 
     if (!g || !p || !f || !y || !r || !phi) return fail(PET_OS_ERR_INVALID_ARG, "NULL argument");
     if (!extra_of(g)) return fail(PET_OS_ERR_INVALID_ARG, "invalid geometry");
     Work w;
-    int rc = work_alloc(g, false, &w, false, true);
-    if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
+    int rc = work_alloc(g, false, &w, false, true, &s);
+    if (rc) return rc;
     double* dst = (double*)w.check_total;      // (two of its four words; no data check here)
     rc = queue_objective(g, p, &w, f, y, r, dst, s);
     double h[2] = {0, 0};
@@ -1212,7 +1256,7 @@ int pet_os_subset_gradient(const pet_os_geom* g, const pet_os_params* p, const f
     const int* angles = subset == 0 ? ex->all_angles : ex->subset_lists + (size_t)(subset - 1) * g->max_sub_angles;
     const int n_al = subset == 0 ? g->d.n_angles : ex->subset_count[subset - 1];
     Work w;
-    int rc = work_alloc(g, false, &w, false, true);
+    int rc = work_alloc(g, false, &w, false, true, &s);
     if (rc) return rc;
     // the ratio sinogram of every ray does not fit the subset-sized scratch
     float* wsino = w.w;
@@ -1221,7 +1265,7 @@ int pet_os_subset_gradient(const pet_os_geom* g, const pet_os_params* p, const f
     if (n_al > g->max_sub_angles) {
         // + 4 floats of padding for the 3D back-projector's 16-byte staging loads
         const size_t n = quad_ok(g) ? quad_floats(g, n_al) : (size_t)n_al * g->n_planes * g->d.n_radial + 4;
-        big = (float*)scratch_take(g, sizeof(float) * n, &big_bytes);
+        big = (float*)scratch_take(g, sizeof(float) * n, &big_bytes, &s);
         if (!big) {
             work_free(&w);
             return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of the ratio sinogram failed");

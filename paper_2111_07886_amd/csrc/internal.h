@@ -82,6 +82,7 @@ struct pet_os_geom {
     struct Kept {
         void* p;
         size_t bytes;
+        hipEvent_t done;        // null, or the end of the work that still uses it
     };
     mutable std::mutex kept_mu;
     mutable std::vector<Kept> kept;
@@ -108,18 +109,21 @@ struct Work {
     const pet_os_geom* keeper = nullptr;       // work_free leaves the scratch with this geometry
 };
 
-// Device memory that a whole call uses and has finished with (its stream
-// synchronized) when it gives it back: a geometry keeps up to two blocks of
-// KEPT_MAX bytes together for its next calls, on any thread or stream, and
-// frees them with itself.  A block taken holds whatever the last call left.
+// Device memory of a whole call: a geometry keeps up to two blocks of KEPT_MAX
+// bytes together for its next calls, on any thread or stream, and frees them
+// with itself.  A block taken holds whatever the last call left; work queued on
+// s comes after that call's (s null: the host has waited for it).  A call gives
+// a block back once its stream is synchronized, or with the work still queued
+// on `after`.
 constexpr size_t KEPT_MAX = (size_t)256 << 20;
-void* scratch_take(const pet_os_geom* g, size_t bytes, size_t* got);
-void scratch_give(const pet_os_geom* g, void* p, size_t bytes);
+void* scratch_take(const pet_os_geom* g, size_t bytes, size_t* got, const hipStream_t* s);
+void scratch_give(const pet_os_geom* g, void* p, size_t bytes, const hipStream_t* after = nullptr);
 void scratch_drop(const pet_os_geom* g);      // free what is kept
 
 // sums: with the partials of the sums over all bins (default U, nnz)
 // (keep: the scratch of a whole call, from and to the geometry's kept blocks)
-int work_alloc(const pet_os_geom* g, bool need_nu, Work* w, bool sums = false, bool keep = false);
+int work_alloc(const pet_os_geom* g, bool need_nu, Work* w, bool sums = false, bool keep = false,
+               const hipStream_t* s = nullptr);
 void work_free(Work* w);
 // bytes of one request's scratch, and the same scratch placed in caller
 // memory at base (cap bytes, 256-byte aligned): no allocation; the reduction
@@ -319,6 +323,9 @@ bool fp3q_ok(const pet_os_geom* g);         // whether the forward projector alo
 size_t quad_floats(const pet_os_geom* g, int n_al);
 int launch_fp3q(const pet_os_geom* g, const FPLaunch& L, hipStream_t s);
 int launch_bp3q(const pet_os_geom* g, const BPLaunch& L, hipStream_t s);
+// A_i^T w of weights in the natural layout by quads, in back3q_bytes of scratch
+size_t back3q_bytes(const pet_os_geom* g, int n_al);
+int launch_back3q(const pet_os_geom* g, const BPLaunch& L, void* scratch, hipStream_t s);
 int fp3q_grid(const pet_os_geom* g, int n_al);
 int bp3q_grid(const pet_os_geom* g);
 size_t bp3q_lds(const pet_os_geom* g);      // bytes of dynamic LDS

@@ -443,6 +443,7 @@ struct BP3QArgs {
     float* out;              // A_i^T w, z fastest
     int nr;                  // staged bin pairs per angle at most
     int buf;                 // float4 of one staging buffer
+    int add;                 // add to what out holds
     Pen3Args pen;            // the penalty blocks' arguments (gradR set) when n_pen > 0
     int n_pen;
 };
@@ -585,11 +586,13 @@ __device__ __forceinline__ void bq_pieces(const GeoK& g, BP3QShared& sh, int el,
 // angles take the half that holds the column's bin only (up: z, w)
 template <bool AXIS>
 __device__ __forceinline__ void bq_fma(float (&acc)[4], int l, bool up, const float4& x) {
-    const float lx = __int_as_float(AXIS && up ? 0 : l), lz = __int_as_float(AXIS && !up ? 0 : l);
-    acc[0] = fmaf(lx, x.x, acc[0]);
-    acc[1] = fmaf(lx, x.y, acc[1]);
-    acc[2] = fmaf(lz, x.z, acc[2]);
-    acc[3] = fmaf(lz, x.w, acc[3]);
+    const float len = __int_as_float(l);
+    const float s0 = fmaf(len, x.x, acc[0]), s1 = fmaf(len, x.y, acc[1]);
+    const float s2 = fmaf(len, x.z, acc[2]), s3 = fmaf(len, x.w, acc[3]);
+    acc[0] = AXIS && up ? acc[0] : s0;
+    acc[1] = AXIS && up ? acc[1] : s1;
+    acc[2] = AXIS && !up ? acc[2] : s2;
+    acc[3] = AXIS && !up ? acc[3] : s3;
 }
 
 // exchange the parts of c and c'
@@ -847,7 +850,7 @@ __device__ __forceinline__ void bp3q_body(const GeoK& g, const BP3QArgs& A, int 
             if (ix < g.nx && 2 * col <= ncol - 1 && kk < nz) {
                 float* o = A.out + (long long)col * nz + kk;
                 float* om = A.out + (long long)(ncol - 1 - col) * nz + kk;
-                if (c0 > 0) {
+                if (c0 > 0 || A.add) {
                     s += *o;
                     sm += *om;
                 }
@@ -987,6 +990,102 @@ int launch_bp3q(const pet_os_geom* G, const BPLaunch& L, hipStream_t s) {
     const dim3 blocks(bp_blocks + a.n_pen);
     if (G->d.nz > 32) petos_launch(k_bp3q<64>, blocks, dim3(NT), bp3q_lds(G), s, G->k, a, bp_blocks);
     else petos_launch(k_bp3q<32>, blocks, dim3(NT), bp3q_lds(G), s, G->k, a, bp_blocks);
+    PETOS_HIP(hipGetLastError());
+    return PET_OS_OK;
+}
+
+// ------------------------------------------------------------------ natural weights
+
+// Back-projection of weights in the natural layout: the listed angles' weights
+// are laid out as quads (k_pack3q), back-projected, and the image turned to its
+// natural layout (k_turn3).  Both copies are bound by memory and take a few
+// microseconds; k_bp3, which stages natural rows and takes every LOR by itself,
+// took 102 us for 10 of 175 angles of a 127x125x29 image (181 bins, ring
+// differences to 9), the three kernels 59 us (7 + 48 + 4).  Angles go in runs of at most
+// BACK_QUADS bytes of quads, a multiple of the 16 whose sums are added together.
+constexpr size_t BACK_QUADS = (size_t)64 << 20;
+
+static int back3q_run(const pet_os_geom* G) {
+    const size_t one = quad_floats(G, 1) * sizeof(float);
+    return (int)std::max<size_t>(1, std::min<size_t>(4096, BACK_QUADS / one / BQ_AMAX)) * BQ_AMAX;
+}
+
+static size_t back3q_image(const pet_os_geom* G) { return ((size_t)G->n_vox * sizeof(float) + 255) & ~(size_t)255; }
+
+size_t back3q_bytes(const pet_os_geom* G, int n_al) {
+    return back3q_image(G) + quad_floats(G, std::min(n_al, back3q_run(G))) * sizeof(float);
+}
+
+constexpr int PQ_P = 32;        // bin pairs per block
+
+__global__ __launch_bounds__(NT) void k_pack3q(GeoK g, const float* __restrict__ w, float4* __restrict__ wq,
+                                               const int* __restrict__ angles) {
+    float4* s_q = reinterpret_cast<float4*>(q_smem);        // [PQ_P][nz + 1]
+    const int D = g.max_rd, Nr = g.n_radial, nz = g.nz, NP = (Nr + 1) / 2;
+    const int p0 = blockIdx.x * PQ_P, d = blockIdx.y, al = blockIdx.z;
+    const long long ab = (long long)angles[al] * Nr, plane = (long long)g.n_angles * Nr;
+    const int pp = g.plane_base[D + d], pn = g.plane_base[D - d], c = threadIdx.x % PQ_P, p = p0 + c;
+    if (p < NP) {
+        const float* lo = w + ab + p;
+        const float* hi = w + ab + (Nr - 1 - p);
+        for (int k = threadIdx.x / PQ_P; k < nz; k += NT / PQ_P) {
+            float4 q = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            const int kr = nz - 1 - d - k;
+            if (kr >= 0) {
+                q.x = lo[(pp + k) * plane];
+                q.z = hi[(pp + kr) * plane];
+                if (d > 0) {
+                    q.y = lo[(pn + kr) * plane];
+                    q.w = hi[(pn + k) * plane];
+                }
+            }
+            s_q[c * (nz + 1) + k] = q;
+        }
+    }
+    __syncthreads();
+    float4* out = wq + (((long long)al * (D + 1) + d) * NP + p0) * nz;
+    const int n = min(PQ_P, NP - p0) * nz;
+    for (int e = threadIdx.x; e < n; e += NT) out[e] = s_q[e + e / nz];
+}
+
+// out (natural) from z (z fastest), tiles of 32 x 32
+__global__ __launch_bounds__(NT) void k_turn3(const float* __restrict__ z, float* __restrict__ out, int nx, int ny,
+                                              int nz) {
+    __shared__ float s_t[32][33];
+    const int x0 = blockIdx.x * 32, z0 = blockIdx.y * 32, y = blockIdx.z, l = threadIdx.x % 32;
+    for (int k = threadIdx.x / 32; k < 32; k += NT / 32)
+        if (x0 + k < nx && z0 + l < nz) s_t[k][l] = z[((long long)y * nx + x0 + k) * nz + z0 + l];
+    __syncthreads();
+    for (int k = threadIdx.x / 32; k < 32; k += NT / 32)
+        if (x0 + l < nx && z0 + k < nz) out[((long long)(z0 + k) * ny + y) * nx + x0 + l] = s_t[l][k];
+}
+
+int launch_back3q(const pet_os_geom* G, const BPLaunch& L, void* scratch, hipStream_t s) {
+    const auto& d = G->d;
+    float* img = reinterpret_cast<float*>(scratch);
+    float4* wq = reinterpret_cast<float4*>((char*)scratch + back3q_image(G));
+    const int run = back3q_run(G);
+    for (int a0 = 0; a0 < L.n_al; a0 += run) {
+        BP3QArgs a{};
+        a.wq = wq;
+        a.angles = L.angles + a0;
+        a.n_al = std::min(run, L.n_al - a0);
+        a.out = img;
+        a.nr = bq_rows(G);
+        a.buf = bq_buf(G);
+        a.add = a0 > 0;
+        // (a grid's z holds 65535 blocks, a run at most 65536 angles: by halves)
+        for (int h = 0; h < a.n_al; h += 32768) {
+            const int na = std::min(32768, a.n_al - h);
+            hipLaunchKernelGGL(k_pack3q, dim3((q_pairs(d.n_radial) + PQ_P - 1) / PQ_P, d.max_ring_diff + 1, na), dim3(NT),
+                               (size_t)PQ_P * (d.nz + 1) * sizeof(float4), s, G->k, L.w,
+                               wq + quad_floats(G, h) / 4, a.angles + h);
+        }
+        const int blocks = bp3q_grid(G);
+        if (d.nz > 32) petos_launch(k_bp3q<64>, dim3(blocks), dim3(NT), bp3q_lds(G), s, G->k, a, blocks);
+        else petos_launch(k_bp3q<32>, dim3(blocks), dim3(NT), bp3q_lds(G), s, G->k, a, blocks);
+    }
+    hipLaunchKernelGGL(k_turn3, dim3((d.nx + 31) / 32, (d.nz + 31) / 32, d.ny), dim3(NT), 0, s, img, L.out, d.nx, d.ny, d.nz);
     PETOS_HIP(hipGetLastError());
     return PET_OS_OK;
 }
