@@ -48,6 +48,13 @@ struct FPArgs {
 // sub-rays, accumulated over major cells [s0, s1] of the ray.  Each pixel the
 // strip of sub-rays can cross gets the same weight the back-projector gives
 // it, so the two are an adjoint pair.
+//
+// Bound by the instructions of the weights, one per pixel that the strip meets
+// (about 3.5 per major cell): the cells are the strip's own, the offset takes
+// one FP64 step per cell, and the weight has no branches.  256x256, 12 angles
+// of 367 bins, 32 sub-rays, with the pixel pass: 15.5 us with a cell of margin
+// on either side, the offset made anew and branches between the weight's
+// pieces, 11.6 us here (back-projection, same weights: 9.5 and 9.1).
 __device__ __forceinline__ float fp_subray_acc(const GeoK& g, const FPArgs& A, const AngleK& AK, int b, int s0,
                                                int s1) {
     const int row_major = AK.row_major;
@@ -77,17 +84,21 @@ __device__ __forceinline__ float fp_subray_acc(const GeoK& g, const FPArgs& A, c
     }
     const TxRay tx = tx_ray(g, AK, b);
     const double hsg = fabs(AK.icv) * g.sub_half;     // strip half-width in minor cells
+    const double dts = row_major ? g.vx * AK.c : g.vy * AK.s;
     for (int m = s0; m <= s1; ++m) {
         const double g0 = __fma_rn(tx.Q, (double)m, tx.P), g1 = g0 + tx.Q;
-        const int c0 = max((int)floor(fmin(g0, g1) - hsg) - 1, 0);
-        const int c1 = min((int)floor(fmax(g0, g1) + hsg) + 1, n_minor - 1);
+        // the cells that the strip meets (the FP32 weights of others, were they
+        // taken, could be positive by rounding, within 1e-4 of a cell)
+        const int c0 = max((int)floor(fmin(g0, g1) - hsg - 1e-4), 0);
+        const int c1 = min((int)floor(fmax(g0, g1) + hsg + 1e-4), n_minor - 1);
+        // the bin's offset from the pixel centres, linear in c
+        const double ts0 = pixel_ts(g, AK, row_major ? 0 : m, row_major ? m : 0, b);
         for (int c = c0; c <= c1; ++c) {
-            const int ix = row_major ? c : m, iy = row_major ? m : c;
-            const float w = subray_weight(g, AK, pixel_ts(g, AK, ix, iy, b));
-            if (w > 0.0f) {
-                if (A.mode == FP_COUNT) { acc += 1.0f; continue; }
-                acc = fmaf(w, img_at(A.f, m * sm + c * sx), acc);
-            }
+            // (loaded before its weight is known, so that it arrives meanwhile)
+            const float v = A.mode == FP_COUNT ? 0.0f : img_at(A.f, m * sm + c * sx);
+            const float w = subray_weight(g, AK, __fma_rn(-(double)c, dts, ts0));
+            if (A.mode == FP_COUNT) acc += w > 0.0f ? 1.0f : 0.0f;
+            else acc = w > 0.0f ? fmaf(w, v, acc) : acc;
         }
     }
     return acc;

@@ -181,29 +181,22 @@ __device__ __forceinline__ double pixel_ts(const GeoK& g, const AngleK& A, int i
 __device__ __forceinline__ float subray_weight(const GeoK& g, const AngleK& A, double ts) {
     const float a = (float)ts + g.sub_x0;
     const float h = g.sub_h, ih = g.inv_sub_h;
-    const int last = g.n_sub - 1;
+    const float last = (float)(g.n_sub - 1);
     const float eo = (float)A.e_out, ei = (float)A.e_in, ide = (float)A.inv_de;
-    const int b0 = (int)floorf((-eo - a) * ih);
-    const int b1 = (int)floorf((-ei - a) * ih);
-    const int b2 = (int)floorf((ei - a) * ih);
-    const int b3 = (int)floorf((eo - a) * ih);
-    float s = 0.0f;
-    int k0 = max(b0 + 1, 0), k1 = min(b1, last);
-    if (k1 >= k0) {                          // rising edge: (e_out + t) / de
-        const float n = (float)(k1 - k0 + 1);
-        const float c0 = eo + fmaf((float)k0, h, a);      // value at the first sample, times de
-        s += ide * (n * c0 + h * 0.5f * n * (n - 1.0f));
-    }
-    k0 = max(b1 + 1, 0);
-    k1 = min(b2, last);
-    if (k1 >= k0) s += (float)(k1 - k0 + 1); // plateau
-    k0 = max(b2 + 1, 0);
-    k1 = min(b3, last);
-    if (k1 >= k0) {                          // falling edge: (e_out - t) / de
-        const float n = (float)(k1 - k0 + 1);
-        const float c0 = eo - fmaf((float)k0, h, a);
-        s += ide * (n * c0 - h * 0.5f * n * (n - 1.0f));
-    }
+    // (whole numbers held as floats; an empty piece adds 0)
+    const float b0 = floorf((-eo - a) * ih);
+    const float b1 = floorf((-ei - a) * ih);
+    const float b2 = floorf((ei - a) * ih);
+    const float b3 = floorf((eo - a) * ih);
+    float k0 = fmaxf(b0 + 1.0f, 0.0f), n = fmaxf(fminf(b1, last) - k0 + 1.0f, 0.0f);
+    // rising edge: (e_out + t) / de, from its value at the first sample, times de
+    float s = ide * (n * (eo + fmaf(k0, h, a)) + h * 0.5f * n * (n - 1.0f));
+    k0 = fmaxf(b1 + 1.0f, 0.0f);
+    s += fmaxf(fminf(b2, last) - k0 + 1.0f, 0.0f);      // plateau
+    // falling edge: (e_out - t) / de
+    k0 = fmaxf(b2 + 1.0f, 0.0f);
+    n = fmaxf(fminf(b3, last) - k0 + 1.0f, 0.0f);
+    s += ide * (n * (eo - fmaf(k0, h, a)) - h * 0.5f * n * (n - 1.0f));
     return (float)A.Lmax * s * g.inv_nsub;
 }
 
