@@ -221,7 +221,6 @@ struct BPLaunch {
     // constants, part_f and red_mu); the update then adds it to b
     float* gradR = nullptr;
     int quad = 0;                      // 3D: w holds quads of mirror rays; the back-projection is left z-fastest
-    const float* bz = nullptr;         // launch_pen3: a z-fastest back-projection to add to, instead of out
 };
 int launch_bp(const pet_os_geom* g, const BPLaunch& L, hipStream_t s);
 // 2D full model: out = B in (PSF), and the image-space part of a subiteration
@@ -326,6 +325,8 @@ int launch_bp3q(const pet_os_geom* g, const BPLaunch& L, hipStream_t s);
 // A_i^T w of weights in the natural layout by quads, in back3q_bytes of scratch
 size_t back3q_bytes(const pet_os_geom* g, int n_al);
 int launch_back3q(const pet_os_geom* g, const BPLaunch& L, void* scratch, hipStream_t s);
+// the z-fastest image z in the natural layout: out, or beta out + z
+int launch_turn3(const pet_os_geom* g, const float* z, float* out, const float* beta, hipStream_t s);
 int fp3q_grid(const pet_os_geom* g, int n_al);
 int bp3q_grid(const pet_os_geom* g);
 size_t bp3q_lds(const pet_os_geom* g);      // bytes of dynamic LDS

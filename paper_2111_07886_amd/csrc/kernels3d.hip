@@ -732,7 +732,6 @@ int launch_pen3(const pet_os_geom* G, const BPLaunch& L, hipStream_t s) {
     Pen3Args a;
     fill_pen3(L, a);
     a.G = L.out;
-    a.bz = L.bz;
     const int grid = pen3_grid(G);
     if (L.want_mu && grid > L.red_mu.cap) return fail(PET_OS_ERR_DEVICE, "mu partials too small");
     petos_launch(k_pen3, dim3(grid), dim3(NT), 0, s, G->k, a);

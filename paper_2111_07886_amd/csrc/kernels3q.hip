@@ -1048,16 +1048,27 @@ __global__ __launch_bounds__(NT) void k_pack3q(GeoK g, const float* __restrict__
     for (int e = threadIdx.x; e < n; e += NT) out[e] = s_q[e + e / nz];
 }
 
-// out (natural) from z (z fastest), tiles of 32 x 32
+// out (natural) from z (z fastest), or z + beta out, tiles of 32 x 32
 __global__ __launch_bounds__(NT) void k_turn3(const float* __restrict__ z, float* __restrict__ out, int nx, int ny,
-                                              int nz) {
+                                              int nz, int add, float beta) {
     __shared__ float s_t[32][33];
     const int x0 = blockIdx.x * 32, z0 = blockIdx.y * 32, y = blockIdx.z, l = threadIdx.x % 32;
     for (int k = threadIdx.x / 32; k < 32; k += NT / 32)
         if (x0 + k < nx && z0 + l < nz) s_t[k][l] = z[((long long)y * nx + x0 + k) * nz + z0 + l];
     __syncthreads();
     for (int k = threadIdx.x / 32; k < 32; k += NT / 32)
-        if (x0 + l < nx && z0 + k < nz) out[((long long)(z0 + k) * ny + y) * nx + x0 + l] = s_t[l][k];
+        if (x0 + l < nx && z0 + k < nz) {
+            float* o = out + ((long long)(z0 + k) * ny + y) * nx + x0 + l;
+            *o = add ? fmaf(beta, *o, s_t[l][k]) : s_t[l][k];
+        }
+}
+
+int launch_turn3(const pet_os_geom* G, const float* z, float* out, const float* beta, hipStream_t s) {
+    const auto& d = G->d;
+    hipLaunchKernelGGL(k_turn3, dim3((d.nx + 31) / 32, (d.nz + 31) / 32, d.ny), dim3(NT), 0, s, z, out, d.nx, d.ny, d.nz,
+                       beta != nullptr, beta != nullptr ? *beta : 0.0f);
+    PETOS_HIP(hipGetLastError());
+    return PET_OS_OK;
 }
 
 int launch_back3q(const pet_os_geom* G, const BPLaunch& L, void* scratch, hipStream_t s) {
@@ -1085,9 +1096,7 @@ int launch_back3q(const pet_os_geom* G, const BPLaunch& L, void* scratch, hipStr
         if (d.nz > 32) petos_launch(k_bp3q<64>, dim3(blocks), dim3(NT), bp3q_lds(G), s, G->k, a, blocks);
         else petos_launch(k_bp3q<32>, dim3(blocks), dim3(NT), bp3q_lds(G), s, G->k, a, blocks);
     }
-    hipLaunchKernelGGL(k_turn3, dim3((d.nx + 31) / 32, (d.nz + 31) / 32, d.ny), dim3(NT), 0, s, img, L.out, d.nx, d.ny, d.nz);
-    PETOS_HIP(hipGetLastError());
-    return PET_OS_OK;
+    return launch_turn3(G, img, L.out, nullptr, s);
 }
 
 // ------------------------------------------------------------------ batched (persistent) kernels

@@ -21,7 +21,6 @@ struct Pen3Args {
     const float* f;
     float* G;                // in: b, out: G (gradR null)
     int g_zfast;             // G is z-fastest
-    const float* bz;         // non-null: b is here, z-fastest, and G (natural) only written
     float* gradR;            // non-null: grad R(f) goes here and G is left alone
     float* mu;
     int want_mu;
@@ -97,7 +96,6 @@ __device__ inline void pen3_body(const GeoK& g, const Pen3Args& A, int vblock, f
             const float gmag = sqrtf(gx * gx + gy * gy + gz * gz);
             const long long j = ((long long)iz * g.ny + iy) * g.nx + ix;
             if (A.gradR != nullptr) A.gradR[j] = gradR;
-            else if (A.bz != nullptr) A.G[j] = fmaf(A.beta_over_M, gradR, A.bz[colz + iz]);
             else {
                 float* G = A.G + (A.g_zfast ? colz + iz : j);
                 *G = fmaf(A.beta_over_M, gradR, *G);
