@@ -11,7 +11,7 @@ subiteration needs, is timed on its own (config.objective_ms).  Inputs are
 resident in HBM before timing.
 
 The same run measures the metric's batched and served half: 96 uneven 2D
-reconstructions advanced by one captured launch per batched subiteration
+reconstructions advanced by one launch sequence per batched subiteration
 against the same requests one at a time ("batched"), and a Poisson arrival
 trace served by the continuous-batching server against the plain path
 ("served", recons/s with p50/p99 latency).  --workload c2 / c1 / c2full give
@@ -419,7 +419,7 @@ def calibrate_copy(dev):
 
 def bench_batched(args, cpu=True):
     """96 uneven 2D reconstructions (10 iterations each): one batch, one
-    captured step per subiteration, vs the same requests one at a time."""
+    step per subiteration, vs the same requests one at a time."""
     import numpy as np
     import torch
 

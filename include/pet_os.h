@@ -317,8 +317,7 @@ int pet_os_state_import(pet_os_state* state, const void* buf, size_t len);
  * Batched execution: many independent reconstructions of different sizes
  * advanced together.  Every step advances each active request by one
  * subiteration (Table I) with one persistent launch per kernel, over a
- * device-resident work list of (request, block) items; the launch sequence
- * is captured once in a hipGraph and replayed.  A request computes exactly
+ * device-resident work list of (request, block) items.  A request computes exactly
  * what pet_os_reconstruct computes for it alone (same kernels, same
  * reductions); the FP64 scalar schedule of every subiteration is evaluated on
  * the host when the request is added.

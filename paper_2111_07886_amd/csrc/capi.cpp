@@ -827,7 +827,7 @@ static int prof_end(hipEvent_t end, hipStream_t s) {
     return PET_OS_OK;
 }
 
-// 3D: the bin-major copy of (y, r) that the staged forward projector reads
+// 3D: the bin-major copy of (y, r) that the quad forward projector reads
 // (its y and r loads are then coalesced), made when the state first sees the
 // pair of buffers, as the data check is.  A state that may not allocate (the
 // static-scratch entry point), or whose allocation fails, reads y and r in

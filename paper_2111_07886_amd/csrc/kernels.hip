@@ -1558,7 +1558,7 @@ int launch_rdp_value(const pet_os_geom* G, const float* f, float gamma_R, float 
 // ------------------------------------------------------------------ batched (persistent) kernels
 // Every block walks a device-resident work list of (slot, block) items with a
 // grid stride; the lists, their lengths and the slot table live in device
-// memory, so one captured graph stays valid while requests come and go.
+// memory.
 
 // (subiteration J of the slot: a queued step's kernels add its number to the
 // counter, which moves on when all steps of a call are queued)

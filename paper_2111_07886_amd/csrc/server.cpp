@@ -71,7 +71,8 @@ std::string desc_key(const pet_os_geom_desc& d) {
     return buf;
 }
 
-// bytes of one request's scratch (mirrors work_alloc) and schedule
+// bytes of one request's scratch and schedule, as the budget counts them: the
+// subset sinogram bin by bin (3D quads may take up to 2.2 times that)
 size_t request_bytes(const pet_os_geom_desc& d, int n_planes, int max_sub, int n_iter, bool nu) {
     const size_t nv = (size_t)d.nx * d.ny * (d.dim == 3 ? d.nz : 1);
     const size_t nb = (size_t)n_planes * d.n_angles * d.n_radial;
