@@ -46,7 +46,7 @@
  *     one device pass over y, r and f followed by a synchronisation of
  *     `stream`; a state makes it when it first sees a (f, y, r) triple of
  *     buffers, not again while the same buffers come back.
- *   - A 3D state (up to 64 rings) also copies y and r
+ *   - A 3D state (up to 64 rings and 15 ring differences) also copies y and r
  *     into a bin-major layout of its own (8 bytes per bin, allocated at the
  *     first subiteration) when it first sees a (y, r) pair of buffers, and
  *     reads the copy while the same pair comes back: new contents in the

@@ -939,7 +939,9 @@ int bp3_shape_single(const pet_os_geom* G, int zb, int dpg_req, int& nb, int& rw
     return PET_OS_OK;
 }
 
-bool fp3_reads_yr(const pet_os_geom* G) { return fp3q_ok(G); }
+// (only up to 15 ring differences: a state keeps its copy while the same
+// buffers come back, and with more it reads whatever they hold)
+bool fp3_reads_yr(const pet_os_geom* G) { return fp3q_ok(G) && G->d.max_ring_diff <= 15; }
 
 // yr[(a * n_radial + b) * n_planes + plane] = (y, r)[(plane * n_angles + a) *
 // n_radial + b]: a transpose of [plane][angle-bin] by 64 x 64 tiles through
