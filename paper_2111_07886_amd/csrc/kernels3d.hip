@@ -977,8 +977,10 @@ int launch_yr3(const pet_os_geom* G, const float* y, const float* r, float2* yr,
 int launch_fp3(const pet_os_geom* G, const FPLaunch& L, hipStream_t s) {
     if (L.n_al == 0) return PET_OS_OK;
     if (L.mode != FP_COUNT && L.fz == nullptr) return fail(PET_OS_ERR_DEVICE, "3D forward projection without z copy");
-    // (FP_COMPACT is a 2D mode of the batch)
-    if (fp3q_ok(G) && L.mode != FP_COMPACT) return launch_fp3q(G, L, s);
+    // (FP_COMPACT is a 2D mode of the batch; a count is each ray's own: where a
+    // ray meets two cell edges at once, rounding tells whether a piece of no
+    // length is there, and not alike for its mirror rays)
+    if (fp3q_ok(G) && L.mode != FP_COMPACT && L.mode != FP_COUNT) return launch_fp3q(G, L, s);
     FP3Args a;
     a.fz = L.fz;
     a.y = L.y;

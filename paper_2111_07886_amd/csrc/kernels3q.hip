@@ -225,7 +225,6 @@ __device__ __forceinline__ void fp3q_body(const GeoK& g, const FP3QArgs& A, int 
     auto column = [&](int mb, int s, int j) {
         const int jj = max(j, 0), mm = min(mb + s, m1);
         const int c = jj * nz, c2 = (axis ? (n_major - 1 - mm) * ms + cm * cs : ncol - 1 - jj) * nz;
-        if (A.mode == FP_COUNT) return make_float4(1.0f, 1.0f, 1.0f, 1.0f);
         const float* fc = A.fz + c;
         const float* f2 = A.fz + c2;
         return make_float4(img_at(fc, kb), img_at(fc, kt), img_at(f2, kt), img_at(f2, kb));
@@ -279,8 +278,7 @@ __device__ __forceinline__ void fp3q_body(const GeoK& g, const FP3QArgs& A, int 
         const bool v2 = c.xc && zc && fr2 > 0.0f && in1 && o1 >= 0 && o1 <= dd;
         const int e0 = c.slot * nz, e1 = e0 + nz;
         const int off[3] = {e0 + o0, (x_first ? e1 : e0) + po1, e1 + o1};
-        const bool count = A.mode == FP_COUNT;      // pieces of length 1 in an image of ones
-        const float len[3] = {count ? 1.0f : Lkf * fr0, count ? 1.0f : Lkf * fr1, count ? 1.0f : Lkf * fr2};
+        const float len[3] = {Lkf * fr0, Lkf * fr1, Lkf * fr2};
         const int present = (c.live && dd <= D) ? (v0 ? 1 : 0) | (v1 ? 2 : 0) | (v2 ? 4 : 0) : 0;
         // (3) the two lists of the wave, in cell order, filled up to eight by
         // pieces of no length
@@ -380,16 +378,12 @@ __device__ __forceinline__ void fp3q_body(const GeoK& g, const FP3QArgs& A, int 
         const int bin[4] = {p, p, pm, pm};
         // rays counted once: d = 0 has no negative side, the centre bin no mirror
         const bool twin[4] = {false, od == 0, p == pm, od == 0 || p == pm};
-        if (A.mode == FP_RATIO || A.mode == FP_EM || A.mode == FP_COUNT) {
+        if (A.mode == FP_RATIO || A.mode == FP_EM) {
             float o4[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 o4[q] = 0.0f;
                 if (!ok || (od == 0 && (q & 1))) continue;
-                if (A.mode == FP_COUNT) {
-                    o4[q] = mine[q];
-                    continue;
-                }
                 float yv, rv;
                 if (A.yr != nullptr) {
                     const float2 d2 = A.yr[((long long)a * Nr + bin[q]) * g.n_planes + plane[q]];
