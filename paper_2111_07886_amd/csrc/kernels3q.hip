@@ -76,7 +76,7 @@ struct FP3QArgs {
 
 constexpr int FQ_CELLS = 32;                  // major cells per stretch
 constexpr int FQ_COLS = 2 * FQ_CELLS + 1;     // staged columns: a cell adds one, a crossing one
-constexpr int FQ_LIST = 3 * FQ_CELLS;         // pieces of a stretch, filled up to a multiple of eight
+constexpr int FQ_LIST = 3 * FQ_CELLS;         // pieces of a stretch, filled up to eights by pieces of no length
 constexpr int FQ_W = 8;                       // waves per block
 
 // float4 of the staged columns; the parts' sums take their place at the end.
@@ -192,6 +192,12 @@ __device__ __forceinline__ void fp3q_body(const GeoK& g, const FP3QArgs& A, int 
         for (int q = 0; q < 4; ++q) acc[u][q] = 0.0f;
     // slots no cell names keep a column that can be staged
     for (int e = lane; e < FQ_COLS; e += 64) s_tab[e] = -1;
+    // A piece of no length reads the wave's own lists, 16 bytes per lane, which
+    // never hold anything but finite numbers (offsets, as denormals, and
+    // lengths): a column of the image could hold an infinity.
+    const int pad = (int)(reinterpret_cast<char*>(s_pc) - smem);
+    static_assert(2 * FQ_LIST * sizeof(int2) >= 64 * sizeof(float4), "the lists hold a quad per lane");
+    for (int e = lane; e < 2 * FQ_LIST; e += 64) s_pc[e] = make_int2(0, 0);
 
     // (1) the transaxial part of a stretch, as in the per-wave projector
     // (lanes past the last cell repeat it and keep no piece), and its columns'
@@ -280,7 +286,7 @@ __device__ __forceinline__ void fp3q_body(const GeoK& g, const FP3QArgs& A, int 
         const int off[3] = {e0 + o0, (x_first ? e1 : e0) + po1, e1 + o1};
         const float len[3] = {Lkf * fr0, Lkf * fr1, Lkf * fr2};
         const int present = (c.live && dd <= D) ? (v0 ? 1 : 0) | (v1 ? 2 : 0) | (v2 ? 4 : 0) : 0;
-        // (3) the two lists of the wave, in cell order, filled up to eight by
+        // (3) the two lists of the wave, in cell order, filled up to eights by
         // pieces of no length
         const int cnt = __popc(present);
         const unsigned long long b0 = __ballot(cnt & 1), b1 = __ballot(cnt & 2);
@@ -296,8 +302,7 @@ __device__ __forceinline__ void fp3q_body(const GeoK& g, const FP3QArgs& A, int 
                 ++pos;
             }
         }
-        q_wave_sync();
-        if (tot > 0 && i < ((8 - tot) & 7)) s_pc[t * FQ_LIST + tot + i] = make_int2(s_pc[t * FQ_LIST + tot - 1].x, 0);
+        if (i < ((8 - tot) & 7)) s_pc[t * FQ_LIST + tot + i] = make_int2(pad, 0);
         __syncthreads();    // the previous stretch's columns are read no more
         // (4) the columns into LDS, and the next stretch's on their way
 #pragma unroll
