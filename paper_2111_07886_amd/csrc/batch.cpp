@@ -142,7 +142,8 @@ int rebuild_lists(pet_os_batch* B) {
         if (!S.used) continue;
         const bool d3 = S.g->d.dim == 3;
         // 2D: forward blocks, then the pixel-pass blocks (snapshot, mu)
-        const bool fq = d3 && fp3q_ok(S.g), quad = d3 && quad_ok(S.g);
+        // (the forward projector that gives the bits of a request alone)
+        const bool quad = d3 && quad_ok(S.g), fq = d3 && fp3q_ok(S.g) && (quad || !fp3s_better(S.g));
         const int wide = S.g->d.nz > 32 ? 1 : 0;
         const int nfp = fq ? fp3q_grid(S.g, S.g->max_sub_angles)
                         : d3 ? fp3_grid(S.g, S.g->max_sub_angles)

@@ -319,6 +319,7 @@ int launch_pen3(const pet_os_geom* g, const BPLaunch& L, hipStream_t s);
 // floats of the subset sinogram of n_al angles in that layout
 bool quad_ok(const pet_os_geom* g);
 bool fp3q_ok(const pet_os_geom* g);         // whether the forward projector alone takes them
+bool fp3s_better(const pet_os_geom* g);     // whether the one that stages single columns is faster (kernels3d.hip)
 size_t quad_floats(const pet_os_geom* g, int n_al);
 int launch_fp3q(const pet_os_geom* g, const FPLaunch& L, hipStream_t s);
 int launch_bp3q(const pet_os_geom* g, const BPLaunch& L, hipStream_t s);

@@ -114,7 +114,7 @@ __device__ __forceinline__ float fp_subray_acc(const GeoK& g, const FPArgs& A, c
 // every SEG, and the batched kernels' choice of it, give the same bits.
 template <int DIM, int SEG, bool SUB = false>
 __device__ void fp_body(const GeoK& g, const FPArgs& A, long long vblock) {
-    static_assert(DIM == 2, "the 3D forward projectors are k_fp3q and k_fp3_wave");
+    static_assert(DIM == 2, "the 3D forward projectors are k_fp3q, k_fp3 and k_fp3_wave");
     static_assert(SEG == 1 || (64 % SEG == 0), "segments of a ray stay in one wave");
     constexpr int RPB = NT / SEG;
     __shared__ double s_red[NT / 64];

@@ -14,9 +14,12 @@
 //            pieces of that stretch in LDS; then every lane adds length *
 //            f[cell, slice r1 + o] for every piece (64 consecutive slices of
 //            the z-fastest copy).  The Poisson ratio (or the FP64
-//            log-likelihood term) is the epilogue, as in 2D.  It takes what
-//            the projector on quads of mirror rays (kernels3q.hip) does not:
-//            more than 64 rings, and the count of nonzeros.
+//            log-likelihood term) is the epilogue, as in 2D.  It takes the
+//            volumes that the projector on quads of mirror rays
+//            (kernels3q.hip) does not, of more than 64 rings.
+//   k_fp3    the same pieces, the columns staged in LDS for all ring
+//            differences of an (angle, bin): geometries with few ring
+//            differences, and the count of nonzeros.
 //   k_bp3    (natural-layout and unit weights, and geometries without quads)
 //            one block per 8x8 column tile and z-range.  A lane owns one
 //            column; wave v takes ring differences v, v+4, ... of each
@@ -57,6 +60,7 @@ struct FP3Args {
     const float* fz;        // image with z fastest: fz[(iy * nx + ix) * nz + iz]
     const float* y;
     const float* r;
+    const float2* yr;       // null, or (y, r) bin-major (k_fp3 reads it instead)
     float* out;
     const int* angles;
     int n_al;
@@ -211,12 +215,22 @@ __device__ void fp3_body(const GeoK& g, const FP3Args& A, long long vblock) {
                     acc += (float)total;    // pieces of the LOR
                 } else {
                     // eight pieces' image loads in flight per lane (sixteen cost
-                    // more in occupancy than they hide in latency)
-#pragma unroll 8
-                    for (int j = 0; j < total; ++j) {
-                        const Piece p = s_pc[wave][j];
-                        acc = fmaf(p.len, img_at(A.fz, p.off + r1), acc);
+                    // more in occupancy than they hide in latency); the stretch
+                    // summed apart, in four sums, which keeps the FP32 chains short
+                    float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+                    int j = 0;
+                    for (; j + 8 <= total; j += 8) {
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) {
+                            const Piece p = s_pc[wave][j + u];
+                            sum[u & 3] = fmaf(p.len, img_at(A.fz, p.off + r1), sum[u & 3]);
+                        }
                     }
+                    for (; j < total; ++j) {
+                        const Piece p = s_pc[wave][j];
+                        sum[0] = fmaf(p.len, img_at(A.fz, p.off + r1), sum[0]);
+                    }
+                    acc += (sum[0] + sum[1]) + (sum[2] + sum[3]);
                 }
             }
             wave_lds_sync();
@@ -258,6 +272,264 @@ __global__ __launch_bounds__(NT) void k_fp3_wave(GeoK g, FP3Args A, long long n_
     const long long vb = xcd_block(blockIdx.x, n_blocks);
     if (vb >= n_blocks) return;
     fp3_body(g, A, vb);
+}
+
+// Forward projection with the ray's image columns staged in LDS, for at most
+// 64 slices and 15 ring differences: what has few ring differences
+// (fp3s_better; weights only where they don't go to a back-projector on quads),
+// and every count of nonzeros.  One block takes one
+// (angle, bin); its eight waves take the ring differences w, w + 8, w + 16,
+// w + 24.  The transaxial path of the ray is the same for every ring
+// difference, so for each stretch of 64 major cells the columns it can enter
+// (minor cells c0 and c0 + qstep of each major cell, all nz slices) are copied
+// to LDS once, and every ring difference reads its pieces there instead of
+// from device memory, where each piece cost a 256-byte wave load through the
+// vector L1.  Pieces, their order and their arithmetic are those of fp3_body, so
+// the results agree bit for bit.
+constexpr int FPS_NT = 512;
+constexpr int FPS_W = FPS_NT / 64;      // waves per block
+constexpr int FPS_DPW = 4;              // ring differences per wave at most
+constexpr int FPS_ZS = 64;              // floats per staged column (nz <= 64)
+constexpr int FPS_SLOTS = 128;          // staged columns of a stretch: slot 2k (c0) and 2k + 1 (c0 + qstep) of cell mb + k
+
+static bool fp3s_ok(const pet_os_geom* G) {
+    return G->d.nz <= FPS_ZS && 2 * G->d.max_ring_diff + 1 <= FPS_W * FPS_DPW;
+}
+
+// Copy a stretch's columns into s_col: slot 2k holds minor cell c0 of major
+// cell mb + k, slot 2k + 1 its neighbour c0 + qstep, all nz slices; columns
+// outside the image or past m1 stay unwritten (no piece refers to them).
+// With nz a multiple of 4 (column starts 16-byte aligned) a wave instruction
+// copies four columns, sixteen lanes of 16 bytes each; else one column, a
+// slice per lane.  Returns without waiting.
+__device__ __forceinline__ void fp3s_stage(const float* fz, float* s_col, const TxRay& tx, int mb, int m1, int n_minor,
+                                           int qstep, int ms, int cs, int nz, int wave, int lane) {
+    if ((nz & 3) == 0) {
+        const int sub = lane >> 4, q = (lane & 15) * 4;
+        for (int s0 = wave * 4; s0 < FPS_SLOTS; s0 += FPS_W * 4) {
+            const int slot = s0 + sub, m = mb + (slot >> 1);
+            bool ok = m <= m1 && q < nz;
+            int src = 0;
+            if (ok) {
+                const int c = (int)floor(__fma_rn(tx.Q, (double)m, tx.P)) + ((slot & 1) ? qstep : 0);
+                ok = (unsigned)c < (unsigned)n_minor;
+                src = __mul24(m, ms) + __mul24(c, cs) + q;
+            }
+            if (ok)
+                __builtin_amdgcn_global_load_lds(fz + src, (__attribute__((address_space(3))) void*)(s_col + s0 * FPS_ZS),
+                                                 16, 0, 0);
+        }
+    } else {
+        for (int slot = wave; slot < FPS_SLOTS; slot += FPS_W) {
+            const int m = mb + (slot >> 1);
+            bool ok = m <= m1 && lane < nz;
+            int src = 0;
+            if (ok) {
+                const int c = (int)floor(__fma_rn(tx.Q, (double)m, tx.P)) + ((slot & 1) ? qstep : 0);
+                ok = (unsigned)c < (unsigned)n_minor;
+                src = __mul24(m, ms) + __mul24(c, cs) + lane;
+            }
+            if (ok)
+                __builtin_amdgcn_global_load_lds(fz + src, (__attribute__((address_space(3))) void*)(s_col + slot * FPS_ZS),
+                                                 4, 0, 0);
+        }
+    }
+}
+
+__device__ void fp3s_body(const GeoK& g, const FP3Args& A, long long vblock) {
+    __shared__ __attribute__((aligned(16))) float s_col[FPS_SLOTS * FPS_ZS];
+    // the pieces as two arrays: length, and the byte offset (off + 16) * 4 of
+    // slice o of the staged column, which fits 16 bits (o >= -15 here), so
+    // that the broadcast reads of a batch of pieces move 6 bytes a piece
+    __shared__ __attribute__((aligned(16))) unsigned short s_po[FPS_W][FP3_CAP];
+    __shared__ __attribute__((aligned(16))) float s_pl[FPS_W][FP3_CAP];
+    __shared__ double s_red[FPS_W];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int D = g.max_rd, ND = 2 * D + 1, Nr = g.n_radial, R = g.n_rings, nz = g.nz;
+    const int b = (int)(vblock % Nr), al = (int)(vblock / Nr);
+    const bool counting = A.mode == FP_COUNT;
+    const int a = A.angles[al];
+    const AngleK& AK = g.ang[a];
+    // the ray's FP64 constants live in LDS (read where used) rather than in
+    // registers across the loops
+    __shared__ double s_ray[5];    // P, L, tau0, tauQ, inv_tauQ
+    const TxRay tx0 = tx_ray(g, AK, b);
+    const ZBin zb0 = z_bin(g, AK, b);
+    if (threadIdx.x == 0) {
+        s_ray[0] = tx0.P;
+        s_ray[1] = tx0.L;
+        s_ray[2] = zb0.tau0;
+        s_ray[3] = zb0.tauQ;
+        s_ray[4] = zb0.inv_tauQ;
+    }
+    TxRay tx = tx0;
+    const int n_major = tx.row_major ? g.ny : g.nx;
+    const int n_minor = tx.row_major ? g.nx : g.ny;
+    int m0, m1;
+    major_range(tx, n_major, n_minor, m0, m1);
+    const int qstep = (tx.Q >= 0.0) ? 1 : -1;
+    const float invQf = (float)tx.invQ;
+    // offset of voxel (minor cell c, major cell m, slice o) in the z-fastest
+    // copy: m ms + c cs + o (24-bit products, as in fp3_body)
+    const int cs = tx.row_major ? nz : g.nx * nz;
+    const int ms = tx.row_major ? g.nx * nz : nz;
+
+    float acc[FPS_DPW];
+#pragma unroll
+    for (int j = 0; j < FPS_DPW; ++j) acc[j] = 0.0f;
+
+    for (int mb = m0; mb <= m1; mb += 64) {
+        // (1) stage the stretch's columns (counting reads no image, and is
+        // given none)
+        __syncthreads();    // the previous stretch's columns are read no more (and s_ray is written)
+        tx.P = s_ray[0];
+        if (!counting) fp3s_stage(A.fz, s_col, tx, mb, m1, n_minor, qstep, ms, cs, nz, wave, lane);
+        __builtin_amdgcn_s_waitcnt(0);      // this wave's copies have landed
+        __syncthreads();                    // and every other wave's
+
+        // (2) the transaxial part of the lane's major cell, shared by the
+        // wave's ring differences (lanes past the last cell repeat it and
+        // keep no piece)
+        const int mraw = mb + lane;
+        const int m = min(mraw, m1);
+        const double gm = __fma_rn(tx.Q, (double)m, tx.P);
+        const double cf = floor(gm);
+        const int c0 = (int)cf, c1 = c0 + qstep;
+        const double ce = (tx.Q >= 0.0) ? cf + 1.0 : cf;
+        const double ge = gm + tx.Q;
+        const bool xc = (tx.Q >= 0.0) ? (ge > ce) : (ge < ce);
+        const float tX = xc ? (float)(ce - gm) * invQf : 1.0f;
+        const bool in0 = (unsigned)c0 < (unsigned)n_minor, in1 = (unsigned)c1 < (unsigned)n_minor;
+        const int sl0 = 2 * (m - mb) * FPS_ZS, sl1 = sl0 + FPS_ZS;    // LDS offsets of the two columns
+
+#pragma unroll
+        for (int j = 0; j < FPS_DPW; ++j) {
+            const int di = wave + FPS_W * j;
+            if (di >= ND) break;
+            const int d = di - D;
+            // (3) the axial part and the pieces, as in fp3_body
+            const double zeta0 = __fma_rn((double)d, s_ray[2], 0.5);
+            const double Qz = (double)d * s_ray[3];
+            const double invQz = (d == 0) ? 0.0 : g.inv_d[di] * s_ray[4];
+            const float Lkf = (float)(s_ray[1] * g.kappa[(long long)b * ND + di]), invQzf = (float)invQz;
+            const int zstep = (Qz >= 0.0) ? 1 : -1;
+            const int olo = min(0, d), ohi = max(0, d);
+            const double zm = __fma_rn(Qz, (double)m, zeta0);
+            const double of = floor(zm);
+            const int o0 = (int)of, o1 = o0 + zstep;
+            const double oe = (Qz >= 0.0) ? of + 1.0 : of;
+            const double ze = zm + Qz;
+            const bool zc = (Qz >= 0.0) ? (ze > oe) : (ze < oe);
+            const float tZ = zc ? (float)(oe - zm) * invQzf : 1.0f;
+            const bool x_first = tX <= tZ;
+            const float t1 = fminf(tX, tZ), t2 = fmaxf(tX, tZ);
+            const int po1 = x_first ? o0 : o1;
+            const bool pin1 = x_first ? in1 : in0;
+            const float f0 = t1, f1 = t2 - t1, f2 = 1.0f - t2;
+            const bool v0 = f0 > 0.0f && in0 && o0 >= olo && o0 <= ohi;
+            const bool v1 = (xc || zc) && f1 > 0.0f && pin1 && po1 >= olo && po1 <= ohi;
+            const bool v2 = xc && zc && f2 > 0.0f && in1 && o1 >= olo && o1 <= ohi;
+            const int off[3] = {sl0 + o0, (x_first ? sl1 : sl0) + po1, sl1 + o1};
+            const float len[3] = {Lkf * f0, Lkf * f1, Lkf * f2};
+            const int present = mraw <= m1 ? (v0 ? 1 : 0) | (v1 ? 2 : 0) | (v2 ? 4 : 0) : 0;
+            // (4) compact the pieces in cell order (as in fp3_body)
+            const int cnt = __popc(present);
+            int pos = 0, total = 0;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const unsigned long long bm = __ballot((cnt >> k) & 1);
+                pos += __builtin_amdgcn_mbcnt_hi((unsigned)(bm >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bm, 0u)) << k;
+                total += __popcll(bm) << k;
+            }
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                if (present & (1 << k)) {
+                    s_po[wave][pos] = (unsigned short)((off[k] + 16) * 4);
+                    s_pl[wave][pos] = len[k];
+                    ++pos;
+                }
+            }
+            wave_lds_sync();
+            // (5) every lane (first ring r1) applies every piece from LDS
+            const int r1 = max(0, -d) + lane;
+            if (r1 <= min(R - 1, R - 1 - d)) {
+                if (counting) {
+                    acc[j] += (float)total;
+                } else {
+                    // byte address of slice o of a piece's column for this
+                    // lane: colb + (o + 16) * 4 with colb at ring r1 - 16
+                    const char* colb = reinterpret_cast<const char*>(s_col) + 4 * r1 - 64;
+                    float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+                    int k = 0;
+                    for (; k + 8 <= total; k += 8) {
+                        // eight pieces: offsets in one 16-byte read, lengths in
+                        // two, the eight column reads in flight together
+                        const uint4 po4 = *reinterpret_cast<const uint4*>(&s_po[wave][k]);
+                        const float4 l0 = *reinterpret_cast<const float4*>(&s_pl[wave][k]);
+                        const float4 l1 = *reinterpret_cast<const float4*>(&s_pl[wave][k + 4]);
+                        const unsigned po[4] = {po4.x, po4.y, po4.z, po4.w};
+                        const float ln[8] = {l0.x, l0.y, l0.z, l0.w, l1.x, l1.y, l1.z, l1.w};
+                        float x[8];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) {
+                            const unsigned ob = (u & 1) ? (po[u >> 1] >> 16) : (po[u >> 1] & 0xffffu);
+                            x[u] = *reinterpret_cast<const float*>(colb + ob);
+                        }
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) sum[u & 3] = fmaf(ln[u], x[u], sum[u & 3]);
+                    }
+                    for (; k < total; ++k)
+                        sum[0] = fmaf(s_pl[wave][k], *reinterpret_cast<const float*>(colb + s_po[wave][k]), sum[0]);
+                    acc[j] += (sum[0] + sum[1]) + (sum[2] + sum[3]);
+                }
+            }
+            wave_lds_sync();
+        }
+    }
+
+    // (6) the rays' outputs, as in fp3_body
+    double term = 0.0;
+#pragma unroll
+    for (int j = 0; j < FPS_DPW; ++j) {
+        const int di = wave + FPS_W * j;
+        if (di >= ND) break;
+        const int d = di - D;
+        const int r1lo = max(0, -d), r1 = r1lo + lane;
+        if (r1 > min(R - 1, R - 1 - d)) continue;
+        const int plane = g.plane_base[di] + (r1 - r1lo);
+        const long long nat = ((long long)plane * g.n_angles + a) * Nr + b;
+        const long long ray = ((long long)al * g.n_planes + plane) * Nr + b;
+        if (A.mode == FP_RATIO || A.mode == FP_EM) {
+            // y and r of the ray: from the bin-major copy the lanes' planes
+            // are consecutive (one 512-byte wave load), in the natural layout
+            // they lie n_angles * n_radial apart
+            float yv, rv;
+            if (A.yr != nullptr) {
+                const float2 v = A.yr[((long long)a * Nr + b) * g.n_planes + plane];
+                yv = v.x;
+                rv = v.y;
+            } else {
+                yv = A.y[nat];
+                rv = A.r[nat];
+            }
+            A.out[ray] = A.mode == FP_RATIO ? 1.0f - yv / (acc[j] + rv) : yv / (acc[j] + rv);
+        } else if (A.mode == FP_COUNT || A.mode == FP_COMPACT) {
+            A.out[ray] = acc[j];
+        } else if (A.mode == FP_PLAIN) {
+            A.out[nat] = acc[j];
+        } else {
+            const double q = (double)acc[j];
+            term += q - (double)A.y[nat] * log(q + (double)A.r[nat]);
+        }
+    }
+    if (A.mode == FP_OBJECTIVE) write_partial(term, A.red, s_red, vblock);
+}
+
+// six waves per SIMD: 44 KB of LDS per block lets three blocks share a CU
+__global__ __launch_bounds__(FPS_NT, 6) void k_fp3(GeoK g, FP3Args A, long long n_blocks) {
+    const long long vb = xcd_block(blockIdx.x, n_blocks);
+    if (vb >= n_blocks) return;
+    fp3s_body(g, A, vb);
 }
 
 // ------------------------------------------------------------------ back projection
@@ -861,9 +1133,25 @@ int fp3_grid(const pet_os_geom* G, int n_al) {
     return (int)((n + FP3_W - 1) / FP3_W);
 }
 
-// blocks of the single-request forward projection: quads of mirror rays, else
-// the per-wave items of fp3_body
-int fp3_launch_grid(const pet_os_geom* G, int n_al) { return fp3q_ok(G) ? fp3q_grid(G, n_al) : fp3_grid(G, n_al); }
+// k_fp3 takes what is not for a back-projector on quads where its one or two rounds of ring
+// differences per wave cost less than the quads' staging of both mirror
+// columns (columns copied 16 bytes a lane, so depths that are multiples of 4):
+// up to 5 ring differences, and up to 1 where a half-wave of quads holds a
+// column.  Objectives over all angles, k_fp3 and quads (us): 170x169x64 to
+// difference 0 345 and 482, to 4 649 and 690, to 5 707 and 716, to 6 781 and
+// 740; 170x169x40 to 5 669 and 684; 100x99x24 to 1 161 and 187, to 3 208 and
+// 193; 130x129x46 to 2 394 and 382.
+bool fp3s_better(const pet_os_geom* G) {
+    return fp3s_ok(G) && G->d.nz % 4 == 0 && G->d.max_ring_diff <= (G->d.nz > 32 ? 5 : 1);
+}
+
+// blocks of the objective's forward projection (partials of its sum): one per
+// (angle, bin) with staged columns, quads of mirror rays, or the per-wave items
+// of fp3_body
+int fp3_launch_grid(const pet_os_geom* G, int n_al) {
+    if (fp3s_better(G)) return n_al * G->d.n_radial;
+    return fp3q_ok(G) ? fp3q_grid(G, n_al) : fp3_grid(G, n_al);
+}
 
 // Slices per block of the batched back-projector, and the default of the
 // single-request one: the smallest of 16, 32, 64 that holds the volume's depth.
@@ -977,22 +1265,25 @@ int launch_yr3(const pet_os_geom* G, const float* y, const float* r, float2* yr,
 int launch_fp3(const pet_os_geom* G, const FPLaunch& L, hipStream_t s) {
     if (L.n_al == 0) return PET_OS_OK;
     if (L.mode != FP_COUNT && L.fz == nullptr) return fail(PET_OS_ERR_DEVICE, "3D forward projection without z copy");
-    // (FP_COMPACT is a 2D mode of the batch; a count is each ray's own: where a
-    // ray meets two cell edges at once, rounding tells whether a piece of no
-    // length is there, and not alike for its mirror rays)
-    if (fp3q_ok(G) && L.mode != FP_COMPACT && L.mode != FP_COUNT) return launch_fp3q(G, L, s);
+    // a count is each ray's own: where a ray meets two cell edges at once,
+    // rounding tells whether a piece of no length is there, and not alike for
+    // its mirror rays (FP_COMPACT is a 2D mode of the batch)
+    const bool staged = L.mode == FP_COUNT ? fp3s_ok(G) : fp3s_better(G) && !L.quad;
+    if (!staged && fp3q_ok(G) && L.mode != FP_COMPACT && L.mode != FP_COUNT) return launch_fp3q(G, L, s);
     FP3Args a;
     a.fz = L.fz;
     a.y = L.y;
     a.r = L.r;
+    a.yr = L.yr;
     a.out = L.out;
     a.angles = L.angles;
     a.n_al = L.n_al;
     a.mode = L.mode;
     a.red = L.red;
-    const int grid = fp3_grid(G, L.n_al);
+    const int grid = staged ? L.n_al * G->d.n_radial : fp3_grid(G, L.n_al);
     if (L.mode == FP_OBJECTIVE && grid > L.red.cap) return fail(PET_OS_ERR_DEVICE, "objective partials too small");
-    petos_launch(k_fp3_wave, dim3(8 * ((grid + 7) / 8)), dim3(NT), 0, s, G->k, a, (long long)grid);
+    if (staged) petos_launch(k_fp3, dim3(8 * ((grid + 7) / 8)), dim3(FPS_NT), 0, s, G->k, a, (long long)grid);
+    else petos_launch(k_fp3_wave, dim3(8 * ((grid + 7) / 8)), dim3(NT), 0, s, G->k, a, (long long)grid);
     PETOS_HIP(hipGetLastError());
     return PET_OS_OK;
 }

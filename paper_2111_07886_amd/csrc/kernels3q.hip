@@ -119,8 +119,9 @@ struct FQCell {
 // and measured 97.6 against 89.5 us.  One subset's weights of a 200x200x64
 // image (281 bins, 8 angles, ring differences to 15): 126.8 us with a block per
 // bin that staged its columns for all its LORs singly, 89.5 us here; to 1 at
-// 170x169x64 26.1 and 34.7 us (the back-projector gives that back, 57.4 and
-// 43.9 us), to 5 44.4 and 42.0 us.
+// 170x169x64 26.1 and 34.7 us (weights for the quad back-projector, which gives
+// that back, 57.4 and 43.9 us; the rest of the few-difference calls go to
+// k_fp3), to 5 44.4 and 42.0 us.
 //
 // KL lanes per k-range: 64, or 32 where the volume has at most 32 slices (the
 // half-waves then take the wave's two ring-difference magnitudes side by side).
@@ -926,7 +927,7 @@ int bp3q_rows(const pet_os_geom* G) { return bq_rows(G); }
 int bp3q_buf(const pet_os_geom* G) { return bq_buf(G); }
 
 // The quad forward projector takes volumes of at most 64 slices (a lane per
-// ring); deeper ones keep the per-wave one.
+// ring), unless k_fp3 is faster (fp3s_better); deeper ones keep the per-wave one.
 bool fp3q_ok(const pet_os_geom* G) { return G->d.dim == 3 && G->d.nz <= 64; }
 
 // The quad back-projector, and with it the quad layout of the weights, also
