@@ -770,11 +770,14 @@ __device__ __forceinline__ void bp3q_body(const GeoK& g, const BP3QArgs& A, int 
     const int tiles_x = bq_tiles_x(g.nx);
     const int tx0 = (vblock % tiles_x) * BQ_X, ty0 = (vblock / tiles_x) * BQ_Y;
     const int Nr = g.n_radial, nz = g.nz, ncol = g.nx * g.ny;
-    float acc[CPG][4];
+    float acc[CPG][4], tot[CPG][2];
 #pragma unroll
-    for (int j = 0; j < CPG; ++j)
+    for (int j = 0; j < CPG; ++j) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) acc[j][q] = 0.0f;
+        tot[j][0] = tot[j][1] = 0.0f;
+    }
+    const int kk = lane % KL, rev = grp * KL + max(0, nz - 1 - kk);    // the slice, the lane of the opposite one
     unsigned long long sw = 0;
     __syncthreads();    // (batched blocks: the staging area is read no more)
     if ((int)threadIdx.x < 2 * BQ_PAD)
@@ -818,7 +821,7 @@ __device__ __forceinline__ void bp3q_body(const GeoK& g, const BP3QArgs& A, int 
             if (q == 0) sh.n_oblique = __popcll(ob);
         }
         __syncthreads();
-        // (2) the steps of its entries, the hits of eight entries at a time
+        // (2) the steps of its entries, the hits of four entries at a time
         const int nob = __builtin_amdgcn_readfirstlane(sh.n_oblique), ne = nob + 2 * (na - nob);
         int cur = 0;
         {
@@ -836,31 +839,36 @@ __device__ __forceinline__ void bp3q_body(const GeoK& g, const BP3QArgs& A, int 
             const int e1 = min(e0 + BQ_E, ne), em = min(max(nob, e0), e1);
             bq_angles<KL, false, CPG>(g, A, sh, e0, em, ne, c0, acc, sw, cur, s_w, wave, lane);
             bq_angles<KL, true, CPG>(g, A, sh, em, e1, ne, c0, acc, sw, cur, s_w, wave, lane);
+            // (3) their sums: the two ends of each column added, to the
+            // chunk's.  (In one chain through all of 10 angles with 10
+            // magnitudes each the image was 1.34e-7 from 64-bit sums, 0.86e-7
+            // so; k_bp3's four sums per column 0.89e-7.)
+#pragma unroll
+            for (int j = 0; j < CPG; ++j) {
+                bq_swap(acc[j], bq_bit<KL>(sw, j, grp));
+                tot[j][0] += acc[j][0] + __shfl(acc[j][1], rev);
+                tot[j][1] += acc[j][3] + __shfl(acc[j][2], rev);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc[j][q] = 0.0f;
+            }
+            sw = 0;
         }
-        // (3) the chunk's sums: the two ends of each column added, to the
-        // columns (later chunks add to what is there, which keeps the FP32
-        // chains short when every angle is projected)
-        const int kk = lane % KL, rev = grp * KL + max(0, nz - 1 - kk);
+        // (4) the chunk's columns (later chunks add to what is there)
 #pragma unroll
         for (int j = 0; j < CPG; ++j) {
             const int ix = tx0 + grp * CPG + j, col = (ty0 + wave) * g.nx + ix;
-            bq_swap(acc[j], bq_bit<KL>(sw, j, grp));
-            float s = acc[j][0] + __shfl(acc[j][1], rev);
-            float sm = acc[j][3] + __shfl(acc[j][2], rev);
             if (ix < g.nx && 2 * col <= ncol - 1 && kk < nz) {
                 float* o = A.out + (long long)col * nz + kk;
                 float* om = A.out + (long long)(ncol - 1 - col) * nz + kk;
                 if (c0 > 0 || A.add) {
-                    s += *o;
-                    sm += *om;
+                    tot[j][0] += *o;
+                    tot[j][1] += *om;
                 }
-                *o = s;
-                if (2 * col != ncol - 1) *om = sm;
+                *o = tot[j][0];
+                if (2 * col != ncol - 1) *om = tot[j][1];
             }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) acc[j][q] = 0.0f;
+            tot[j][0] = tot[j][1] = 0.0f;
         }
-        sw = 0;
     }
 }
 
@@ -892,8 +900,11 @@ __device__ __forceinline__ bool bq_tile(const GeoK& g, int block, int& tile) {
 // The first bp_blocks blocks back-project; A.n_pen more compute the penalty
 // gradient and mu of the entering iterate (pen3_body, halo tile in the
 // staging area).
-template <int KL>
-__global__ __launch_bounds__(NT, 5) void k_bp3q(GeoK g, BP3QArgs A, int bp_blocks) {
+//
+// OCC blocks per CU: five, or four, whose registers hold the chunk's sums that
+// five keep in scratch memory (with which a kernel starts 1 us later).
+template <int KL, int OCC>
+__global__ __launch_bounds__(NT, OCC) void k_bp3q(GeoK g, BP3QArgs A, int bp_blocks) {
     __shared__ BP3QShared sh;
     if ((int)blockIdx.x >= bp_blocks) {
         pen3_body(g, A.pen, (int)blockIdx.x - bp_blocks, reinterpret_cast<float*>(q_smem), sh.red);
@@ -970,6 +981,24 @@ int launch_fp3q(const pet_os_geom* G, const FPLaunch& L, hipStream_t s) {
     return PET_OS_OK;
 }
 
+// the back-projection's blocks and those of the penalty
+static int bq_launch(const pet_os_geom* G, const BP3QArgs& a, hipStream_t s) {
+    const int n = bp3q_grid(G);
+    const dim3 blocks(n + a.n_pen), threads(NT);
+    const size_t lds = bp3q_lds(G);
+    if (G->d.nz > 32) petos_launch(k_bp3q<64, 5>, blocks, threads, lds, s, G->k, a, n);
+    // Five blocks per CU where the tiles are more than four each and the LDS of
+    // five is there (handed out by 1280 bytes of 160 KB): 10 angles of a
+    // 200x199x24 image to difference 9 (1250 tiles) 81.2 and 103 us with five
+    // and four, of 32 slices (four fit) 107.5 and 106.4, of a 127x125x29 image
+    // (512 tiles) 61.3 and 60.4.
+    else if (n > 4 * 256 && 5 * ((lds + sizeof(BP3QShared) + 1279) / 1280) <= 128)
+        petos_launch(k_bp3q<32, 5>, blocks, threads, lds, s, G->k, a, n);
+    else petos_launch(k_bp3q<32, 4>, blocks, threads, lds, s, G->k, a, n);
+    PETOS_HIP(hipGetLastError());
+    return PET_OS_OK;
+}
+
 int launch_bp3q(const pet_os_geom* G, const BPLaunch& L, hipStream_t s) {
     if ((L.f != nullptr) != (L.gradR != nullptr))
         return fail(PET_OS_ERR_DEVICE, "3D back-projection: the penalty blocks need both f and gradR");
@@ -986,12 +1015,7 @@ int launch_bp3q(const pet_os_geom* G, const BPLaunch& L, hipStream_t s) {
         a.n_pen = pen3_grid(G);
         if (L.want_mu && a.n_pen > L.red_mu.cap) return fail(PET_OS_ERR_DEVICE, "mu partials too small");
     }
-    const int bp_blocks = bp3q_grid(G);
-    const dim3 blocks(bp_blocks + a.n_pen);
-    if (G->d.nz > 32) petos_launch(k_bp3q<64>, blocks, dim3(NT), bp3q_lds(G), s, G->k, a, bp_blocks);
-    else petos_launch(k_bp3q<32>, blocks, dim3(NT), bp3q_lds(G), s, G->k, a, bp_blocks);
-    PETOS_HIP(hipGetLastError());
-    return PET_OS_OK;
+    return bq_launch(G, a, s);
 }
 
 // ------------------------------------------------------------------ natural weights
@@ -1092,9 +1116,8 @@ int launch_back3q(const pet_os_geom* G, const BPLaunch& L, void* scratch, hipStr
                                (size_t)PQ_P * (d.nz + 1) * sizeof(float4), s, G->k, L.w,
                                wq + quad_floats(G, h) / 4, a.angles + h);
         }
-        const int blocks = bp3q_grid(G);
-        if (d.nz > 32) petos_launch(k_bp3q<64>, dim3(blocks), dim3(NT), bp3q_lds(G), s, G->k, a, blocks);
-        else petos_launch(k_bp3q<32>, dim3(blocks), dim3(NT), bp3q_lds(G), s, G->k, a, blocks);
+        const int rc = bq_launch(G, a, s);
+        if (rc) return rc;
     }
     return launch_turn3(G, img, L.out, nullptr, s);
 }
