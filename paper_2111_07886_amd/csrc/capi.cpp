@@ -1267,6 +1267,7 @@ int pet_os_subset_gradient(const pet_os_geom* g, const pet_os_params* p, const f
         const size_t n = quad_ok(g) ? quad_floats(g, n_al) : (size_t)n_al * g->n_planes * g->d.n_radial + 4;
         big = (float*)scratch_take(g, sizeof(float) * n, &big_bytes, &s);
         if (!big) {
+            (void)hipStreamSynchronize(s);      // w's block may only be ordered after its last user, on s
             work_free(&w);
             return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of the ratio sinogram failed");
         }

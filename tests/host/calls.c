@@ -1,0 +1,90 @@
+/* Whole calls of the library on the stand-in HIP runtime (hip_stub.h): what
+ * they allocate, wait for and hand on.  One scenario per argument. */
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include "hip_stub.h"
+#include "pet_os.h"
+
+int hipGetLastError(void);
+
+static int A_, B_, C_;
+#define A ((void*)&A_)
+#define B ((void*)&B_)
+#define C ((void*)&C_)
+static float buf[16];       /* stands for the caller's device buffers (no kernel runs) */
+
+#define CHECK(c)                                                       \
+    do {                                                               \
+        if (!(c)) {                                                    \
+            printf("line %d: %s (%s)\n", __LINE__, #c, pet_os_last_error()); \
+            exit(1);                                                   \
+        }                                                              \
+    } while (0)
+
+static pet_os_geom* geometry(int n, int nz, int angles, int rd, int subsets) {
+    pet_os_geom_desc d;
+    memset(&d, 0, sizeof(d));
+    d.dim = nz > 1 ? 3 : 2;
+    d.nx = d.ny = n;
+    d.nz = nz;
+    d.vx = d.vy = d.ds = 2.0;
+    d.vz = d.ring_pitch = nz > 1 ? 2.5 : 1.0;
+    d.n_angles = angles;
+    d.n_radial = 3 * n / 2 + 1;
+    d.n_rings = nz;
+    d.max_ring_diff = rd;
+    d.det_radius = 2.0 * n;
+    d.n_subsets = subsets;
+    pet_os_geom* g = NULL;
+    CHECK(pet_os_create_geometry(&d, &g) == PET_OS_OK);
+    return g;
+}
+
+static pet_os_params params(void) {
+    pet_os_params p;
+    memset(&p, 0, sizeof(p));
+    p.mode = PET_OS_BSREM;
+    p.beta = 0.1;
+    p.gamma_R = 2.0;
+    p.eps = 1e-12;
+    p.U = 1e3;
+    p.t_clip = 1e-4;
+    p.lambda0 = 1.0;
+    p.a = 0.25;
+    p.objective_every = 1;
+    return p;
+}
+
+/* A gradient that finds no memory for its sinogram gives back what it took;
+ * the next call may not use it while another stream's work does. */
+static void failed_call(void) {
+    pet_os_geom* g = geometry(64, 16, 64, 3, 8);
+    pet_os_params p = params();
+    double phi;
+    CHECK(pet_os_back(g, buf, 0, buf, A) == PET_OS_OK);
+    void* used = stub_last_malloc;
+    CHECK(stub_pending(A));
+    stub_limit = stub_live;
+    CHECK(pet_os_subset_gradient(g, &p, buf, buf, buf, 0, buf, B) == PET_OS_ERR_OUT_OF_MEMORY);
+    stub_limit = (size_t)1 << 34;
+    hipGetLastError();
+    const long waits = stub_stream_waits;
+    stub_last_copy = NULL;
+    CHECK(pet_os_objective(g, &p, buf, buf, buf, &phi, C) == PET_OS_OK);
+    CHECK(stub_last_copy != NULL);
+    CHECK(stub_block(stub_last_copy) != used || !stub_pending(A) || stub_stream_waits > waits);
+}
+
+int main(int argc, char** argv) {
+    static const struct { const char* name; void (*run)(void); } all[] = {{"failed_call", failed_call}};
+    for (size_t k = 0; argc > 1 && k < sizeof(all) / sizeof(all[0]); ++k)
+        if (!strcmp(argv[1], all[k].name)) {
+            all[k].run();
+            printf("ok\n");
+            return 0;
+        }
+    printf("no such scenario\n");
+    return 2;
+}

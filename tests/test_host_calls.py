@@ -1,0 +1,39 @@
+"""Bookkeeping of whole calls without a GPU: the built library runs on a
+stand-in for the HIP runtime (tests/host: host memory, kernels that do nothing,
+streams whose work stays pending), which sees every allocation, wait and launch
+that a call makes."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    if shutil.which("gcc") is None:
+        pytest.skip("gcc not available")
+    lib = os.path.join(ROOT, "paper_2111_07886_amd", "libpet_os.so")
+    if not os.path.exists(lib):
+        from paper_2111_07886_amd import build
+        build.build()
+    exe = str(tmp_path_factory.mktemp("host") / "calls")
+    # -rdynamic: the library's HIP calls resolve to the program's
+    subprocess.run(["gcc", "-O1", "-g", "-std=gnu11", "-Wall", "-rdynamic", "-I", os.path.join(ROOT, "include"),
+                    os.path.join(HERE, "host", "calls.c"), os.path.join(HERE, "host", "hip_stub.c"), "-o", exe, lib,
+                    "-Wl,-rpath," + os.path.dirname(lib), "-lpthread"], check=True, capture_output=True)
+    return exe
+
+
+def run(program, scenario):
+    res = subprocess.run([program, scenario], capture_output=True, text=True, timeout=60)
+    assert res.returncode == 0 and res.stdout.strip() == "ok", res.stdout + res.stderr
+
+
+def test_a_failed_call_gives_back_scratch_in_order(program):
+    """A call that runs out of memory gives back scratch that another stream's
+    queued work still uses: the next call waits for it or takes other memory."""
+    run(program, "failed_call")
