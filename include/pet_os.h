@@ -53,6 +53,10 @@
  *     same buffers need a state of their own.  If that allocation fails, or
  *     for pet_os_reconstruct_noalloc, y and r are read where they are.
  *   - Calls are asynchronous on `stream` unless stated otherwise.
+ *   - Device memory: the scratch that whole calls (pet_os_forward, _back,
+ *     _objective, _subset_gradient, _reconstruct) allocate is kept for the
+ *     next calls, up to 256 MiB per device over all geometries, until the last
+ *     geometry is destroyed or an allocation of the library needs it.
  */
 #ifndef PET_OS_H
 #define PET_OS_H

@@ -177,7 +177,7 @@ int rebuild_lists(pet_os_batch* B) {
         B->d_lists = nullptr;
         const size_t cap = std::max(bytes, 2 * B->lists_cap);
         B->lists_cap = 0;
-        if (hipMalloc(&B->d_lists, cap) != hipSuccess)
+        if (!device_alloc((void**)&B->d_lists, cap))
             return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of the work lists failed");
         B->lists_cap = cap;
     }
@@ -279,7 +279,7 @@ int add_together(pet_os_batch* B, int n, const pet_os_geom* const* geoms, const 
         o_work[k] = bytes;
         bytes += up(work_bytes(geoms[k], need_nu(k)));
     }
-    if (hipMalloc(&B->slab, bytes) != hipSuccess) return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of scratch failed");
+    if (!device_alloc((void**)&B->slab, bytes)) return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of scratch failed");
     char* base = (char*)B->slab;
     auto* totals = (unsigned long long*)base;
     std::vector<char> sched(subs * (sizeof(float) + sizeof(int)));
@@ -336,7 +336,7 @@ int pet_os_batch_create(int32_t max_slots, pet_os_batch** out) {
     B->max_slots = max_slots;
     B->slots.resize(max_slots);
     B->h_slots.assign(max_slots, SlotDev{});
-    if (hipMalloc(&B->d_slots, sizeof(SlotDev) * (size_t)max_slots) != hipSuccess) {
+    if (!device_alloc((void**)&B->d_slots, sizeof(SlotDev) * (size_t)max_slots)) {
         delete B;
         return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of the slot table failed");
     }
@@ -397,8 +397,8 @@ int pet_os_batch_add(pet_os_batch* B, const pet_os_geom* g, const pet_os_params*
     std::vector<float> step;
     std::vector<int> nu;
     schedule_table(*p, M, S.J_end, step, nu);
-    if (hipMalloc(&S.d_step, step.size() * sizeof(float)) != hipSuccess ||
-        hipMalloc(&S.d_nu, nu.size() * sizeof(int)) != hipSuccess) {
+    if (!device_alloc((void**)&S.d_step, step.size() * sizeof(float)) ||
+        !device_alloc((void**)&S.d_nu, nu.size() * sizeof(int))) {
         slot_release(S);
         return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of the schedule failed");
     }
@@ -636,7 +636,7 @@ static int autotune3(pet_os_geom* g, GeomExtra* ex, int32_t flags, hipStream_t s
     // three bins past the last row
     const size_t nw = (size_t)g->max_sub_angles * g->n_planes * g->d.n_radial;
     float *w = nullptr, *img = nullptr;
-    if (hipMalloc(&w, (nw + 4) * sizeof(float)) != hipSuccess || hipMalloc(&img, (size_t)g->n_vox * sizeof(float)) != hipSuccess) {
+    if (!device_alloc((void**)&w, (nw + 4) * sizeof(float)) || !device_alloc((void**)&img, (size_t)g->n_vox * sizeof(float))) {
         if (w) (void)hipFree(w);
         return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc failed in autotune");
     }
@@ -698,8 +698,8 @@ extern "C" int pet_os_autotune(pet_os_geom* g, int32_t flags, pet_os_stream stre
     hipStream_t s = (hipStream_t)stream;
     const size_t nw = (size_t)g->max_sub_angles * g->n_planes * g->d.n_radial;
     float *f = nullptr, *w = nullptr, *img = nullptr;
-    if (hipMalloc(&f, (size_t)g->n_vox * sizeof(float)) != hipSuccess ||
-        hipMalloc(&w, (nw + 4) * sizeof(float)) != hipSuccess || hipMalloc(&img, (size_t)g->n_vox * sizeof(float)) != hipSuccess) {
+    if (!device_alloc((void**)&f, (size_t)g->n_vox * sizeof(float)) ||
+        !device_alloc((void**)&w, (nw + 4) * sizeof(float)) || !device_alloc((void**)&img, (size_t)g->n_vox * sizeof(float))) {
         if (f) (void)hipFree(f);
         if (w) (void)hipFree(w);
         return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc failed in autotune");

@@ -336,7 +336,7 @@ static int create_geometry(const pet_os_geom_desc* desc, const float* att_host, 
     size_t o_tmp = cv.take<float>(d.psf_fwhm > 0.0 ? (size_t)G->n_vox : 1);
     size_t total = cv.off;
     char* blk = nullptr;
-    if (hipMalloc(&blk, total) != hipSuccess) {
+    if (!device_alloc((void**)&blk, total)) {
         delete G;
         return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of geometry tables failed");
     }
@@ -424,12 +424,14 @@ static int create_geometry(const pet_os_geom_desc* desc, const float* att_host, 
 
 int pet_os_destroy_geometry(pet_os_geom* geom) {
     if (!geom) return fail(PET_OS_ERR_INVALID_ARG, "geom is NULL");
+    bool last = false;
     {
         std::lock_guard<std::mutex> lk(g_geo_mu);
         g_geo_extra.erase(geom);
+        last = g_geo_extra.empty();
     }
     if (geom->dev_block) (void)hipFree(geom->dev_block);
-    scratch_drop(geom);
+    if (last) scratch_release();
     delete geom;
     return PET_OS_OK;
 }
@@ -525,99 +527,18 @@ void work_carve_at(const pet_os_geom* g, bool need_nu, void* base, Work* w) {
     work_carve(work_layout(g, need_nu, false), (char*)base, w);
 }
 
-// An allocation and its release cost a short call more than its kernels do
-// (they also wait for the whole device): a 128x128x32 forward projection took
-// 97 us with them for 39 us of kernels.
-void* scratch_take(const pet_os_geom* g, size_t bytes, size_t* got, const hipStream_t* s) {
-    int dev = -1;
-    if (hipGetDevice(&dev) == hipSuccess && dev == g->device) {
-        std::lock_guard<std::mutex> lk(g->kept_mu);
-        auto best = g->kept.end();
-        for (auto it = g->kept.begin(); it != g->kept.end(); ++it)
-            if (it->bytes >= bytes && (best == g->kept.end() || it->bytes < best->bytes)) best = it;
-        if (best != g->kept.end()) {
-            const pet_os_geom::Kept k = *best;
-            *got = k.bytes;
-            g->kept.erase(best);
-            if (k.done) {
-                const hipError_t e = s ? hipStreamWaitEvent(*s, k.done, 0) : hipEventSynchronize(k.done);
-                if (e != hipSuccess) (void)hipDeviceSynchronize();
-                (void)hipEventDestroy(k.done);
-            }
-            return k.p;
-        }
-    }
-    void* p = nullptr;
-    *got = bytes;
-    if (hipMalloc(&p, bytes) == hipSuccess) return p;
-    (void)hipGetLastError();
-    scratch_drop(g);        // what the geometry keeps may be what is missing
-    return hipMalloc(&p, bytes) == hipSuccess ? p : nullptr;
-}
-
-void scratch_drop(const pet_os_geom* g) {
-    std::vector<pet_os_geom::Kept> old;
-    {
-        std::lock_guard<std::mutex> lk(g->kept_mu);
-        old.swap(g->kept);
-    }
-    for (auto& k : old) {
-        if (k.done) {
-            (void)hipEventSynchronize(k.done);
-            (void)hipEventDestroy(k.done);
-        }
-        (void)hipFree(k.p);
-    }
-}
-
-void scratch_give(const pet_os_geom* g, void* p, size_t bytes, const hipStream_t* after) {
-    int dev = -1;
-    hipEvent_t done = nullptr;
-    if (after && (hipEventCreateWithFlags(&done, hipEventDisableTiming) != hipSuccess ||
-                  hipEventRecord(done, *after) != hipSuccess)) {
-        (void)hipStreamSynchronize(*after);
-        if (done) (void)hipEventDestroy(done);
-        done = nullptr;
-    }
-    if (hipGetDevice(&dev) == hipSuccess && dev == g->device && bytes <= KEPT_MAX) {
-        std::lock_guard<std::mutex> lk(g->kept_mu);
-        // a larger block takes the place of the smallest
-        size_t total = bytes, least = 0;
-        for (size_t i = 0; i < g->kept.size(); ++i) {
-            total += g->kept[i].bytes;
-            if (g->kept[i].bytes < g->kept[least].bytes) least = i;
-        }
-        if (g->kept.size() < 2 && total <= KEPT_MAX) {
-            g->kept.push_back({p, bytes, done});
-            return;
-        }
-        if (!g->kept.empty() && g->kept[least].bytes < bytes && total - g->kept[least].bytes <= KEPT_MAX) {
-            std::swap(g->kept[least].p, p);
-            std::swap(g->kept[least].done, done);
-            g->kept[least].bytes = bytes;
-        }
-    }
-    if (done) {
-        (void)hipEventSynchronize(done);
-        (void)hipEventDestroy(done);
-    }
-    (void)hipFree(p);
-}
-
 int work_alloc(const pet_os_geom* g, bool need_nu, Work* w, bool sums, bool keep, const hipStream_t* s) {
     *w = Work{};
     const WorkLayout L = work_layout(g, need_nu, sums);
     char* blk = nullptr;
     if (keep) {
-        size_t got = 0;
-        blk = (char*)scratch_take(g, L.bytes, &got, s);
+        blk = (char*)scratch_take(L.bytes, s);
         if (!blk) return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of scratch failed");
         work_carve(L, blk, w);
-        w->bytes = got;
-        w->keeper = g;
+        w->kept = true;
         return PET_OS_OK;
     }
-    if (hipMalloc(&blk, L.bytes) != hipSuccess) return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of scratch failed");
+    if (!device_alloc((void**)&blk, L.bytes)) return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of scratch failed");
     work_carve(L, blk, w);
     if (hipMemset(blk + L.o_tot, 0, RED_COUNT * sizeof(double)) != hipSuccess) {
         (void)hipFree(blk);
@@ -644,7 +565,7 @@ int work_place(const pet_os_geom* g, bool need_nu, void* base, size_t cap, size_
 }
 
 void work_free(Work* w) {
-    if (w->keeper) scratch_give(w->keeper, w->red_block, w->bytes);
+    if (w->kept) scratch_give(w->red_block);
     else if (w->red_block) (void)hipFree(w->red_block);
     *w = Work{};
 }
@@ -837,15 +758,10 @@ static int ensure_yr(pet_os_state* st, const float* y, const float* r, hipStream
     if (!st->may_allocate || !fp3_reads_yr(g)) return PET_OS_OK;
     if (st->yr != nullptr && st->yr_y == y && st->yr_r == r) return PET_OS_OK;
     if (st->yr == nullptr) {
+        const size_t bytes = (size_t)g->n_bins * sizeof(float2);
         void* p = nullptr;
-        st->yr_bytes = (size_t)g->n_bins * sizeof(float2);
-        if (st->w.keeper) {
-            p = scratch_take(g, st->yr_bytes, &st->yr_bytes, &s);
-            if (!p) (void)hipGetLastError();
-        } else if (hipMalloc(&p, st->yr_bytes) != hipSuccess) {
-            (void)hipGetLastError();
-            p = nullptr;
-        }
+        if (st->w.kept) p = scratch_take(bytes, &s);
+        else (void)device_alloc(&p, bytes);
         if (!p) return PET_OS_OK;       // the natural layout serves
         st->yr = (float2*)p;
     }
@@ -1021,7 +937,7 @@ static int state_create(const pet_os_geom* g, const pet_os_params* p, bool keep,
         // the M subset sensitivities A_i^T 1 of the EM update
         GeomExtra* ex = extra_of(g);
         const int M = g->d.n_subsets;
-        if (hipMalloc(&st->osem_sens, sizeof(float) * (size_t)M * g->n_vox) != hipSuccess) {
+        if (!device_alloc((void**)&st->osem_sens, sizeof(float) * (size_t)M * g->n_vox)) {
             work_free(&st->w);
             delete st;
             return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of the subset sensitivities failed");
@@ -1056,7 +972,7 @@ int pet_os_state_create(const pet_os_geom* g, const pet_os_params* p, pet_os_sta
 
 int pet_os_state_destroy(pet_os_state* st) {
     if (!st) return fail(PET_OS_ERR_INVALID_ARG, "state is NULL");
-    if (st->yr && st->w.keeper) scratch_give(st->w.keeper, st->yr, st->yr_bytes);
+    if (st->yr && st->w.kept) scratch_give(st->yr);
     else if (st->yr) (void)hipFree(st->yr);
     work_free(&st->w);
     if (st->osem_sens) (void)hipFree(st->osem_sens);
@@ -1107,14 +1023,13 @@ int pet_os_forward(const pet_os_geom* g, const float* f, int32_t subset, float* 
     if (g->d.dim == 2 && g->k.psf_kx > 0) {
         // the PSF-blurred image, in scratch given back before returning
         hipStream_t s = (hipStream_t)stream;
-        size_t got = 0;
-        float* tmp = (float*)scratch_take(g, sizeof(float) * (size_t)g->n_vox, &got, &s);
+        float* tmp = (float*)scratch_take(sizeof(float) * (size_t)g->n_vox, &s);
         if (!tmp) return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc failed");
         int rc = launch_blur(g, f, tmp, s);
         F.f = tmp;
         if (!rc) rc = launch_fp(g, F, s);
         if (hipStreamSynchronize(s) != hipSuccess && !rc) rc = fail(PET_OS_ERR_DEVICE, "stream synchronize failed");
-        scratch_give(g, tmp, got);
+        scratch_give(tmp);
         return rc;
     }
     if (g->d.dim == 2) return launch_fp(g, F, (hipStream_t)stream);
@@ -1144,14 +1059,13 @@ int pet_os_back(const pet_os_geom* g, const float* w, int32_t subset, float* out
     if (g->d.dim == 2 && g->k.psf_kx > 0) {
         // back-projection into scratch, then the (symmetric) PSF into out
         hipStream_t s = (hipStream_t)stream;
-        size_t got = 0;
-        float* tmp = (float*)scratch_take(g, sizeof(float) * (size_t)g->n_vox, &got, &s);
+        float* tmp = (float*)scratch_take(sizeof(float) * (size_t)g->n_vox, &s);
         if (!tmp) return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc failed");
         B.out = tmp;
         int rc = launch_bp(g, B, s);
         if (!rc) rc = launch_blur(g, tmp, out, s);
         if (hipStreamSynchronize(s) != hipSuccess && !rc) rc = fail(PET_OS_ERR_DEVICE, "stream synchronize failed");
-        scratch_give(g, tmp, got);
+        scratch_give(tmp);
         return rc;
     }
     hipStream_t s = (hipStream_t)stream;
@@ -1164,13 +1078,12 @@ int pet_os_back(const pet_os_geom* g, const float* w, int32_t subset, float* out
         // A call under capture, whose launches would use the scratch again and
         // again, and one that finds no memory keep the kernel that needs none.
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        size_t got = 0;
         void* tmp = hipStreamIsCapturing(s, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone
-                        ? scratch_take(g, back3q_bytes(g, B.n_al), &got, &s)
+                        ? scratch_take(back3q_bytes(g, B.n_al), &s)
                         : nullptr;
         if (tmp) {
             const int rc = launch_back3q(g, B, tmp, s);
-            scratch_give(g, tmp, got, &s);
+            scratch_give(tmp, &s);
             return rc;
         }
         (void)hipGetLastError();
@@ -1193,13 +1106,15 @@ int pet_os_attenuation_factors(const pet_os_geom* g, const float* mu, float* att
     return rc;
 }
 
-int pet_os_objective(const pet_os_geom* g, const pet_os_params* p, const float* f, const float* y,
-                     const float* r, double* phi, pet_os_stream stream) {
+}  // extern "C"
+
+int petos::objective(const pet_os_geom* g, const pet_os_params* p, const float* f, const float* y, const float* r,
+                     double* phi, pet_os_stream stream, bool keep) {
     if (!g || !p || !f || !y || !r || !phi) return fail(PET_OS_ERR_INVALID_ARG, "NULL argument");
     if (!extra_of(g)) return fail(PET_OS_ERR_INVALID_ARG, "invalid geometry");
     Work w;
     hipStream_t s = (hipStream_t)stream;
-    int rc = work_alloc(g, false, &w, false, true, &s);
+    int rc = work_alloc(g, false, &w, false, keep, &s);
     if (rc) return rc;
     double* dst = (double*)w.check_total;      // (two of its four words; no data check here)
     rc = queue_objective(g, p, &w, f, y, r, dst, s);
@@ -1212,6 +1127,13 @@ int pet_os_objective(const pet_os_geom* g, const pet_os_params* p, const float* 
     *phi = h[0] + p->beta * h[1];
     if (!std::isfinite(*phi)) return fail(PET_OS_ERR_NUMERIC, "objective is not finite");
     return PET_OS_OK;
+}
+
+extern "C" {
+
+int pet_os_objective(const pet_os_geom* g, const pet_os_params* p, const float* f, const float* y,
+                     const float* r, double* phi, pet_os_stream stream) {
+    return objective(g, p, f, y, r, phi, stream, true);
 }
 
 int pet_os_default_U(const pet_os_geom* g, const float* f0, const float* y, const float* r, double* U,
@@ -1261,11 +1183,10 @@ int pet_os_subset_gradient(const pet_os_geom* g, const pet_os_params* p, const f
     // the ratio sinogram of every ray does not fit the subset-sized scratch
     float* wsino = w.w;
     float* big = nullptr;
-    size_t big_bytes = 0;
     if (n_al > g->max_sub_angles) {
         // + 4 floats of padding for the 3D back-projector's 16-byte staging loads
         const size_t n = quad_ok(g) ? quad_floats(g, n_al) : (size_t)n_al * g->n_planes * g->d.n_radial + 4;
-        big = (float*)scratch_take(g, sizeof(float) * n, &big_bytes, &s);
+        big = (float*)scratch_take(sizeof(float) * n, &s);
         if (!big) {
             (void)hipStreamSynchronize(s);      // w's block may only be ordered after its last user, on s
             work_free(&w);
@@ -1322,7 +1243,7 @@ int pet_os_subset_gradient(const pet_os_geom* g, const pet_os_params* p, const f
         rc = launch_bp(g, B, s);
     }
     if (hipStreamSynchronize(s) != hipSuccess && !rc) rc = fail(PET_OS_ERR_DEVICE, "stream synchronize failed");
-    if (big) scratch_give(g, big, big_bytes);
+    if (big) scratch_give(big);
     work_free(&w);
     return rc;
 }
@@ -1343,7 +1264,7 @@ int pet_os_gradient_angles(const pet_os_geom* g, const float* h_prev, const floa
     hipStream_t s = (hipStream_t)stream;
     const size_t nd = angle_scratch_doubles(g->n_vox);
     double* blk = nullptr;
-    if (hipMalloc(&blk, nd * sizeof(double)) != hipSuccess) return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc failed");
+    if (!device_alloc((void**)&blk, nd * sizeof(double))) return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc failed");
     double* sums = blk + nd - 8;
     int rc = launch_gradient_angles(g, h_prev, h_cur, f, smooth_frac, var_frac, blk, s);
     double h[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -1398,7 +1319,7 @@ static int ensure_obj(pet_os_state* st, int n) {
         st->obj_dev = nullptr;
         st->obj_cap = 0;
     }
-    if (hipMalloc(&st->obj_dev, 2 * sizeof(double) * (size_t)n) != hipSuccess)
+    if (!device_alloc((void**)&st->obj_dev, 2 * sizeof(double) * (size_t)n))
         return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of objective slots failed");
     st->obj_cap = n;
     return PET_OS_OK;
@@ -1516,7 +1437,7 @@ int pet_os_nnz(const pet_os_geom* g, int32_t subset, int64_t* nnz) {
     int rc = work_alloc(g, false, &w, true);
     if (rc) return rc;
     float* cnt = nullptr;
-    if (hipMalloc(&cnt, (size_t)n * sizeof(float)) != hipSuccess) {
+    if (!device_alloc((void**)&cnt, (size_t)n * sizeof(float))) {
         work_free(&w);
         return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc failed");
     }

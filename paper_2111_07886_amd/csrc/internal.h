@@ -78,14 +78,6 @@ struct pet_os_geom {
     int tuned_dpg = 0;                  // 3D ring differences per staging group (0: default)
     bool full_model = false;            // sub-rays, PSF or attenuation (2D; single-request paths only)
     std::vector<int> subset_angles(int subset) const;   // subset in 1..M, 0 = all
-    // scratch of whole calls kept between them (scratch_take, scratch_give)
-    struct Kept {
-        void* p;
-        size_t bytes;
-        hipEvent_t done;        // null, or the end of the work that still uses it
-    };
-    mutable std::mutex kept_mu;
-    mutable std::vector<Kept> kept;
 };
 
 namespace petos {
@@ -106,22 +98,21 @@ struct Work {
     unsigned* check_part = nullptr;            // data check: per-block counts [CHECK_GRID][4]
     unsigned long long* check_total = nullptr; // data check: the four totals
     size_t bytes = 0;
-    const pet_os_geom* keeper = nullptr;       // work_free leaves the scratch with this geometry
+    bool kept = false;                         // of a whole call: work_free gives it back (scratch_give)
 };
 
-// Device memory of a whole call: a geometry keeps up to two blocks of KEPT_MAX
-// bytes together for its next calls, on any thread or stream, and frees them
-// with itself.  A block taken holds whatever the last call left; work queued on
-// s comes after that call's (s null: the host has waited for it).  A call gives
-// a block back once its stream is synchronized, or with the work still queued
-// on `after`.
-constexpr size_t KEPT_MAX = (size_t)256 << 20;
-void* scratch_take(const pet_os_geom* g, size_t bytes, size_t* got, const hipStream_t* s);
-void scratch_give(const pet_os_geom* g, void* p, size_t bytes, const hipStream_t* after = nullptr);
-void scratch_drop(const pet_os_geom* g);      // free what is kept
+// Device memory of a whole call (scratch.cpp): blocks are kept between calls, for
+// any geometry, thread and stream.  A block taken holds whatever the last call
+// left; work queued on s comes after that call's (s null: the host has waited
+// for it).  A call gives a block back once its stream is synchronized, or with
+// the work still queued on `after`.
+void* scratch_take(size_t bytes, const hipStream_t* s);
+void scratch_give(void* p, const hipStream_t* after = nullptr);
+void scratch_release();                       // free the idle blocks
+bool device_alloc(void** p, size_t bytes);    // hipMalloc, with the idle blocks freed if it fails
 
 // sums: with the partials of the sums over all bins (default U, nnz)
-// (keep: the scratch of a whole call, from and to the geometry's kept blocks)
+// (keep: the scratch of a whole call, from and to the kept blocks)
 int work_alloc(const pet_os_geom* g, bool need_nu, Work* w, bool sums = false, bool keep = false,
                const hipStream_t* s = nullptr);
 void work_free(Work* w);
@@ -408,6 +399,9 @@ void launch_batch3_pen(const SlotDev* d_slots, const Item* list, const int* cnt,
 }  // namespace petos
 
 namespace petos {
+// pet_os_objective; keep: its scratch from and to the kept blocks
+int objective(const pet_os_geom* g, const pet_os_params* p, const float* f, const float* y, const float* r, double* phi,
+              pet_os_stream stream, bool keep);
 // n_iter iterations of Table I on a state (no objective evaluations), queued on s
 int run_plain(pet_os_state* st, float* f, const float* y, const float* r, int n_iter, hipStream_t s);
 }  // namespace petos
@@ -434,7 +428,6 @@ struct pet_os_state {
     // 3D: bin-major copy of the (y, r) buffers yr_y, yr_r (made with the data
     // check, when the state may allocate)
     float2* yr = nullptr;
-    size_t yr_bytes = 0;
     const float* yr_y = nullptr;
     const float* yr_r = nullptr;
     bool may_allocate = true;

@@ -143,9 +143,8 @@ struct HipExecutor : Executor {
         return PET_OS_OK;
     }
     int objective(void* g, const pet_os_request& rq, double* phi) override {
-        const int rc = pet_os_objective((const pet_os_geom*)g, &rq.params, rq.f, rq.y, rq.r, phi, stream);
-        scratch_drop((const pet_os_geom*)g);    // (the budget counts none)
-        return rc;
+        // (scratch of its own: the budget counts no kept blocks)
+        return petos::objective((const pet_os_geom*)g, &rq.params, rq.f, rq.y, rq.r, phi, stream, false);
     }
     int remove(int slot) override { return pet_os_batch_remove(batch, slot, stream); }
     int reset() override {

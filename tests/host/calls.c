@@ -77,8 +77,39 @@ static void failed_call(void) {
     CHECK(stub_block(stub_last_copy) != used || !stub_pending(A) || stub_stream_waits > waits);
 }
 
+/* What whole calls keep is bounded over all geometries, yields to the library's
+ * own allocations and goes with the last geometry. */
+static void memory_kept(void) {
+    enum { N = 24 };
+    pet_os_geom* g[N];
+    pet_os_params p = params();
+    double phi;
+    const size_t before = stub_live;
+    size_t tables = 0;
+    for (int k = 0; k < N; ++k) {
+        g[k] = geometry(128 + 2 * k, 16, 60, 3, 8);
+        tables += stub_block_bytes(stub_last_malloc);
+    }
+    for (int k = 0; k < N; ++k) {
+        CHECK(pet_os_forward(g[k], buf, 0, buf, A) == PET_OS_OK);
+        CHECK(pet_os_objective(g[k], &p, buf, buf, buf, &phi, A) == PET_OS_OK);
+        CHECK(pet_os_subset_gradient(g[k], &p, buf, buf, buf, 0, buf, B) == PET_OS_OK);
+        CHECK(pet_os_back(g[k], buf, 1, buf, C) == PET_OS_OK);
+    }
+    CHECK(stub_live - tables - before <= (size_t)256 << 20);
+    CHECK(stub_live - tables - before > (size_t)1 << 20);
+    /* no memory left but what is kept: a geometry's tables get it */
+    stub_limit = stub_live;
+    pet_os_geom* one = geometry(128, 16, 60, 3, 8);
+    stub_limit = (size_t)1 << 34;
+    CHECK(pet_os_destroy_geometry(one) == PET_OS_OK);
+    for (int k = 0; k < N; ++k) CHECK(pet_os_destroy_geometry(g[k]) == PET_OS_OK);
+    CHECK(stub_live == before);
+}
+
 int main(int argc, char** argv) {
-    static const struct { const char* name; void (*run)(void); } all[] = {{"failed_call", failed_call}};
+    static const struct { const char* name; void (*run)(void); } all[] = {
+        {"failed_call", failed_call}, {"memory_kept", memory_kept}};
     for (size_t k = 0; argc > 1 && k < sizeof(all) / sizeof(all[0]); ++k)
         if (!strcmp(argv[1], all[k].name)) {
             all[k].run();

@@ -37,3 +37,10 @@ def test_a_failed_call_gives_back_scratch_in_order(program):
     """A call that runs out of memory gives back scratch that another stream's
     queued work still uses: the next call waits for it or takes other memory."""
     run(program, "failed_call")
+
+
+def test_kept_memory_is_bounded_over_all_geometries(program):
+    """At most 256 MiB per device stay with the library between calls, whatever
+    the number of geometries; its own allocations get them when memory is out,
+    and the last geometry's end frees them."""
+    run(program, "memory_kept")
