@@ -103,9 +103,9 @@ struct Work {
 
 // Device memory of a whole call (scratch.cpp): blocks are kept between calls, for
 // any geometry, thread and stream.  A block taken holds whatever the last call
-// left; work queued on s comes after that call's (s null: the host has waited
-// for it).  A call gives a block back once its stream is synchronized, or with
-// the work still queued on `after`.
+// left; that call's work is done, or comes before what is queued on s from now
+// on (s null: it is done).  A call gives a block back once its stream is
+// synchronized, or with the work still queued on `after`.
 void* scratch_take(size_t bytes, const hipStream_t* s);
 void scratch_give(void* p, const hipStream_t* after = nullptr);
 void scratch_release();                       // free the idle blocks

@@ -107,9 +107,31 @@ static void memory_kept(void) {
     CHECK(stub_live == before);
 }
 
+/* Calls on one stream don't wait for what another has queued, on the device or
+ * on the host, although they use scratch of the same sizes. */
+static void streams(void) {
+    pet_os_geom* g = geometry(64, 16, 64, 3, 8);
+    pet_os_params p = params();
+    double phi;
+    for (int n = 0; n < 3; ++n) {
+        CHECK(pet_os_back(g, buf, 0, buf, A) == PET_OS_OK);
+        CHECK(pet_os_back(g, buf, 0, buf, B) == PET_OS_OK);
+    }
+    CHECK(stub_stream_waits == 0 && stub_host_waits == 0 && stub_pending(A) && stub_pending(B));
+    CHECK(pet_os_objective(g, &p, buf, buf, buf, &phi, C) == PET_OS_OK);
+    CHECK(pet_os_forward(g, buf, 0, buf, C) == PET_OS_OK);
+    CHECK(pet_os_subset_gradient(g, &p, buf, buf, buf, 0, buf, C) == PET_OS_OK);
+    CHECK(pet_os_reconstruct(g, &p, buf, buf, buf, 1, NULL, C) == PET_OS_OK);
+    CHECK(stub_stream_waits == 0 && stub_pending(A) && stub_pending(B));
+    /* and a stream's own calls go on without more and more memory */
+    const long mallocs = stub_mallocs;
+    for (int n = 0; n < 20; ++n) CHECK(pet_os_back(g, buf, 0, buf, A) == PET_OS_OK);
+    CHECK(stub_mallocs - mallocs <= 3 && stub_stream_waits == 0);
+}
+
 int main(int argc, char** argv) {
     static const struct { const char* name; void (*run)(void); } all[] = {
-        {"failed_call", failed_call}, {"memory_kept", memory_kept}};
+        {"failed_call", failed_call}, {"memory_kept", memory_kept}, {"streams", streams}};
     for (size_t k = 0; argc > 1 && k < sizeof(all) / sizeof(all[0]); ++k)
         if (!strcmp(argv[1], all[k].name)) {
             all[k].run();

@@ -44,3 +44,9 @@ def test_kept_memory_is_bounded_over_all_geometries(program):
     the number of geometries; its own allocations get them when memory is out,
     and the last geometry's end frees them."""
     run(program, "memory_kept")
+
+
+def test_streams_do_not_wait_for_each_other(program):
+    """Back-projections on two streams, and whole calls on a third, take scratch
+    that no other stream's queued work uses."""
+    run(program, "streams")
