@@ -1076,10 +1076,11 @@ int pet_os_back(const pet_os_geom* g, const float* w, int32_t subset, float* out
     // bins (60480) 30.1 and 27.3, at 53x50x46 (64464) 36.3 and 27.5.
     if (g->d.dim == 3 && quad_ok(g) && (int64_t)B.n_al * g->n_planes * g->d.n_radial >= 32768) {
         // A call under capture, whose launches would use the scratch again and
-        // again, and one that finds no memory keep the kernel that needs none.
+        // again, and one that finds no room for it among the kept blocks (this
+        // call does not wait, so it cannot free) keep the kernel that needs none.
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         void* tmp = hipStreamIsCapturing(s, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone
-                        ? scratch_take(back3q_bytes(g, B.n_al), &s)
+                        ? scratch_take(back3q_bytes(g, B.n_al), &s, true)
                         : nullptr;
         if (tmp) {
             const int rc = launch_back3q(g, B, tmp, s);

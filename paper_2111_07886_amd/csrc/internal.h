@@ -105,8 +105,9 @@ struct Work {
 // any geometry, thread and stream.  A block taken holds whatever the last call
 // left; that call's work is done, or comes before what is queued on s from now
 // on (s null: it is done).  A call gives a block back once its stream is
-// synchronized, or with the work still queued on `after`.
-void* scratch_take(size_t bytes, const hipStream_t* s);
+// synchronized, or with the work still queued on `after`.  async: without a wait
+// or a release, now and when the block is given back (null: no room).
+void* scratch_take(size_t bytes, const hipStream_t* s, bool async = false);
 void scratch_give(void* p, const hipStream_t* after = nullptr);
 void scratch_release();                       // free the idle blocks
 bool device_alloc(void** p, size_t bytes);    // hipMalloc, with the idle blocks freed if it fails

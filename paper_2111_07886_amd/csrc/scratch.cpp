@@ -102,11 +102,15 @@ bool device_alloc(void** p, size_t bytes) {
 // a gap of 2 us between the kernels (back-projections of 127x125x29, 10 angles,
 // one after the other 60.7 us with one block, 58.6 with three): so the longest
 // idle of QUEUED blocks.
-void* scratch_take(size_t bytes, const hipStream_t* s) {
+//
+// A call that is asynchronous (async) takes no block that it would have to free
+// or wait for: none if there is no room among the kept ones.
+void* scratch_take(size_t bytes, const hipStream_t* s, bool async) {
     constexpr int QUEUED = 3;
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) return nullptr;
     bool kept = false;
+    unsigned long long tag = 0;
     std::vector<Block> old;
     Block got;
     {
@@ -124,10 +128,20 @@ void* scratch_take(size_t bytes, const hipStream_t* s) {
         }
         Block* take = done;
         if (take == nullptr && (fits >= QUEUED || !has_room(dev, bytes, nullptr))) take = mine;
-        if (take == nullptr) kept = has_room(dev, bytes, &old);
+        if (take == nullptr) kept = has_room(dev, bytes, async ? nullptr : &old);
         if (take != nullptr) {
             take->lent = true;
             got = *take;
+        } else if (kept) {
+            // (its place, before the memory)
+            Block b;
+            b.bytes = bytes;
+            b.device = dev;
+            b.lent = true;
+            tag = b.use = ++g_use;
+            g_blocks.push_back(b);
+        } else if (async) {
+            return nullptr;
         }
     }
     if (got.p != nullptr) {
@@ -137,20 +151,21 @@ void* scratch_take(size_t bytes, const hipStream_t* s) {
     }
     free_blocks(old);
     void* p = nullptr;
-    if (!device_alloc(&p, bytes)) return nullptr;
+    if (!async) {
+        (void)device_alloc(&p, bytes);
+    } else if (hipMalloc(&p, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        p = nullptr;
+    }
     if (kept) {
-        // (another thread may have taken the room: then the block is not kept)
         std::lock_guard<std::mutex> lk(g_mu);
-        if (has_room(dev, bytes, &old)) {
-            Block b;
-            b.p = p;
-            b.bytes = bytes;
-            b.device = dev;
-            b.lent = true;
-            g_blocks.push_back(b);
+        for (auto it = g_blocks.begin(); it != g_blocks.end(); ++it) {
+            if (it->p != nullptr || it->use != tag) continue;
+            if (p != nullptr) it->p = p;
+            else g_blocks.erase(it);
+            break;
         }
     }
-    free_blocks(old);
     return p;
 }
 

@@ -129,9 +129,33 @@ static void streams(void) {
     CHECK(stub_mallocs - mallocs <= 3 && stub_stream_waits == 0);
 }
 
+/* A back-projection is asynchronous whatever memory there is: where the kept
+ * blocks are all in use it takes the kernel that needs none. */
+static void asynchronous(void) {
+    enum { N = 40 };
+    static int s[N];
+    pet_os_geom* g = geometry(256, 16, 60, 3, 1);
+    const size_t before = stub_live;
+    for (int k = 0; k < N; ++k) {
+        CHECK(pet_os_back(g, buf, 0, buf, &s[k]) == PET_OS_OK);
+        CHECK(stub_pending(&s[k]));
+    }
+    CHECK(stub_host_waits == 0 && stub_stream_waits == 0 && stub_frees == 0);
+    CHECK(stub_live - before <= (size_t)256 << 20);
+    const int columns = stub_launches_of("k_bp3I"), quads = stub_launches_of("k_bp3q");
+    CHECK(columns > 0 && quads > 0);
+    /* no memory at all */
+    for (int k = 0; k < N; ++k) stub_finish(&s[k]);
+    pet_os_geom* h = geometry(400, 16, 60, 3, 1);
+    stub_limit = stub_live;
+    CHECK(pet_os_back(h, buf, 0, buf, A) == PET_OS_OK);
+    CHECK(stub_pending(A) && stub_host_waits == 0 && stub_frees == 0);
+}
+
 int main(int argc, char** argv) {
     static const struct { const char* name; void (*run)(void); } all[] = {
-        {"failed_call", failed_call}, {"memory_kept", memory_kept}, {"streams", streams}};
+        {"failed_call", failed_call}, {"memory_kept", memory_kept}, {"streams", streams},
+        {"asynchronous", asynchronous}};
     for (size_t k = 0; argc > 1 && k < sizeof(all) / sizeof(all[0]); ++k)
         if (!strcmp(argv[1], all[k].name)) {
             all[k].run();

@@ -50,3 +50,9 @@ def test_streams_do_not_wait_for_each_other(program):
     """Back-projections on two streams, and whole calls on a third, take scratch
     that no other stream's queued work uses."""
     run(program, "streams")
+
+
+def test_a_back_projection_stays_asynchronous(program):
+    """A back-projection neither waits nor frees, whatever its scratch finds: 40
+    streams at once, more than the kept blocks hold, and no memory left."""
+    run(program, "asynchronous")
