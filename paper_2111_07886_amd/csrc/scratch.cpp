@@ -31,6 +31,16 @@ struct Block {
     unsigned long long use = 0;     // larger: given back later
 };
 
+// While another stream of this thread (or, in global mode, of any) is being
+// captured, allocations, releases and event queries end that capture with an
+// error unless the thread is in relaxed mode.  No call here queues anything on a
+// capturing stream.
+struct Relaxed {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
 std::mutex g_mu;                    // never held across a call that waits
 std::vector<Block> g_blocks;
 unsigned long long g_use = 0;
@@ -107,6 +117,7 @@ bool device_alloc(void** p, size_t bytes) {
 // or wait for: none if there is no room among the kept ones.
 void* scratch_take(size_t bytes, const hipStream_t* s, bool async) {
     constexpr int QUEUED = 3;
+    const Relaxed relaxed;
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) return nullptr;
     bool kept = false;
@@ -170,6 +181,7 @@ void* scratch_take(size_t bytes, const hipStream_t* s, bool async) {
 }
 
 void scratch_give(void* p, const hipStream_t* after) {
+    const Relaxed relaxed;
     hipEvent_t ev = nullptr;
     bool kept = false;
     {

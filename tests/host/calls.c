@@ -152,10 +152,18 @@ static void asynchronous(void) {
     CHECK(stub_pending(A) && stub_host_waits == 0 && stub_frees == 0);
 }
 
+/* A back-projection does not break the capture of another stream. */
+static void beside_a_capture(void) {
+    pet_os_geom* g = geometry(64, 16, 64, 3, 8);
+    stub_capturing = 1;
+    for (int n = 0; n < 5; ++n) CHECK(pet_os_back(g, buf, 0, buf, A) == PET_OS_OK);
+    CHECK(stub_capture_breaks == 0);
+}
+
 int main(int argc, char** argv) {
     static const struct { const char* name; void (*run)(void); } all[] = {
         {"failed_call", failed_call}, {"memory_kept", memory_kept}, {"streams", streams},
-        {"asynchronous", asynchronous}};
+        {"asynchronous", asynchronous}, {"beside_a_capture", beside_a_capture}};
     for (size_t k = 0; argc > 1 && k < sizeof(all) / sizeof(all[0]); ++k)
         if (!strcmp(argv[1], all[k].name)) {
             all[k].run();

@@ -56,3 +56,9 @@ def test_a_back_projection_stays_asynchronous(program):
     """A back-projection neither waits nor frees, whatever its scratch finds: 40
     streams at once, more than the kept blocks hold, and no memory left."""
     run(program, "asynchronous")
+
+
+def test_a_back_projection_beside_a_capture(program):
+    """A back-projection on one stream makes no call that ends the capture of
+    another stream (global capture mode forbids allocations and event queries)."""
+    run(program, "beside_a_capture")
