@@ -62,6 +62,8 @@ struct pet_os_batch {
     int grids[WL_COUNT] = {};
     size_t bp3q_lds = 0;             // dynamic LDS of the quad back-projection: the largest of the slots'
     bool lists_dirty = true;
+    int ahead = 0;                   // steps queued since the device's counters last moved
+    unsigned updated = 0;            // of a step that failed halfway: the lists whose iterates it wrote
     size_t bytes = 0;
 };
 
@@ -76,6 +78,14 @@ void slot_release(BatchSlot& s) {
         if (s.d_nu) (void)hipFree(s.d_nu);
     }
     s = BatchSlot{};
+}
+
+// move the device's counters past the steps queued since they last moved
+int batch_settle(pet_os_batch* B, hipStream_t st) {
+    if (B->ahead == 0) return PET_OS_OK;
+    const int rc = launch_batch_advance(B->d_slots, B->max_slots, B->ahead, st);
+    if (!rc) B->ahead = 0;
+    return rc;
 }
 
 int upload_slot(pet_os_batch* B, int idx) {
@@ -376,6 +386,11 @@ int pet_os_batch_add(pet_os_batch* B, const pet_os_geom* g, const pet_os_params*
         if (!B->slots[s].used) { idx = s; break; }
     if (idx < 0) return fail(PET_OS_ERR_BUDGET, "no free slot");
     hipStream_t st = (hipStream_t)stream;
+    if ((rc = batch_settle(B, st))) return rc;
+    if (B->updated != 0) {
+        // (a step that failed halfway is none of the new request's)
+        if ((rc = pet_os_batch_step(B, 1, stream))) return rc;
+    }
     PETOS_HIP(hipStreamSynchronize(st));       // the slot table is read by queued steps
 
     BatchSlot S;
@@ -443,24 +458,31 @@ int pet_os_batch_remove(pet_os_batch* B, int32_t slot, pet_os_stream stream) {
 int pet_os_batch_step(pet_os_batch* B, int32_t n_steps, pet_os_stream stream) {
     if (!B || n_steps < 0) return fail(PET_OS_ERR_INVALID_ARG, "bad argument");
     hipStream_t st = (hipStream_t)stream;
-    int rc;
+    int rc = PET_OS_OK;
     // (a step is not for a caller's own graph: the host counts the steps)
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     PETOS_HIP(hipStreamIsCapturing(st, &cs));
     if (cs != hipStreamCaptureStatusNone) return fail(PET_OS_ERR_DEVICE, "batch step on a capturing stream");
-    if (B->lists_dirty) {
+    if ((rc = batch_settle(B, st))) return rc;
+    if (B->lists_dirty && B->updated == 0) {
         PETOS_HIP(hipStreamSynchronize(st));
         if ((rc = rebuild_lists(B))) return rc;
     }
     // Launched one by one: queued kernels of a stream follow each other without
     // a gap, where a graph of one step (3 to 9 kernels) left 8 us before each
     // of its launches, more than a kernel's launch costs the host.
-    for (int n = 0; n < n_steps; ++n)
-        if ((rc = launch_batch_step(B->d_slots, n, B->d_items, B->d_counts, B->grids, B->bp3q_lds, st))) return rc;
-    if (n_steps > 0 && (rc = launch_batch_advance(B->d_slots, B->max_slots, n_steps, st))) return rc;
+    // A step that fails is not counted and goes on where it stopped when the
+    // caller tries again; those before it are.
+    int n = 0;
+    for (; n < n_steps && !rc; ++n) {
+        rc = launch_batch_step(B->d_slots, B->ahead, B->d_items, B->d_counts, B->grids, B->bp3q_lds, &B->updated, st);
+        if (rc) break;
+        ++B->ahead;
+    }
     for (auto& s : B->slots)
-        if (s.used) s.J_next = std::min<int64_t>(s.J_end + 1, s.J_next + n_steps);
-    return PET_OS_OK;
+        if (s.used) s.J_next = std::min<int64_t>(s.J_end + 1, s.J_next + n);
+    const int arc = batch_settle(B, st);
+    return rc ? rc : arc;
 }
 
 int pet_os_batch_run(pet_os_batch* B, pet_os_stream stream) {

@@ -383,8 +383,10 @@ enum { WL_FP = 0, WL_BP0 = 1, WL_BP1 = 2, WL_FP3 = 3, WL_BP3 = 4, WL_UPD3 = 10, 
 // Queue one batched subiteration, the step-th since the slots' counters moved:
 // forward, back-projection (one launch per tile kind), update.  Empty lists
 // (no grid) are not launched.  launch_batch_advance moves the counters on.
+// updated: the lists (bits) whose iterates a failed attempt at this step has
+// written already, which are left out; 0 after a whole step.
 int launch_batch_step(const SlotDev* d_slots, int step, Item* const lists[WL_COUNT], const int* d_counts,
-                      const int grids[WL_COUNT], size_t bp3q_lds_bytes, hipStream_t s);
+                      const int grids[WL_COUNT], size_t bp3q_lds_bytes, unsigned* updated, hipStream_t s);
 int launch_batch_advance(SlotDev* d_slots, int n_slots, int n, hipStream_t s);
 void launch_batch3q_fp(const SlotDev* d_slots, const Item* list, const int* cnt, int grid, int step, int kl,
                        hipStream_t s);

@@ -1698,7 +1698,7 @@ int launch_batch_advance(SlotDev* d_slots, int n_slots, int n, hipStream_t s) {
 }
 
 int launch_batch_step(const SlotDev* d_slots, int step, Item* const lists[WL_COUNT], const int* d_counts,
-                      const int grids[WL_COUNT], size_t bp3q_lds_bytes, hipStream_t s) {
+                      const int grids[WL_COUNT], size_t bp3q_lds_bytes, unsigned* updated, hipStream_t s) {
     auto live = [&](int k) { return grids[k] > 0; };
     if (live(WL_FP))
         hipLaunchKernelGGL(k_fp_batch, dim3(grids[WL_FP]), dim3(NT), 0, s, d_slots, lists[WL_FP], d_counts + WL_FP,
@@ -1708,15 +1708,6 @@ int launch_batch_step(const SlotDev* d_slots, int step, Item* const lists[WL_COU
         if (live(WL_FP3Q + k))
             launch_batch3q_fp(d_slots, lists[WL_FP3Q + k], d_counts + WL_FP3Q + k, grids[WL_FP3Q + k], step,
                               k ? 64 : 32, s);
-    if (live(WL_BP0))
-        hipLaunchKernelGGL((k_bp_batch<Tile2L>), dim3(grids[WL_BP0]), dim3(NT), bp_lds_budget(0), s, d_slots,
-                           lists[WL_BP0], d_counts + WL_BP0, step);
-    if (live(WL_BP1))
-        hipLaunchKernelGGL((k_bp_batch<Tile2S>), dim3(grids[WL_BP1]), dim3(NT), bp_lds_budget(1), s, d_slots,
-                           lists[WL_BP1], d_counts + WL_BP1, step);
-    if (live(WL_BPW))
-        hipLaunchKernelGGL(k_bpw_batch, dim3(grids[WL_BPW]), dim3(NT), 0, s, d_slots, lists[WL_BPW],
-                           d_counts + WL_BPW, step);
     const int zbs[3] = {16, 32, 64};
     for (int k = 0; k < 6; ++k)
         if (live(WL_BP3 + k))
@@ -1727,8 +1718,24 @@ int launch_batch_step(const SlotDev* d_slots, int step, Item* const lists[WL_COU
             launch_batch3q_bp(d_slots, lists[WL_BP3Q + k], d_counts + WL_BP3Q + k, grids[WL_BP3Q + k], step,
                               k ? 64 : 32, bp3q_lds_bytes, s);
     if (live(WL_PEN3)) launch_batch3_pen(d_slots, lists[WL_PEN3], d_counts + WL_PEN3, grids[WL_PEN3], step, s);
-    if (live(WL_UPD3)) launch_batch3_upd(d_slots, lists[WL_UPD3], d_counts + WL_UPD3, grids[WL_UPD3], step, s);
+    // what is queued so far can be queued again; what follows writes iterates
     PETOS_HIP(hipGetLastError());
+    for (int k : {(int)WL_BP0, (int)WL_BP1, (int)WL_BPW, (int)WL_UPD3}) {
+        if (!live(k) || ((*updated >> k) & 1u)) continue;
+        if (k == WL_BP0)
+            hipLaunchKernelGGL((k_bp_batch<Tile2L>), dim3(grids[k]), dim3(NT), bp_lds_budget(0), s, d_slots, lists[k],
+                               d_counts + k, step);
+        else if (k == WL_BP1)
+            hipLaunchKernelGGL((k_bp_batch<Tile2S>), dim3(grids[k]), dim3(NT), bp_lds_budget(1), s, d_slots, lists[k],
+                               d_counts + k, step);
+        else if (k == WL_BPW)
+            hipLaunchKernelGGL(k_bpw_batch, dim3(grids[k]), dim3(NT), 0, s, d_slots, lists[k], d_counts + k, step);
+        else
+            launch_batch3_upd(d_slots, lists[k], d_counts + k, grids[k], step, s);
+        PETOS_HIP(hipGetLastError());
+        *updated |= 1u << k;
+    }
+    *updated = 0;
     return PET_OS_OK;
 }
 

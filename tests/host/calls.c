@@ -160,10 +160,47 @@ static void beside_a_capture(void) {
     CHECK(stub_capture_breaks == 0);
 }
 
+/* A batch whose step fails keeps its count: the steps queued before it are
+ * counted, and its updates are not queued again. */
+static void failed_step(void) {
+    enum { N = 2, STEPS = 12 };
+    static float y[1 << 20];
+    pet_os_geom* g[N] = {geometry(64, 1, 60, 0, 4), geometry(64, 16, 24, 3, 4)};
+    pet_os_params p = params();
+    const char* forward[] = {"k_fp_batch", "k_fp3q_batch"};
+    const char* update[] = {"k_bp_batch", "k_upd3_batch"};
+    for (int bad = 0; bad < 13; ++bad) {
+        pet_os_batch* b = NULL;
+        int32_t slot, active;
+        int64_t left, was[2];
+        CHECK(pet_os_batch_create(4, &b) == PET_OS_OK);
+        for (int k = 0; k < N; ++k) CHECK(pet_os_batch_add(b, g[k], &p, y, y, y, 3, A, &slot) == PET_OS_OK);
+        CHECK(pet_os_batch_step(b, 1, A) == PET_OS_OK);
+        for (int k = 0; k < N; ++k) was[k] = stub_launches_of(update[k]) - 1;
+        const int f0 = stub_launches_of(forward[0]) - 1;
+        /* launch number `bad` of the next ones fails */
+        stub_fail_launch = stub_launches + bad;
+        CHECK(pet_os_batch_step(b, 2, A) == PET_OS_ERR_DEVICE);
+        stub_fail_launch = -1;
+        hipGetLastError();
+        CHECK(pet_os_batch_slot_status(b, 0, &active, &left) == PET_OS_OK);
+        const int done = stub_launches_of(update[0]) - (int)was[0], dun = stub_launches_of(update[1]) - (int)was[1];
+        const int steps = done < dun ? done : dun;
+        CHECK(left == STEPS - steps);
+        /* to the end: every update once */
+        CHECK(pet_os_batch_run(b, A) == PET_OS_OK);
+        CHECK(pet_os_batch_slot_status(b, 1, &active, &left) == PET_OS_OK && left == 0 && !active);
+        for (int k = 0; k < N; ++k) CHECK(stub_launches_of(update[k]) - was[k] == STEPS);
+        CHECK(stub_launches_of(forward[0]) - f0 >= STEPS);
+        CHECK(pet_os_batch_destroy(b) == PET_OS_OK);
+    }
+}
+
 int main(int argc, char** argv) {
     static const struct { const char* name; void (*run)(void); } all[] = {
         {"failed_call", failed_call}, {"memory_kept", memory_kept}, {"streams", streams},
-        {"asynchronous", asynchronous}, {"beside_a_capture", beside_a_capture}};
+        {"asynchronous", asynchronous}, {"beside_a_capture", beside_a_capture},
+        {"failed_step", failed_step}};
     for (size_t k = 0; argc > 1 && k < sizeof(all) / sizeof(all[0]); ++k)
         if (!strcmp(argv[1], all[k].name)) {
             all[k].run();

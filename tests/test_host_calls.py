@@ -62,3 +62,9 @@ def test_a_back_projection_beside_a_capture(program):
     """A back-projection on one stream makes no call that ends the capture of
     another stream (global capture mode forbids allocations and event queries)."""
     run(program, "beside_a_capture")
+
+
+def test_a_failed_batch_step_is_taken_up_again(program):
+    """A launch that fails, at every place of two batched steps: the steps before
+    it are counted, and running on updates each request once per step."""
+    run(program, "failed_step")
