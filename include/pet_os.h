@@ -421,7 +421,10 @@ typedef struct {
 } pet_os_server_stats_t;
 
 /* A server on the current device with its own streams; hbm_budget_bytes caps
- * the device memory it allocates, max_slots the concurrent requests. */
+ * the device memory it allocates, max_slots the concurrent requests.  A result
+ * is that of pet_os_reconstruct bit for bit, but within rounding where a 3D
+ * request's scratch fits the whole budget only with the subset sinogram bin by
+ * bin (the 3D projectors' own layout takes up to 2.2 times that). */
 int pet_os_server_create(size_t hbm_budget_bytes, int32_t max_slots, pet_os_server** out);
 /* Finishes every queued and running request, then stops. */
 int pet_os_server_destroy(pet_os_server* server);

@@ -43,6 +43,7 @@ struct BatchSlot {
     int* d_nu = nullptr;
     bool owned = true;               // w, d_step and d_nu are this slot's (else parts of the batch's slab)
     int fp_seg = 1, bp_kind = 0;
+    bool quad = false;               // 3D: w in quads of mirror rays
     size_t bytes = 0;
 };
 
@@ -153,7 +154,7 @@ int rebuild_lists(pet_os_batch* B) {
         const bool d3 = S.g->d.dim == 3;
         // 2D: forward blocks, then the pixel-pass blocks (snapshot, mu)
         // (the forward projector that gives the bits of a request alone)
-        const bool quad = d3 && quad_ok(S.g), fq = d3 && fp3q_ok(S.g) && (quad || !fp3s_better(S.g));
+        const bool quad = S.quad, fq = d3 && fp3q_ok(S.g) && (quad || !fp3s_better(S.g));
         const int wide = S.g->d.nz > 32 ? 1 : 0;
         const int nfp = fq ? fp3q_grid(S.g, S.g->max_sub_angles)
                         : d3 ? fp3_grid(S.g, S.g->max_sub_angles)
@@ -252,7 +253,7 @@ int slot_record(BatchSlot& S, const GeomExtra* ex, SlotDev& D) {
     D.box = make_box(p->U, p->t_clip);
     D.fp_seg = S.fp_seg;
     D.bp_kind = S.bp_kind;
-    if (g->d.dim == 3 && quad_ok(g)) {
+    if (S.quad) {
         D.quad = 1;
         D.rows_max = bp3q_rows(g);
         D.chunk = bp3q_buf(g);
@@ -306,6 +307,7 @@ int add_together(pet_os_batch* B, int n, const pet_os_geom* const* geoms, const 
         S.y = y[k];
         S.r = r[k];
         S.J_end = (int64_t)n_iter[k] * S.g->d.n_subsets;
+        S.quad = quad_ok(S.g);
         work_carve_at(S.g, need_nu(k), base + o_work[k], &S.w);
         rc = check_launch(S.g, &S.p, S.w.check_part, totals + 4 * (size_t)k, S.f, S.y, S.r, st);
         if (!rc) rc = launch_sum_f(S.g, S.f, S.w.fz, S.w.red[RED_SUMF], st);
@@ -374,6 +376,13 @@ int pet_os_batch_destroy(pet_os_batch* B) {
 
 int pet_os_batch_add(pet_os_batch* B, const pet_os_geom* g, const pet_os_params* p, float* f, const float* y,
                      const float* r, int32_t n_iter, pet_os_stream stream, int32_t* slot_out) {
+    return batch_add(B, g, p, f, y, r, n_iter, stream, slot_out, false);
+}
+
+}  // extern "C"
+
+int petos::batch_add(pet_os_batch* B, const pet_os_geom* g, const pet_os_params* p, float* f, const float* y,
+                     const float* r, int32_t n_iter, pet_os_stream stream, int32_t* slot_out, bool compact) {
     if (!B || !g || !p || !f || !y || !r) return fail(PET_OS_ERR_INVALID_ARG, "NULL argument");
     if (n_iter < 1) return fail(PET_OS_ERR_INVALID_ARG, "n_iter must be >= 1");
     GeomExtra* ex = extra_of(g);
@@ -403,7 +412,8 @@ int pet_os_batch_add(pet_os_batch* B, const pet_os_geom* g, const pet_os_params*
     S.J_next = 1;
     S.J_end = (int64_t)n_iter * M;
     const bool need_nu = p->mode == PET_OS_P1 || p->mode == PET_OS_P2;
-    rc = work_alloc(g, need_nu, &S.w);
+    S.quad = quad_ok(g) && !compact;
+    rc = work_alloc(g, need_nu, &S.w, false, false, nullptr, S.quad);
     if (rc) return rc;
     if ((rc = check_data(g, p, &S.w, f, y, r, st))) {
         work_free(&S.w);
@@ -441,6 +451,8 @@ int pet_os_batch_add(pet_os_batch* B, const pet_os_geom* g, const pet_os_params*
     if (slot_out) *slot_out = idx;
     return PET_OS_OK;
 }
+
+extern "C" {
 
 int pet_os_batch_remove(pet_os_batch* B, int32_t slot, pet_os_stream stream) {
     if (!B || slot < 0 || slot >= B->max_slots || !B->slots[slot].used)

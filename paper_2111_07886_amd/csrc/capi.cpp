@@ -527,9 +527,19 @@ void work_carve_at(const pet_os_geom* g, bool need_nu, void* base, Work* w) {
     work_carve(work_layout(g, need_nu, false), (char*)base, w);
 }
 
-int work_alloc(const pet_os_geom* g, bool need_nu, Work* w, bool sums, bool keep, const hipStream_t* s) {
+size_t work_bytes_of(const pet_os_geom_desc& d, int n_planes, int max_sub, bool need_nu, bool quads) {
+    pet_os_geom g{};
+    g.d = d;
+    g.n_planes = n_planes;
+    g.n_vox = (int64_t)d.nx * d.ny * d.nz;
+    g.n_bins = (int64_t)n_planes * d.n_angles * d.n_radial;
+    g.max_sub_angles = max_sub;
+    return work_layout(&g, need_nu, false, quads).bytes;
+}
+
+int work_alloc(const pet_os_geom* g, bool need_nu, Work* w, bool sums, bool keep, const hipStream_t* s, bool quads) {
     *w = Work{};
-    const WorkLayout L = work_layout(g, need_nu, sums);
+    const WorkLayout L = work_layout(g, need_nu, sums, quads);
     char* blk = nullptr;
     if (keep) {
         blk = (char*)scratch_take(L.bytes, s);

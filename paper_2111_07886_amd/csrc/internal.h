@@ -113,9 +113,12 @@ void scratch_release();                       // free the idle blocks
 bool device_alloc(void** p, size_t bytes);    // hipMalloc, with the idle blocks freed if it fails
 
 // sums: with the partials of the sums over all bins (default U, nnz)
-// (keep: the scratch of a whole call, from and to the kept blocks)
+// (keep: the scratch of a whole call, from and to the kept blocks; quads: room
+// for the subset sinogram as quads where the geometry takes them)
 int work_alloc(const pet_os_geom* g, bool need_nu, Work* w, bool sums = false, bool keep = false,
-               const hipStream_t* s = nullptr);
+               const hipStream_t* s = nullptr, bool quads = true);
+// its bytes, from a descriptor
+size_t work_bytes_of(const pet_os_geom_desc& d, int n_planes, int max_sub, bool need_nu, bool quads);
 void work_free(Work* w);
 // bytes of one request's scratch, and the same scratch placed in caller
 // memory at base (cap bytes, 256-byte aligned): no allocation; the reduction
@@ -405,6 +408,10 @@ namespace petos {
 // pet_os_objective; keep: its scratch from and to the kept blocks
 int objective(const pet_os_geom* g, const pet_os_params* p, const float* f, const float* y, const float* r, double* phi,
               pet_os_stream stream, bool keep);
+// pet_os_batch_add; compact: with the subset sinogram bin by bin, whatever the
+// geometry takes
+int batch_add(pet_os_batch* batch, const pet_os_geom* geom, const pet_os_params* params, float* f, const float* y,
+              const float* r, int32_t n_iter, pet_os_stream stream, int32_t* slot, bool compact);
 // n_iter iterations of Table I on a state (no objective evaluations), queued on s
 int run_plain(pet_os_state* st, float* f, const float* y, const float* r, int n_iter, hipStream_t s);
 }  // namespace petos

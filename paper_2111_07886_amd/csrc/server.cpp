@@ -61,6 +61,7 @@ struct Req {
     int64_t remaining = 0;        // subiterations left
     std::string geo_key;
     size_t bytes = 0;             // scratch + schedule charged to the budget
+    bool compact = false;         // 3D: runs with the subset sinogram bin by bin
 };
 
 std::string desc_key(const pet_os_geom_desc& d) {
@@ -71,9 +72,9 @@ std::string desc_key(const pet_os_geom_desc& d) {
     return buf;
 }
 
-// bytes of one request's scratch and schedule, as the budget counts them: the
-// subset sinogram bin by bin (3D quads may take up to 2.2 times that)
-size_t request_bytes(const pet_os_geom_desc& d, int n_planes, int max_sub, int n_iter, bool nu) {
+// the least bytes of one request's scratch and schedule: a request for which
+// these exceed the whole budget is refused
+size_t least_bytes(const pet_os_geom_desc& d, int n_planes, int max_sub, int n_iter, bool nu) {
     const size_t nv = (size_t)d.nx * d.ny * (d.dim == 3 ? d.nz : 1);
     const size_t nb = (size_t)n_planes * d.n_angles * d.n_radial;
     size_t b = (size_t)max_sub * n_planes * d.n_radial * 4 + nv * 4 * (nu ? 4 : 3);
@@ -100,7 +101,7 @@ struct Executor {
     // geometry for a descriptor (created on first use); *bytes = device bytes held
     virtual int geometry(const pet_os_geom_desc& d, void** g, size_t* bytes) = 0;
     virtual void drop_geometry(void* g) = 0;
-    virtual int add(void* g, const pet_os_request& rq, int* slot) = 0;
+    virtual int add(void* g, const pet_os_request& rq, bool compact, int* slot) = 0;
     virtual int step() = 0;                       // one batched subiteration (asynchronous)
     virtual int sync() = 0;                       // wait for queued steps
     virtual int objective(void* g, const pet_os_request& rq, double* phi) = 0;
@@ -134,8 +135,8 @@ struct HipExecutor : Executor {
         return PET_OS_OK;
     }
     void drop_geometry(void* g) override { pet_os_destroy_geometry((pet_os_geom*)g); }
-    int add(void* g, const pet_os_request& rq, int* slot) override {
-        return pet_os_batch_add(batch, (const pet_os_geom*)g, &rq.params, rq.f, rq.y, rq.r, rq.n_iter, stream, slot);
+    int add(void* g, const pet_os_request& rq, bool compact, int* slot) override {
+        return batch_add(batch, (const pet_os_geom*)g, &rq.params, rq.f, rq.y, rq.r, rq.n_iter, stream, slot, compact);
     }
     int step() override { return pet_os_batch_step(batch, 1, stream); }
     int sync() override {
@@ -169,7 +170,7 @@ struct SimExecutor : Executor {
         return PET_OS_OK;
     }
     void drop_geometry(void* g) override { delete (pet_os_geom_desc*)g; }
-    int add(void*, const pet_os_request&, int* slot) override {
+    int add(void*, const pet_os_request&, bool, int* slot) override {
         if (fail_add > 0) { --fail_add; return fail(PET_OS_ERR_OUT_OF_MEMORY, "injected: out of memory on admission"); }
         if (bad_data > 0) { --bad_data; return fail(PET_OS_ERR_INVALID_ARG, "injected: r: 1 entries not > 0 or not finite"); }
         for (int s = 0; s < max_slots; ++s)
@@ -305,15 +306,23 @@ bool pet_os_server::try_admit(int lane, std::unique_lock<std::mutex>& lk) {
     const int np = n_planes_desc(d);
     const int max_sub = (d.n_angles + d.n_subsets - 1) / d.n_subsets;
     const bool nu = r->rq.params.mode == PET_OS_P1 || r->rq.params.mode == PET_OS_P2;
-    r->bytes = request_bytes(d, np, max_sub, r->rq.n_iter, nu);
     auto git = geos.find(r->geo_key);
     const size_t gbytes = git == geos.end() ? geometry_bytes(d, np) : 0;
-    if (r->bytes + gbytes > budget) {
+    const size_t own = git == geos.end() ? gbytes : git->second.bytes;
+    if (least_bytes(d, np, max_sub, r->rq.n_iter, nu) + own > budget) {
         queue.erase(qit);
         finish(r, PET_OS_ERR_BUDGET, "request needs more device memory than the whole budget");
         cv_done.notify_all();
         return true;
     }
+    // What the request will allocate.  Where the 3D projectors' layout of the
+    // subset sinogram (up to 2.2 times its bins) would not fit the whole budget
+    // it runs bin by bin; and one that is only by the roundings of least_bytes
+    // within the budget gets all of it.
+    const size_t sched = (size_t)r->rq.n_iter * d.n_subsets * (sizeof(float) + sizeof(int));
+    r->bytes = work_bytes_of(d, np, max_sub, nu, true) + sched;
+    r->compact = r->bytes + own > budget;
+    if (r->compact) r->bytes = std::min(work_bytes_of(d, np, max_sub, nu, false) + sched, budget - own);
     if (used_bytes + r->bytes + gbytes > budget) evict_unused(r->bytes + gbytes);
     if (used_bytes + r->bytes + gbytes > budget) return false;      // wait for running requests to leave
     queue.erase(qit);
@@ -362,7 +371,7 @@ bool pet_os_server::try_admit(int lane, std::unique_lock<std::mutex>& lk) {
     lk.unlock();
     if (!rc) {
         std::lock_guard<std::mutex> api(api_mu);
-        rc = ex->add(ge->g, r->rq, &slot);
+        rc = ex->add(ge->g, r->rq, r->compact, &slot);
     }
     lk.lock();
     --admitting;
