@@ -258,7 +258,7 @@ struct pet_os_server {
     void run(int lane);
     void finish(const std::shared_ptr<Req>& r, int status, const std::string& msg);
     bool try_admit(int lane, std::unique_lock<std::mutex>& lk);
-    void evict_unused(size_t need);
+    void evict_unused(size_t need, const std::string& but);
 };
 
 void pet_os_server::finish(const std::shared_ptr<Req>& r, int status, const std::string& msg) {
@@ -268,11 +268,12 @@ void pet_os_server::finish(const std::shared_ptr<Req>& r, int status, const std:
     r->done = true;
 }
 
-void pet_os_server::evict_unused(size_t need) {
+// (but: the key of a geometry that stays)
+void pet_os_server::evict_unused(size_t need, const std::string& but) {
     while (used_bytes + need > budget) {
         auto victim = geos.end();
         for (auto it = geos.begin(); it != geos.end(); ++it)
-            if (it->second.refs == 0 && (victim == geos.end() || it->second.last_use < victim->second.last_use))
+            if (it->second.refs == 0 && it->first != but && (victim == geos.end() || it->second.last_use < victim->second.last_use))
                 victim = it;
         if (victim == geos.end()) return;
         {
@@ -323,7 +324,7 @@ bool pet_os_server::try_admit(int lane, std::unique_lock<std::mutex>& lk) {
     r->bytes = work_bytes_of(d, np, max_sub, nu, true) + sched;
     r->compact = r->bytes + own > budget;
     if (r->compact) r->bytes = std::min(work_bytes_of(d, np, max_sub, nu, false) + sched, budget - own);
-    if (used_bytes + r->bytes + gbytes > budget) evict_unused(r->bytes + gbytes);
+    if (used_bytes + r->bytes + gbytes > budget) evict_unused(r->bytes + gbytes, r->geo_key);
     if (used_bytes + r->bytes + gbytes > budget) return false;      // wait for running requests to leave
     queue.erase(qit);
     r->res.t_admit = now();

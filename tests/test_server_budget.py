@@ -1,7 +1,8 @@
 """The server's device-memory budget: a request is charged what it allocates, in
-3D with the projectors' own layout of the subset sinogram, and one that fits the
-whole budget only bin by bin is taken and charged for that.  (Simulated executor;
-the device runs the tight budget too.)"""
+3D with the projectors' own layout of the subset sinogram; one that fits the
+whole budget only bin by bin is taken and charged for that; and the geometry
+that a request is about to use is not evicted for it.  (Simulated executor; the
+device runs the tight budget too.)"""
 import time
 
 import numpy as np
@@ -66,6 +67,18 @@ def test_a_tight_budget_takes_the_request_bin_by_bin(pet):
         time.sleep(0.0005)
     assert all(S.wait(t)["status"] == 0 for t in ts)
     assert geo < most <= budget and S.stats()["max_active"] == 1
+    S.close()
+
+
+def test_its_own_geometry_is_not_evicted(pet):
+    """A longer request of the only cached geometry, when memory is short: that
+    geometry stays (it had been looked up before the eviction)."""
+    d, p = desc(), configs.params_3d()
+    per, geo = charged(pet, d, p)
+    S = pet.Server(per + 4096, 4, simulate=True, step_us=10)
+    for n in (2, 1000, 2):                  # (the long schedule is 16 KB more)
+        assert S.wait(S.submit(d, p, n_iter=n))["status"] == 0
+        assert S.stats()["geometries_cached"] == 1 and S.stats()["bytes_in_use"] == geo
     S.close()
 
 
