@@ -39,7 +39,7 @@
 //            (eqn:gradRD), mu (Sec. III-B) and FP64 partials of sum mu.
 //            In a single-request subiteration its blocks (pen3.h) run in the
 //            back-projector's launch.
-//   k_upd3   the update of k_update on 64 x 32 (x, z) tiles, also writing
+//   k_upd3   the update of k_update on 32 x 32 (x, z) tiles, also writing
 //            the z-fastest copy through LDS; FP64 partials of sum f.
 //   k_prep3  the z-fastest copy and the sum-f partials of a caller's image
 //            (the same tiles and summation order as k_upd3).
@@ -1037,11 +1037,11 @@ constexpr int U3X = 32, U3Z = 32;
 constexpr int U3R = NT / U3X;          // slices at a time
 
 // update == false: only copy f into fz and write the partials of sum f
-__device__ void upd3_body(const Upd3Args& A, long long vblock, bool update) {
+__device__ void upd3_body(const Upd3Args& A, unsigned vblock, bool update) {
     __shared__ float s_t[U3X * (U3Z + 1)];
     __shared__ double s_red[NT / 64];
-    const int nxt = (A.nx + U3X - 1) / U3X;
-    long long t = vblock;
+    const unsigned nxt = (A.nx + U3X - 1) / U3X;
+    unsigned t = vblock;
     const int xt = (int)(t % nxt);
     t /= nxt;
     const int y = (int)(t % A.ny);
@@ -1123,8 +1123,15 @@ __device__ void upd3_body(const Upd3Args& A, long long vblock, bool update) {
     write_partial(part, A.red_f, s_red, vblock);
 }
 
-__global__ __launch_bounds__(NT) void k_upd3(Upd3Args A) { upd3_body(A, blockIdx.x, true); }
-__global__ __launch_bounds__(NT) void k_prep3(Upd3Args A) { upd3_body(A, blockIdx.x, false); }
+// (tiles in rows of the grid where they are too many for one: upd3_dim)
+__global__ __launch_bounds__(NT) void k_upd3(Upd3Args A, unsigned n) {
+    const unsigned b = blockIdx.y * gridDim.x + blockIdx.x;
+    if (b < n) upd3_body(A, b, true);
+}
+__global__ __launch_bounds__(NT) void k_prep3(Upd3Args A, unsigned n) {
+    const unsigned b = blockIdx.y * gridDim.x + blockIdx.x;
+    if (b < n) upd3_body(A, b, false);
+}
 
 // ------------------------------------------------------------------ host side
 
@@ -1377,13 +1384,17 @@ static void fill_upd3(const pet_os_geom* G, const UpdLaunch& L, Upd3Args& a) {
     a.osem_sens = L.osem_sens;
 }
 
+// a launch holds fewer than 2^32 threads along x (2^24 tiles: an image of 2^29
+// pixels and one slice, or 2^23 rows of more than 64 pixels)
+static dim3 upd3_dim(int n) { return n < (1 << 22) ? dim3(n) : dim3(1 << 22, (n + (1 << 22) - 1) >> 22); }
+
 int launch_update3(const pet_os_geom* G, const UpdLaunch& L, hipStream_t s) {
     Upd3Args a;
     fill_upd3(G, L, a);
     const int grid = upd3_grid(G);
     if (grid > L.red_f.cap) return fail(PET_OS_ERR_DEVICE, "sum partials too small");
     if (L.fz == nullptr) return fail(PET_OS_ERR_DEVICE, "3D update without z copy");
-    petos_launch(k_upd3, dim3(grid), dim3(NT), 0, s, a);
+    petos_launch(k_upd3, upd3_dim(grid), dim3(NT), 0, s, a, (unsigned)grid);
     PETOS_HIP(hipGetLastError());
     return PET_OS_OK;
 }
@@ -1397,7 +1408,7 @@ int launch_prep3(const pet_os_geom* G, const float* f, float* fz, Reduction red,
     fill_upd3(G, L, a);
     const int grid = upd3_grid(G);
     if (grid > red.cap) return fail(PET_OS_ERR_DEVICE, "sum partials too small");
-    hipLaunchKernelGGL(k_prep3, dim3(grid), dim3(NT), 0, s, a);
+    hipLaunchKernelGGL(k_prep3, upd3_dim(grid), dim3(NT), 0, s, a, (unsigned)grid);
     PETOS_HIP(hipGetLastError());
     return PET_OS_OK;
 }

@@ -946,14 +946,16 @@ bool fp3q_ok(const pet_os_geom* G) { return G->d.dim == 3 && G->d.nz <= 64; }
 // narrower than two: bins finer than 0.71 of a square voxel do not qualify),
 // that the staged rows fit LDS, and that the layout's zeros (few unless nearly
 // every ring pair is measured) keep the subset sinogram below 2.2 times its
-// bins; other geometries keep the column tiles of k_bp3.  Where it qualifies it
+// bins, and that its tiles and the image's make a launch (2^32 threads; an image
+// of 2^28 columns takes half of them); other geometries keep the column tiles of
+// k_bp3.  Where it qualifies it
 // is the faster at every size and ring difference tried: 15.6 against 23.9 us
 // at 60x59x12 to difference 1, 61.6 against 91.2 at 170x169x64 to 8.
 bool quad_ok(const pet_os_geom* G) {
     const auto& d = G->d;
     return fp3q_ok(G) && std::sqrt(d.vx * d.vx + d.vy * d.vy) < 1.999 * d.ds &&
            2 * (size_t)bq_buf(G) * sizeof(float4) <= BQ_LDS_MAX &&
-           5 * quad_floats(G, 1) <= 11 * (size_t)G->n_planes * d.n_radial;
+           5 * quad_floats(G, 1) <= 11 * (size_t)G->n_planes * d.n_radial && (int64_t)d.nx * d.ny <= (int64_t)1 << 28;
 }
 
 int fp3q_grid(const pet_os_geom* G, int n_al) { return fq_grid(G, n_al); }
@@ -1072,11 +1074,15 @@ __global__ __launch_bounds__(NT) void k_pack3q(GeoK g, const float* __restrict__
     for (int e = threadIdx.x; e < n; e += NT) out[e] = s_q[e + e / nz];
 }
 
-// out (natural) from z (z fastest), or z + beta out, tiles of 32 x 32
+// out (natural) from z (z fastest), or z + beta out, tiles of 32 x 32 (a block
+// per row y, TURN_Y of them along the grid's y, which holds 65535)
+constexpr int TURN_Y = 32768;
 __global__ __launch_bounds__(NT) void k_turn3(const float* __restrict__ z, float* __restrict__ out, int nx, int ny,
                                               int nz, int add, float beta) {
     __shared__ float s_t[32][33];
-    const int x0 = blockIdx.x * 32, z0 = blockIdx.y * 32, y = blockIdx.z, l = threadIdx.x % 32;
+    const int tz = (nz + 31) / 32, z0 = (blockIdx.z % tz) * 32, y = (blockIdx.z / tz) * TURN_Y + blockIdx.y;
+    const int x0 = blockIdx.x * 32, l = threadIdx.x % 32;
+    if (y >= ny) return;
     for (int k = threadIdx.x / 32; k < 32; k += NT / 32)
         if (x0 + k < nx && z0 + l < nz) s_t[k][l] = z[((long long)y * nx + x0 + k) * nz + z0 + l];
     __syncthreads();
@@ -1089,7 +1095,8 @@ __global__ __launch_bounds__(NT) void k_turn3(const float* __restrict__ z, float
 
 int launch_turn3(const pet_os_geom* G, const float* z, float* out, const float* beta, hipStream_t s) {
     const auto& d = G->d;
-    hipLaunchKernelGGL(k_turn3, dim3((d.nx + 31) / 32, (d.nz + 31) / 32, d.ny), dim3(NT), 0, s, z, out, d.nx, d.ny, d.nz,
+    const int rows = std::min(d.ny, TURN_Y), turns = (d.ny + TURN_Y - 1) / TURN_Y;
+    hipLaunchKernelGGL(k_turn3, dim3((d.nx + 31) / 32, rows, (d.nz + 31) / 32 * turns), dim3(NT), 0, s, z, out, d.nx, d.ny, d.nz,
                        beta != nullptr, beta != nullptr ? *beta : 0.0f);
     PETOS_HIP(hipGetLastError());
     return PET_OS_OK;

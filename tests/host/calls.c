@@ -196,11 +196,36 @@ static void failed_step(void) {
     }
 }
 
+/* Images of more rows than a grid's y and z hold. */
+static void large_grids(void) {
+    pet_os_geom_desc d;
+    memset(&d, 0, sizeof(d));
+    d.dim = 3;
+    d.nx = 3;
+    d.ny = 70001;
+    d.nz = d.n_rings = 33;
+    d.vx = d.vy = d.ds = 2.0;
+    d.vz = d.ring_pitch = 2.5;
+    d.n_angles = 8;
+    d.n_radial = 301;
+    d.max_ring_diff = 1;
+    d.det_radius = 1e5;
+    d.n_subsets = 2;
+    pet_os_geom* g = NULL;
+    pet_os_params p = params();
+    double phi;
+    CHECK(pet_os_create_geometry(&d, &g) == PET_OS_OK);
+    CHECK(pet_os_back(g, buf, 0, buf, A) == PET_OS_OK && stub_launches_of("k_turn3") == 1);
+    CHECK(pet_os_subset_gradient(g, &p, buf, buf, buf, 1, buf, A) == PET_OS_OK && stub_launches_of("k_turn3") == 2);
+    CHECK(pet_os_objective(g, &p, buf, buf, buf, &phi, A) == PET_OS_OK);
+    CHECK(pet_os_reconstruct(g, &p, buf, buf, buf, 1, NULL, A) == PET_OS_OK);
+}
+
 int main(int argc, char** argv) {
     static const struct { const char* name; void (*run)(void); } all[] = {
         {"failed_call", failed_call}, {"memory_kept", memory_kept}, {"streams", streams},
         {"asynchronous", asynchronous}, {"beside_a_capture", beside_a_capture},
-        {"failed_step", failed_step}};
+        {"failed_step", failed_step}, {"large_grids", large_grids}};
     for (size_t k = 0; argc > 1 && k < sizeof(all) / sizeof(all[0]); ++k)
         if (!strcmp(argv[1], all[k].name)) {
             all[k].run();

@@ -68,3 +68,8 @@ def test_a_failed_batch_step_is_taken_up_again(program):
     """A launch that fails, at every place of two batched steps: the steps before
     it are counted, and running on updates each request once per step."""
     run(program, "failed_step")
+
+
+def test_launches_of_images_with_many_rows(program):
+    """Every launch for an image of 70001 rows is within the limits of a grid."""
+    run(program, "large_grids")
