@@ -367,9 +367,12 @@ int pet_os_reconstruct_batch(int32_t n, const pet_os_geom* const* geoms, const p
  * this geometry's first subset and keeps the fastest for all later launches
  * with this geometry (plain and batched).  In 3D it times the single-request
  * back-projector's slices per block (16, 32, 64) and ring differences staged
- * together (4, 8) instead; batched 3D launches keep their fixed shape.  The
- * default shape is timed first and another replaces it only when at least
- * 3 % faster.  flags bit 0: ignore the cache.
+ * together (4, 8) instead, of the back-projector of geometries that do not go
+ * by quads of mirror rays (bins finer than 0.71 of a voxel, more than 64
+ * slices); where they do, nothing is timed and the shape, which the smallest
+ * calls still use, stays the default or a cached one.  Batched 3D launches keep
+ * their fixed shape.  The default shape is timed first and another replaces it
+ * only when at least 3 % faster.  flags bit 0: ignore the cache.
  * When the environment variable PET_OS_TUNE_CACHE names a file, results are
  * read from / appended to it keyed by the geometry descriptor.  Synchronous. */
 int pet_os_autotune(pet_os_geom* geom, int32_t flags, pet_os_stream stream);
@@ -378,7 +381,8 @@ int pet_os_autotune(pet_os_geom* geom, int32_t flags, pet_os_stream stream);
  * (defaults[4]), each as {forward-projector threads per ray (2D; 0 in 3D),
  * back-projector tile kind (2D: 0 = 16x16, 1 = 8x8 with four angle groups;
  * 3D: 2), 3D slices per block, 3D ring differences per staging group (0 in
- * 2D)}.  Host only; either array may be NULL. */
+ * 2D)}; in 3D those of the back-projector that pet_os_autotune times.  Host
+ * only; either array may be NULL. */
 int pet_os_geometry_shapes(const pet_os_geom* geom, int32_t* current, int32_t* defaults);
 
 /* ------------------------------------------------------------------------

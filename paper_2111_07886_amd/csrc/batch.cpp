@@ -650,7 +650,7 @@ extern "C" int pet_os_geometry_shapes(const pet_os_geom* g, int32_t* current, in
 // 3D: the single-request back-projector's slices per block (16, 32, 64, at
 // most the default) and ring differences per staging group (4, 8), timed on
 // the first subset; the forward projector has a single shape.  Cached as
-// "0 <zb * 16 + dpg>".
+// "0 <zb * 16 + dpg>".  (Nothing is timed where subiterations go by quads.)
 static int autotune3(pet_os_geom* g, GeomExtra* ex, int32_t flags, hipStream_t s) {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     const std::string key = tune_key(g->d);
@@ -666,6 +666,10 @@ static int autotune3(pet_os_geom* g, GeomExtra* ex, int32_t flags, hipStream_t s
             return PET_OS_OK;
         }
     }
+    // The shapes are k_bp3's: where the quad back-projector takes the geometry
+    // (no shape to choose) k_bp3 is left the smallest calls and those under
+    // capture, for which the default serves.
+    if (quad_ok(g)) return PET_OS_OK;
     // + 4 floats: the 3D back-projector's 16-byte staging loads may read up to
     // three bins past the last row
     const size_t nw = (size_t)g->max_sub_angles * g->n_planes * g->d.n_radial;

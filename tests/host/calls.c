@@ -221,11 +221,25 @@ static void large_grids(void) {
     CHECK(pet_os_reconstruct(g, &p, buf, buf, buf, 1, NULL, A) == PET_OS_OK);
 }
 
+/* The 3D autotuner times only shapes that subiterations can use. */
+static void autotune(void) {
+    int32_t now[4], def[4];
+    pet_os_geom* g = geometry(64, 16, 64, 3, 8);        /* by quads */
+    const long before = stub_launches, mallocs = stub_mallocs;
+    CHECK(pet_os_autotune(g, 1, A) == PET_OS_OK);
+    CHECK(stub_launches == before && stub_mallocs == mallocs);
+    CHECK(pet_os_geometry_shapes(g, now, def) == PET_OS_OK && !memcmp(now, def, sizeof(now)));
+    pet_os_geom* deep = geometry(24, 70, 24, 3, 8);     /* not */
+    const long made = stub_launches;
+    CHECK(pet_os_autotune(deep, 1, A) == PET_OS_OK && stub_launches > made);
+}
+
 int main(int argc, char** argv) {
     static const struct { const char* name; void (*run)(void); } all[] = {
         {"failed_call", failed_call}, {"memory_kept", memory_kept}, {"streams", streams},
         {"asynchronous", asynchronous}, {"beside_a_capture", beside_a_capture},
-        {"failed_step", failed_step}, {"large_grids", large_grids}};
+        {"failed_step", failed_step}, {"large_grids", large_grids},
+        {"autotune", autotune}};
     for (size_t k = 0; argc > 1 && k < sizeof(all) / sizeof(all[0]); ++k)
         if (!strcmp(argv[1], all[k].name)) {
             all[k].run();

@@ -73,3 +73,8 @@ def test_a_failed_batch_step_is_taken_up_again(program):
 def test_launches_of_images_with_many_rows(program):
     """Every launch for an image of 70001 rows is within the limits of a grid."""
     run(program, "large_grids")
+
+
+def test_the_autotuner_times_what_subiterations_use(program):
+    """No trial launches for a 3D geometry whose subiterations go by quads."""
+    run(program, "autotune")
