@@ -1152,7 +1152,7 @@ int pet_os_default_U(const pet_os_geom* g, const float* f0, const float* y, cons
     if (!g || !f0 || !y || !r || !U) return fail(PET_OS_ERR_INVALID_ARG, "NULL argument");
     hipStream_t s = (hipStream_t)stream;
     Work w;
-    int rc = work_alloc(g, false, &w, true);
+    int rc = work_alloc(g, false, &w, true, false, nullptr, false);
     if (rc) return rc;
     rc = launch_sum(y, g->n_bins, w.red[RED_SUMY], s);
     if (!rc) rc = launch_finalize(w.red[RED_SUMY], elem_grid(g->n_bins), s);
@@ -1445,7 +1445,7 @@ int pet_os_nnz(const pet_os_geom* g, int32_t subset, int64_t* nnz) {
     const int n_al = subset == 0 ? g->d.n_angles : ex->subset_count[subset - 1];
     const int64_t n = (int64_t)n_al * g->n_planes * g->d.n_radial;
     Work w;
-    int rc = work_alloc(g, false, &w, true);
+    int rc = work_alloc(g, false, &w, true, false, nullptr, false);
     if (rc) return rc;
     float* cnt = nullptr;
     if (!device_alloc((void**)&cnt, (size_t)n * sizeof(float))) {
