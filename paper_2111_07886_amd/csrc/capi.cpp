@@ -760,12 +760,12 @@ static int prof_end(hipEvent_t end, hipStream_t s) {
 
 // 3D: the bin-major copy of (y, r) that the quad forward projector reads
 // (its y and r loads are then coalesced), made when the state first sees the
-// pair of buffers, as the data check is.  A state that may not allocate (the
+// pair of buffers, as the data check is (a whole call's state sees one pair).  A state that may not allocate (the
 // static-scratch entry point), or whose allocation fails, reads y and r in
 // their natural layout instead.
 static int ensure_yr(pet_os_state* st, const float* y, const float* r, hipStream_t s) {
     const pet_os_geom* g = st->g;
-    if (!st->may_allocate || !fp3_reads_yr(g)) return PET_OS_OK;
+    if (!st->may_allocate || !fp3_reads_yr(g, st->w.kept)) return PET_OS_OK;
     if (st->yr != nullptr && st->yr_y == y && st->yr_r == r) return PET_OS_OK;
     if (st->yr == nullptr) {
         const size_t bytes = (size_t)g->n_bins * sizeof(float2);

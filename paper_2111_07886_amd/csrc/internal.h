@@ -180,9 +180,10 @@ struct FPLaunch {
 };
 int launch_fp(const pet_os_geom* g, const FPLaunch& L, hipStream_t s);
 // 3D: the bin-major copy of y and r that the quad forward projector reads
-// (yr: n_bins pairs); whether the geometry's forward projector uses it
+// (yr: n_bins pairs); whether the geometry's forward projector uses it, in a
+// state or in a whole call
 int launch_yr3(const pet_os_geom* g, const float* y, const float* r, float2* yr, hipStream_t s);
-bool fp3_reads_yr(const pet_os_geom* g);
+bool fp3_reads_yr(const pet_os_geom* g, bool whole_call);
 
 enum NuMode { NU_ONE = 0, NU_COMPUTE = 1, NU_COMPUTE_FREEZE = 2, NU_FROZEN = 3 };
 

@@ -1234,9 +1234,12 @@ int bp3_shape_single(const pet_os_geom* G, int zb, int dpg_req, int& nb, int& rw
     return PET_OS_OK;
 }
 
-// (only up to 15 ring differences: a state keeps its copy while the same
-// buffers come back, and with more it reads whatever they hold)
-bool fp3_reads_yr(const pet_os_geom* G) { return fp3q_ok(G) && G->d.max_ring_diff <= 15; }
+// (a state keeps its copy while the same buffers come back; with more than 15
+// ring differences only that of a whole call, whose buffers hold still, has one:
+// the others read whatever the buffers hold)
+bool fp3_reads_yr(const pet_os_geom* G, bool whole_call) {
+    return fp3q_ok(G) && (whole_call || G->d.max_ring_diff <= 15);
+}
 
 // yr[(a * n_radial + b) * n_planes + plane] = (y, r)[(plane * n_angles + a) *
 // n_radial + b]: a transpose of [plane][angle-bin] by 64 x 64 tiles through
