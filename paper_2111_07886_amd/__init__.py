@@ -414,7 +414,7 @@ def reconstruct(geom: Geometry, params: dict, f, y, r, n_iter: int, want_objecti
     return list(obj) if want_objective else None
 
 
-NOALLOC_SCRATCH_BYTES = 64 << 20      # PET_OS_NOALLOC_SCRATCH_BYTES
+NOALLOC_SCRATCH_BYTES = 96 << 20      # PET_OS_NOALLOC_SCRATCH_BYTES
 
 
 def reconstruct_noalloc(geom: Geometry, params: dict, f, y, r, n_iter: int, stream=None):

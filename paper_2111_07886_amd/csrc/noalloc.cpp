@@ -3,8 +3,8 @@
 // callers that cannot allocate device memory.
 //
 // The array below is this library's own global in device memory: every GPU
-// the library runs on holds one copy of PET_OS_NOALLOC_SCRATCH_BYTES until the
-// process ends.  Host code never uses its name as an address: at a device's
+// the library runs on holds one copy (SCRATCH_BYTES, 216 MiB) until the process
+// ends.  Host code never uses its name as an address: at a device's
 // first call the device address of that device's copy is looked up once
 // (hipGetSymbolAddress) and kept, and only that address reaches kernels and
 // fills.  Every call on a GPU shares the GPU's copy, so calls that overlap on
@@ -20,8 +20,10 @@
 namespace {
 
 // A request is accepted by its scratch with the subset sinogram bin by bin, at
-// most PET_OS_NOALLOC_SCRATCH_BYTES; the 3D projectors' layout of the sinogram
-// takes up to 2.2 times the bins' floats (quad_ok).
+// most PET_OS_NOALLOC_SCRATCH_BYTES (96 MiB); the 3D projectors' layout of the
+// sinogram takes up to 2.2 times the bins' floats (quad_ok).  120 MiB more than
+// the requests that fit need bin by bin, so that each of them gives the bits of
+// pet_os_reconstruct, which goes by quads.
 constexpr size_t SCRATCH_BYTES = (size_t)PET_OS_NOALLOC_SCRATCH_BYTES / 4 * 9;
 static __device__ __align__(256) char scratch[SCRATCH_BYTES];
 
