@@ -43,7 +43,6 @@ struct BatchSlot {
     int* d_nu = nullptr;
     bool owned = true;               // w, d_step and d_nu are this slot's (else parts of the batch's slab)
     int fp_seg = 1, bp_kind = 0;
-    bool quad = false;               // 3D: w in quads of mirror rays
     size_t bytes = 0;
 };
 
@@ -154,7 +153,7 @@ int rebuild_lists(pet_os_batch* B) {
         const bool d3 = S.g->d.dim == 3;
         // 2D: forward blocks, then the pixel-pass blocks (snapshot, mu)
         // (the forward projector that gives the bits of a request alone)
-        const bool quad = S.quad, fq = d3 && fp3q_ok(S.g) && (quad || !fp3s_better(S.g));
+        const bool quad = S.w.quads, fq = d3 && fp3q_ok(S.g) && (quad || !fp3s_better(S.g));
         const int wide = S.g->d.nz > 32 ? 1 : 0;
         const int nfp = fq ? fp3q_grid(S.g, S.g->max_sub_angles)
                         : d3 ? fp3_grid(S.g, S.g->max_sub_angles)
@@ -253,7 +252,7 @@ int slot_record(BatchSlot& S, const GeomExtra* ex, SlotDev& D) {
     D.box = make_box(p->U, p->t_clip);
     D.fp_seg = S.fp_seg;
     D.bp_kind = S.bp_kind;
-    if (S.quad) {
+    if (S.w.quads) {
         D.quad = 1;
         D.rows_max = bp3q_rows(g);
         D.chunk = bp3q_buf(g);
@@ -286,11 +285,19 @@ int add_together(pet_os_batch* B, int n, const pet_os_geom* const* geoms, const 
     bytes += up(subs * (sizeof(float) + sizeof(int)));
     std::vector<size_t> o_work(m);
     auto need_nu = [&](int k) { return params[k].mode == PET_OS_P1 || params[k].mode == PET_OS_P2; };
-    for (int k = 0; k < m; ++k) {
-        o_work[k] = bytes;
-        bytes += up(work_bytes(geoms[k], need_nu(k)));
+    // (where only the 3D quads' room is missing, bin by bin)
+    const size_t o_slots = bytes;
+    bool quads = true;
+    for (int tries = 0; tries < 2 && B->slab == nullptr; ++tries) {
+        quads = tries == 0;
+        bytes = o_slots;
+        for (int k = 0; k < m; ++k) {
+            o_work[k] = bytes;
+            bytes += up(work_bytes(geoms[k], need_nu(k), quads));
+        }
+        (void)device_alloc(&B->slab, bytes);
     }
-    if (!device_alloc((void**)&B->slab, bytes)) return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of scratch failed");
+    if (B->slab == nullptr) return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of scratch failed");
     char* base = (char*)B->slab;
     auto* totals = (unsigned long long*)base;
     std::vector<char> sched(subs * (sizeof(float) + sizeof(int)));
@@ -307,8 +314,7 @@ int add_together(pet_os_batch* B, int n, const pet_os_geom* const* geoms, const 
         S.y = y[k];
         S.r = r[k];
         S.J_end = (int64_t)n_iter[k] * S.g->d.n_subsets;
-        S.quad = quad_ok(S.g);
-        work_carve_at(S.g, need_nu(k), base + o_work[k], &S.w);
+        work_carve_at(S.g, need_nu(k), quads, base + o_work[k], &S.w);
         rc = check_launch(S.g, &S.p, S.w.check_part, totals + 4 * (size_t)k, S.f, S.y, S.r, st);
         if (!rc) rc = launch_sum_f(S.g, S.f, S.w.fz, S.w.red[RED_SUMF], st);
         schedule_table(S.p, S.g->d.n_subsets, S.J_end, step, nu);
@@ -412,8 +418,7 @@ int petos::batch_add(pet_os_batch* B, const pet_os_geom* g, const pet_os_params*
     S.J_next = 1;
     S.J_end = (int64_t)n_iter * M;
     const bool need_nu = p->mode == PET_OS_P1 || p->mode == PET_OS_P2;
-    S.quad = quad_ok(g) && !compact;
-    rc = work_alloc(g, need_nu, &S.w, false, false, nullptr, S.quad);
+    rc = work_alloc(g, need_nu, &S.w, false, false, nullptr, !compact);
     if (rc) return rc;
     if ((rc = check_data(g, p, &S.w, f, y, r, st))) {
         work_free(&S.w);

@@ -462,7 +462,7 @@ namespace petos {
 struct WorkLayout {
     size_t o_w, o_G, o_mu, o_nu, o_fz, o_snap, o_fb, o_red[RED_COUNT], o_tot, o_chk, o_chkt, bytes;
     int caps[RED_COUNT];
-    bool need_nu, d3, psf;
+    bool need_nu, d3, psf, quads;
 };
 
 // sums: with the partials of the sums over all bins; quads: the subset
@@ -477,7 +477,8 @@ static WorkLayout work_layout(const pet_os_geom* g, bool need_nu, bool sums, boo
     // + 4 floats: the 3D back-projector's 16-byte staging loads may read up to
     // three bins past the last row
     const size_t compact = (size_t)g->max_sub_angles * g->n_planes * g->d.n_radial + 4;
-    L.o_w = cv.take<float>(quads && quad_ok(g) ? std::max(compact, quad_floats(g, g->max_sub_angles)) : compact);
+    L.quads = quads && quad_ok(g);
+    L.o_w = cv.take<float>(L.quads ? std::max(compact, quad_floats(g, g->max_sub_angles)) : compact);
     L.o_G = cv.take<float>(nv);
     L.o_mu = cv.take<float>(nv);
     L.o_nu = need_nu ? cv.take<float>(nv) : 0;
@@ -503,6 +504,7 @@ static WorkLayout work_layout(const pet_os_geom* g, bool need_nu, bool sums, boo
 static void work_carve(const WorkLayout& L, char* blk, Work* w) {
     *w = Work{};
     w->bytes = L.bytes;
+    w->quads = L.quads;
     w->red_block = (double*)blk;
     w->w = (float*)(blk + L.o_w);
     w->G = (float*)(blk + L.o_G);
@@ -521,10 +523,12 @@ static void work_carve(const WorkLayout& L, char* blk, Work* w) {
     }
 }
 
-size_t work_bytes(const pet_os_geom* g, bool need_nu) { return work_layout(g, need_nu, false).bytes; }
+size_t work_bytes(const pet_os_geom* g, bool need_nu, bool quads) {
+    return work_layout(g, need_nu, false, quads).bytes;
+}
 
-void work_carve_at(const pet_os_geom* g, bool need_nu, void* base, Work* w) {
-    work_carve(work_layout(g, need_nu, false), (char*)base, w);
+void work_carve_at(const pet_os_geom* g, bool need_nu, bool quads, void* base, Work* w) {
+    work_carve(work_layout(g, need_nu, false, quads), (char*)base, w);
 }
 
 size_t work_bytes_of(const pet_os_geom_desc& d, int n_planes, int max_sub, bool need_nu, bool quads) {
@@ -540,17 +544,16 @@ size_t work_bytes_of(const pet_os_geom_desc& d, int n_planes, int max_sub, bool 
 int work_alloc(const pet_os_geom* g, bool need_nu, Work* w, bool sums, bool keep, const hipStream_t* s, bool quads) {
     *w = Work{};
     const WorkLayout L = work_layout(g, need_nu, sums, quads);
-    char* blk = nullptr;
-    if (keep) {
-        blk = (char*)scratch_take(L.bytes, s);
-        if (!blk) return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of scratch failed");
-        work_carve(L, blk, w);
-        w->kept = true;
-        return PET_OS_OK;
-    }
-    if (!device_alloc((void**)&blk, L.bytes)) return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of scratch failed");
-    work_carve(L, blk, w);
-    if (hipMemset(blk + L.o_tot, 0, RED_COUNT * sizeof(double)) != hipSuccess) {
+    void* blk = nullptr;
+    if (keep) blk = scratch_take(L.bytes, s);
+    else (void)device_alloc(&blk, L.bytes);
+    // (where only the quads' room is missing, bin by bin)
+    if (blk == nullptr && L.quads) return work_alloc(g, need_nu, w, sums, keep, s, false);
+    if (blk == nullptr) return fail(PET_OS_ERR_OUT_OF_MEMORY, "hipMalloc of scratch failed");
+    work_carve(L, (char*)blk, w);
+    w->kept = keep;
+    if (keep) return PET_OS_OK;
+    if (hipMemset((char*)blk + L.o_tot, 0, RED_COUNT * sizeof(double)) != hipSuccess) {
         (void)hipFree(blk);
         *w = Work{};
         return fail(PET_OS_ERR_DEVICE, "scratch init failed");
@@ -805,7 +808,7 @@ static int run_subiteration(pet_os_state* st, float* f, const float* y, const fl
     F.f = f; F.fz = st->w.fz; F.y = y; F.r = r; F.out = st->w.w; F.angles = angles; F.n_al = n_al;
     if (d3 && (rc = ensure_yr(st, y, r, s))) return rc;
     F.yr = (d3 && st->yr != nullptr && st->yr_y == y && st->yr_r == r) ? st->yr : nullptr;
-    F.quad = quad_ok(g) ? 1 : 0;
+    F.quad = st->w.quads ? 1 : 0;
     const bool osem = st->p.mode == PET_OS_OSEM;
     const float* sens_i = osem ? st->osem_sens + (size_t)(st->i - 1) * g->n_vox : nullptr;
     F.mode = osem ? FP_EM : FP_RATIO;
@@ -1196,8 +1199,12 @@ int pet_os_subset_gradient(const pet_os_geom* g, const pet_os_params* p, const f
     float* big = nullptr;
     if (n_al > g->max_sub_angles) {
         // + 4 floats of padding for the 3D back-projector's 16-byte staging loads
-        const size_t n = quad_ok(g) ? quad_floats(g, n_al) : (size_t)n_al * g->n_planes * g->d.n_radial + 4;
-        big = (float*)scratch_take(sizeof(float) * n, &s);
+        const size_t n = (size_t)n_al * g->n_planes * g->d.n_radial + 4;
+        if (w.quads) big = (float*)scratch_take(sizeof(float) * quad_floats(g, n_al), &s);
+        if (!big) {
+            w.quads = false;
+            big = (float*)scratch_take(sizeof(float) * n, &s);
+        }
         if (!big) {
             (void)hipStreamSynchronize(s);      // w's block may only be ordered after its last user, on s
             work_free(&w);
@@ -1209,7 +1216,7 @@ int pet_os_subset_gradient(const pet_os_geom* g, const pet_os_params* p, const f
     FPLaunch F{};
     F.f = f; F.fz = w.fz; F.y = y; F.r = r; F.out = wsino; F.angles = angles; F.n_al = n_al;
     F.mode = FP_RATIO;
-    F.quad = quad_ok(g) ? 1 : 0;
+    F.quad = w.quads ? 1 : 0;
     F.seg = fp_seg_for(g, (long long)n_al * g->n_planes * g->d.n_radial, g->tuned_seg);
     const bool psf = g->d.dim == 2 && g->k.psf_kx > 0;
     if (psf && !rc) {

@@ -98,6 +98,7 @@ struct Work {
     unsigned* check_part = nullptr;            // data check: per-block counts [CHECK_GRID][4]
     unsigned long long* check_total = nullptr; // data check: the four totals
     size_t bytes = 0;
+    bool quads = false;                        // 3D: w has room for quads of mirror rays (and so holds them)
     bool kept = false;                         // of a whole call: work_free gives it back (scratch_give)
 };
 
@@ -113,8 +114,9 @@ void scratch_release();                       // free the idle blocks
 bool device_alloc(void** p, size_t bytes);    // hipMalloc, with the idle blocks freed if it fails
 
 // sums: with the partials of the sums over all bins (default U, nnz)
-// (keep: the scratch of a whole call, from and to the kept blocks; quads: room
-// for the subset sinogram as quads where the geometry takes them)
+// (keep: the scratch of a whole call, from and to the kept blocks; quads: with
+// room for the subset sinogram as quads where the geometry takes them and there
+// is the memory, Work::quads)
 int work_alloc(const pet_os_geom* g, bool need_nu, Work* w, bool sums = false, bool keep = false,
                const hipStream_t* s = nullptr, bool quads = true);
 // its bytes, from a descriptor
@@ -124,8 +126,9 @@ void work_free(Work* w);
 // memory at base (cap bytes, 256-byte aligned): no allocation; the reduction
 // totals are cleared by a fill kernel on s.  Requests of more than `most`
 // bytes with the subset sinogram bin by bin are refused, whatever its layout.
-size_t work_bytes(const pet_os_geom* g, bool need_nu);
-void work_carve_at(const pet_os_geom* g, bool need_nu, void* base, Work* w);   // (work_bytes there, nothing cleared)
+size_t work_bytes(const pet_os_geom* g, bool need_nu, bool quads);
+// (work_bytes there, nothing cleared)
+void work_carve_at(const pet_os_geom* g, bool need_nu, bool quads, void* base, Work* w);
 int work_place(const pet_os_geom* g, bool need_nu, void* base, size_t cap, size_t most, Work* w, hipStream_t s);
 
 // device angle lists of a geometry

@@ -234,12 +234,41 @@ static void autotune(void) {
     CHECK(pet_os_autotune(deep, 1, A) == PET_OS_OK && stub_launches > made);
 }
 
+/* Memory for the subset sinogram bin by bin, but not as quads, is enough. */
+static void memory_limits(void) {
+    pet_os_geom* g = geometry(32, 24, 64, 23, 1);
+    pet_os_params p = params();
+    const size_t compact = (size_t)64 * 24 * 24 * 49 * 4, quads = (size_t)4 * 64 * 24 * 25 * 24 * 4;
+    const size_t images = (size_t)5 * 32 * 32 * 24 * 4 + (1 << 20);
+    CHECK(quads > compact + images);
+    const size_t limit = stub_live + compact + images;
+    const int columns = stub_launches_of("k_bp3I");
+    stub_limit = limit;
+    pet_os_state* st = NULL;
+    CHECK(pet_os_state_create(g, &p, &st) == PET_OS_OK);
+    hipGetLastError();
+    CHECK(pet_os_subiteration(st, buf, buf, buf, A) == PET_OS_OK && stub_launches_of("k_bp3I") == columns + 1);
+    CHECK(pet_os_state_destroy(st) == PET_OS_OK);
+    CHECK(pet_os_reconstruct(g, &p, buf, buf, buf, 1, NULL, A) == PET_OS_OK);
+    CHECK(stub_launches_of("k_bp3I") == columns + 2);
+    CHECK(pet_os_subset_gradient(g, &p, buf, buf, buf, 1, buf, A) == PET_OS_OK);
+    CHECK(stub_launches_of("k_bp3I") == columns + 3);
+    const pet_os_geom* gs[1] = {g};
+    float* fs[1] = {buf};
+    const float* ys[1] = {buf};
+    const int32_t n[1] = {1};
+    CHECK(pet_os_reconstruct_batch(1, gs, &p, fs, ys, ys, n, A) == PET_OS_OK);
+    CHECK(stub_launches_of("k_bp3_batch") == 1 && stub_launches_of("k_bp3q") == 0);
+    stub_limit = (size_t)1 << 34;
+    CHECK(pet_os_reconstruct(g, &p, buf, buf, buf, 1, NULL, A) == PET_OS_OK && stub_launches_of("k_bp3q") == 1);
+}
+
 int main(int argc, char** argv) {
     static const struct { const char* name; void (*run)(void); } all[] = {
         {"failed_call", failed_call}, {"memory_kept", memory_kept}, {"streams", streams},
         {"asynchronous", asynchronous}, {"beside_a_capture", beside_a_capture},
         {"failed_step", failed_step}, {"large_grids", large_grids},
-        {"autotune", autotune}};
+        {"autotune", autotune}, {"memory_limits", memory_limits}};
     for (size_t k = 0; argc > 1 && k < sizeof(all) / sizeof(all[0]); ++k)
         if (!strcmp(argv[1], all[k].name)) {
             all[k].run();

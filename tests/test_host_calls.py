@@ -78,3 +78,9 @@ def test_launches_of_images_with_many_rows(program):
 def test_the_autotuner_times_what_subiterations_use(program):
     """No trial launches for a 3D geometry whose subiterations go by quads."""
     run(program, "autotune")
+
+
+def test_memory_for_the_sinogram_bin_by_bin_is_enough(program):
+    """States, reconstructions, gradients and batches that have memory for the
+    subset sinogram bin by bin, but not in the 3D projectors' own layout, run."""
+    run(program, "memory_limits")
