@@ -292,8 +292,10 @@ constexpr int FPS_DPW = 4;              // ring differences per wave at most
 constexpr int FPS_ZS = 64;              // floats per staged column (nz <= 64)
 constexpr int FPS_SLOTS = 128;          // staged columns of a stretch: slot 2k (c0) and 2k + 1 (c0 + qstep) of cell mb + k
 
+// (a launch holds fewer than 2^32 threads: 2^23 bins of all angles)
 static bool fp3s_ok(const pet_os_geom* G) {
-    return G->d.nz <= FPS_ZS && 2 * G->d.max_ring_diff + 1 <= FPS_W * FPS_DPW;
+    return G->d.nz <= FPS_ZS && 2 * G->d.max_ring_diff + 1 <= FPS_W * FPS_DPW &&
+           (int64_t)G->d.n_angles * G->d.n_radial < (int64_t)1 << 23;
 }
 
 // Copy a stretch's columns into s_col: slot 2k holds minor cell c0 of major

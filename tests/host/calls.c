@@ -196,7 +196,8 @@ static void failed_step(void) {
     }
 }
 
-/* Images of more rows than a grid's y and z hold. */
+/* Images of more rows than a grid's y and z hold, and rays of more angles and
+ * bins than a launch of a block each. */
 static void large_grids(void) {
     pet_os_geom_desc d;
     memset(&d, 0, sizeof(d));
@@ -219,6 +220,17 @@ static void large_grids(void) {
     CHECK(pet_os_subset_gradient(g, &p, buf, buf, buf, 1, buf, A) == PET_OS_OK && stub_launches_of("k_turn3") == 2);
     CHECK(pet_os_objective(g, &p, buf, buf, buf, &phi, A) == PET_OS_OK);
     CHECK(pet_os_reconstruct(g, &p, buf, buf, buf, 1, NULL, A) == PET_OS_OK);
+    d.nx = d.ny = 40;
+    d.nz = d.n_rings = 4;
+    d.n_angles = 8200;
+    d.n_radial = 1101;
+    d.max_ring_diff = 0;
+    d.n_subsets = 4;
+    int64_t nnz;
+    CHECK(pet_os_create_geometry(&d, &g) == PET_OS_OK);
+    CHECK(pet_os_forward(g, buf, 0, buf, A) == PET_OS_OK);
+    CHECK(pet_os_objective(g, &p, buf, buf, buf, &phi, A) == PET_OS_OK);
+    CHECK(pet_os_nnz(g, 0, &nnz) == PET_OS_OK);
 }
 
 /* The 3D autotuner times only shapes that subiterations can use. */

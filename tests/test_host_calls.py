@@ -71,7 +71,8 @@ def test_a_failed_batch_step_is_taken_up_again(program):
 
 
 def test_launches_of_images_with_many_rows(program):
-    """Every launch for an image of 70001 rows is within the limits of a grid."""
+    """Every launch for an image of 70001 rows, or for 8200 angles of 1101 bins, is
+    within the limits of a grid."""
     run(program, "large_grids")
 
 
