@@ -868,7 +868,8 @@ def main():
         "config": {"workload": WORKLOADS[args.workload] if not args.mode else
                    WORKLOADS[args.workload].replace("SDP-P2", "OSEM" if args.mode == "OSEM" else "SDP-" + args.mode),
                    "subsets": M, "nnz_per_subset": int(nnz_sub), "rays_per_subset": int(rays_sub),
-                   "voxels": q, "autotuned": not args.no_autotune, "shapes": shapes["current"],
+                   # (the 3D workload goes by quads, which have no shapes to time)
+                   "voxels": q, "autotuned": not args.no_autotune and w.desc["dim"] == 2, "shapes": shapes["current"],
                    "attenuation": w.att is not None,
                    "objective_last": obj[-1] if obj else None,
                    "objective_ms": None if obj_ms is None else round(obj_ms, 4),
