@@ -57,6 +57,7 @@ void free_blocks(std::vector<Block>& old) {
 // (g_mu held) whether the block's work is over
 bool is_done(Block& b) {
     if (b.pending) {
+        const Relaxed relaxed;
         if (hipEventQuery(b.done) == hipSuccess) b.pending = false;
         else (void)hipGetLastError();
     }
@@ -117,7 +118,6 @@ bool device_alloc(void** p, size_t bytes) {
 // or wait for: none if there is no room among the kept ones.
 void* scratch_take(size_t bytes, const hipStream_t* s, bool async) {
     constexpr int QUEUED = 3;
-    const Relaxed relaxed;
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) return nullptr;
     bool kept = false;
@@ -160,6 +160,7 @@ void* scratch_take(size_t bytes, const hipStream_t* s, bool async) {
         if (got.pending && hipStreamWaitEvent(*s, got.done, 0) != hipSuccess) (void)hipEventSynchronize(got.done);
         return got.p;
     }
+    const Relaxed relaxed;
     free_blocks(old);
     void* p = nullptr;
     if (!async) {
@@ -181,7 +182,6 @@ void* scratch_take(size_t bytes, const hipStream_t* s, bool async) {
 }
 
 void scratch_give(void* p, const hipStream_t* after) {
-    const Relaxed relaxed;
     hipEvent_t ev = nullptr;
     bool kept = false;
     {
@@ -194,11 +194,13 @@ void scratch_give(void* p, const hipStream_t* after) {
     }
     bool pending = false;
     if (after) {
+        const Relaxed relaxed;
         pending = kept && (ev != nullptr || hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess) &&
                   hipEventRecord(ev, *after) == hipSuccess;
         if (!pending) (void)hipStreamSynchronize(*after);
     }
     if (!kept) {
+        const Relaxed relaxed;
         (void)hipFree(p);
         return;
     }
